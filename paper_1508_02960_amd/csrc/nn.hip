@@ -48,6 +48,22 @@ __device__ __forceinline__ void store_out(void* out, long long i, float v, int r
     static_cast<float*>(out)[i] = v;
 }
 
+// store_out of four consecutive values as one word (i a multiple of 4, out
+// aligned to the word)
+template <bool ACT>
+__device__ __forceinline__ void store_out4(void* out, long long i, float v0, float v1, float v2,
+                                           float v3, int relu) {
+  if constexpr (ACT) {
+    const uint32_t lo = (uint32_t)f2bf(relu ? fmaxf(v0, 0.f) : v0) |
+                        ((uint32_t)f2bf(relu ? fmaxf(v1, 0.f) : v1) << 16);
+    const uint32_t hi = (uint32_t)f2bf(relu ? fmaxf(v2, 0.f) : v2) |
+                        ((uint32_t)f2bf(relu ? fmaxf(v3, 0.f) : v3) << 16);
+    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + i) = make_uint2(lo, hi);
+  } else {
+    *reinterpret_cast<float4*>(static_cast<float*>(out) + i) = make_float4(v0, v1, v2, v3);
+  }
+}
+
 // voxel index -> (n, z, y, x)
 __device__ __forceinline__ void unflatten(long long m, const Shape& s, int& n, int& z, int& y,
                                           int& x) {
@@ -77,7 +93,9 @@ __device__ __forceinline__ long long neighbour(int n, int z, int y, int x, int t
 // column l % 16.
 constexpr int kPad = 8;
 
-// Tiled forward convolution: block tile 128 voxels x BN output channels
+// Tiled forward convolution for boxes of many tiles that are no multiple of
+// the spatial tile, and for any input the kernels below do not take: block
+// tile 128 voxels x BN output channels
 // (BN = 16, 32 or 64), K = 27 ci staged 64 at a time through LDS.  Each of
 // the 4 wavefronts owns 32 voxel rows (two 16-row MFMA tiles) against all
 // BN/16 column tiles.  The 27 neighbour voxels of the block's 128 rows are
@@ -201,115 +219,387 @@ __global__ __launch_bounds__(256) void conv_fwd_tiled_kernel(const uint16_t* __r
 }
 
 // Spatially tiled forward convolution for ci % 32 == 0 and box edges that
-// are multiples of the tile: each block computes a 4 x 8 x 8 voxel tile
-// (z, y, x; 256 rows of the implicit GEMM) against BN output channels.  The
-// input is taken 32 channels at a time: the 6 x 10 x 10 halo of the tile
-// (periodic wrap) is staged in LDS once per chunk, so each input voxel is
-// fetched about 2.3 times instead of once per tap, and the 27 taps read
-// their A operands from LDS at shifted halo positions.  Wavefront wv owns
-// the z layer wv of the tile (64 rows = 4 MFMA row tiles); B operands (the
-// weights of one tap and 32 channels) come from global memory (L1/L2
-// resident), one tap ahead.
+// are multiples of 4 x 8 x 8 (z, y, x).  The four wavefronts of a block are
+// WZ = 4 / WC z layers times WC groups of 16 NT output channels; a wavefront
+// computes MT MFMA tiles of 16 voxels (TX = 16: one x row each, TX = 8: two x
+// rows of 8), i.e. RPM MT rows of its layer.  The input is taken 32 channels
+// at a time: the halo of the block's tile (periodic wrap) goes straight from
+// global memory to LDS (16 bytes per lane, no registers).
+//
+// The kernel is bound by what feeds the matrix cores, so the work is arranged
+// for operand reuse.  A voxel fragment (16 voxels x 32 channels at one x
+// shift) is read from LDS once per dz and serves every row of the
+// wavefront's patch that it is a dy neighbour of, up to three; the weights of
+// the nine taps of a dz sit in registers and are replaced tap row by tap row
+// as the sweep over the input rows passes their last use.  Per 32 channels a
+// wavefront with MT = 8 then reads 90 voxel and 54 weight fragments for 432
+// MFMAs, against 108 LDS reads per 216 MFMAs for one read per tap and row.
+// Every output still adds its taps in the order dz, dy, dx (the sweep over
+// input rows meets dy = 0, 1, 2 of an output row in that order), so the
+// results do not depend on MT, WC or TX.
+//
+// The weights are the MFMA's row operand: a lane then holds four consecutive
+// output channels of one voxel and stores them as one word.
+//
+// LDS: halo voxel (row R = hz HY + hy, column hx) starts at 64 (R P + hx)
+// bytes, P the row pitch (20 or 12); its four 16-byte channel octets are
+// permuted by (hx >> 1) ^ 2 R (mod 4), so that 8 consecutive voxels of a row
+// read at one octet cover all banks.
+//
+// 96 -> 32 channels at 64^3 x 4 (174 GFLOP), BF16 output: 323 -> 215 us (808
+// TFLOP/s) against one LDS read per tap and row; 192 -> 64 at 32^3 x 4: 172 ->
+// 101 us; 96 -> 32 at one 64^3 box: 105 -> 60 us.
 constexpr int kTZ = 4, kTY = 8, kTX = 8;
 constexpr int kHZ = kTZ + 2, kHY = kTY + 2, kHX = kTX + 2;
 constexpr int kHalo = kHZ * kHY * kHX;  // 600 voxels
 constexpr int kCC = 32;                 // channels per chunk
-constexpr int kHLD = kCC + 8;           // LDS row stride (halfs) of a halo voxel
 
-template <int BN, bool ACT>
-__global__ __launch_bounds__(256) void conv_fwd_spatial_kernel(const uint16_t* __restrict__ x,
-                                                               const uint16_t* __restrict__ w,
-                                                               const float* __restrict__ bias,
-                                                               void* __restrict__ y, Shape s,
-                                                               int ci, int co, int relu) {
-  constexpr int NT = BN / 16;
-  __shared__ __attribute__((aligned(16))) uint16_t Hs[kHalo * kHLD];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  // tile position
-  const int tx_n = s.w / kTX, ty_n = s.h / kTY, tz_n = s.d / kTZ;
-  long long t = blockIdx.x;
-  const int bx = (int)(t % tx_n);
+// 16 bytes per lane from global memory to LDS: lane l's go to lds + 16 l (lds
+// the same in every lane).
+__device__ __forceinline__ void load_to_lds(const void* g, void* lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
+// Consecutive workgroups go to the eight XCDs in turn; work item of block b of
+// n so that each XCD takes a contiguous range of items (neighbouring tiles
+// share halo lines in its L2).
+__device__ __forceinline__ int xcd_item(int b, int n) {
+  return n % 8 ? b : (b % 8) * (n / 8) + b / 8;
+}
+
+template <int TX, int MT, int NT, int WC, bool ACT>
+__global__ __launch_bounds__(256, 2) void conv_fwd_spatial_kernel(const uint16_t* __restrict__ x,
+                                                                  const uint16_t* __restrict__ w,
+                                                                  const float* __restrict__ bias,
+                                                                  void* __restrict__ y, Shape s,
+                                                                  int ci, int co, int relu,
+                                                                  int vec) {
+  constexpr int WZ = 4 / WC, RPM = 16 / TX;
+  constexpr int TY = RPM * MT;                   // rows of the tile
+  constexpr int HZ = WZ + 2, HY = TY + 2, P = TX + 4;
+  static_assert(HY % 2 == 0, "the octet permutation needs an even number of halo rows");
+  constexpr int NQ = (HZ * HY * P * 4 + 63) / 64;  // wavefront loads of a staging pass
+  constexpr int NL = (NQ + 3) / 4;                 // ... per wavefront (at most)
+  __shared__ __attribute__((aligned(16))) unsigned char Hs[NQ * 1024];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wz = wv / WC, wc = wv % WC;
+  // work item: tile (x, then y, then z, then n) and group of 16 NT WC channels
+  const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
+  int t = xcd_item(blockIdx.x, gridDim.x);
+  const int n0 = (t % cgs) * 16 * NT * WC + 16 * NT * wc;
+  t /= cgs;
+  const int tx_n = s.w / TX, ty_n = s.h / TY, tz_n = s.d / WZ;
+  const int x0 = (t % tx_n) * TX;
   t /= tx_n;
-  const int by = (int)(t % ty_n);
+  const int y0 = (t % ty_n) * TY;
   t /= ty_n;
-  const int bz = (int)(t % tz_n);
-  const int bn_ = (int)(t / tz_n);
-  const int x0 = bx * kTX, y0 = by * kTY, z0 = bz * kTZ;
-  const int n0 = blockIdx.y * BN;
-  const int K = 27 * ci;
-  // the lane's rows: row tile rt holds tile rows 16 rt + (lane & 15), i.e.
-  // (tz, ty, tx) = (wv, 2 rt + (lane & 15) / 8, lane & 7)
-  const int lx = lane & 7, ly = (lane & 15) >> 3, oct = lane >> 4;
+  const int z0 = (t % tz_n) * WZ;
+  const int bn_ = t / tz_n;
+  const int col = lane & 15, oct = lane >> 4;
+  const int lx = col & (TX - 1), ly = col / TX;
 
-  f32x4 acc[4][NT];
+  // this lane's source granule (16 bytes of a voxel) of each staging load
+  uint32_t src[NL];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int i = 0; i < NL; ++i) {
+    const int g = (wv + 4 * i) * 64 + lane;
+    const int hv = g >> 2;
+    int R = hv / P, hx = hv - R * P;
+    const int o = (g & 3) ^ ((hx >> 1) & 3) ^ ((R & 1) << 1);
+    if (hx >= TX + 2) hx = 0;      // pitch padding: any voxel
+    if (R >= HZ * HY) R = 0;       // past the halo
+    const int hz = R / HY, hy = R - hz * HY;
+    int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
+    zz = zz < 0 ? zz + s.d : (zz >= s.d ? zz - s.d : zz);
+    yy = yy < 0 ? yy + s.h : (yy >= s.h ? yy - s.h : yy);
+    xx = xx < 0 ? xx + s.w : (xx >= s.w ? xx - s.w : xx);
+    src[i] = (uint32_t)(((bn_ * s.d + zz) * s.h + yy) * s.w + xx) * (uint32_t)(ci >> 3) + (uint32_t)o;
+  }
+  // LDS byte of this lane's 16 bytes of a voxel fragment: x shift dx, row
+  // parity, plus a constant per row
+  int la[3][2];
+#pragma unroll
+  for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+    for (int par = 0; par < 2; ++par)
+      la[dx][par] = ((wz * HY + ly) * P + lx + dx) * 64 +
+                    16 * (oct ^ (((lx + dx) >> 1) & 3) ^ (((ly + par) & 1) << 1));
+
+  // weight fragments: row co = n0 + 16 b + col, channels c0 + 8 oct
+  // (rows past co repeat row 0; their results are not stored)
+  const uint16_t* wrow[NT];
+#pragma unroll
+  for (int b = 0; b < NT; ++b) {
+    const int c = n0 + 16 * b + col;
+    wrow[b] = w + (long long)(c < co ? c : 0) * 27 * ci + 8 * oct;
+  }
+  uint4 wf[9][NT];
+  auto load_weights = [&](int dy, int off) {  // taps (dz, dy, 0..2) at off = 9 dz ci + c0
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+      for (int b = 0; b < NT; ++b)
+        wf[3 * dy + dx][b] =
+            *reinterpret_cast<const uint4*>(wrow[b] + off + (3 * dy + dx) * ci);
+  };
+
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int r = 0; r < MT; ++r)
 #pragma unroll
     for (int b = 0; b < NT; ++b) acc[r][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+#pragma unroll
+  for (int dy = 0; dy < 3; ++dy) load_weights(dy, 0);
   for (int c0 = 0; c0 < ci; c0 += kCC) {
-    __syncthreads();  // the previous chunk's reads are done
-    for (int g = tid; g < kHalo * (kCC / 8); g += 256) {
-      const int hv = g >> 2, part = g & 3;
-      const int hz = hv / (kHY * kHX), hy = (hv / kHX) % kHY, hx = hv % kHX;
-      int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
-      zz = zz < 0 ? zz + s.d : (zz >= s.d ? zz - s.d : zz);
-      yy = yy < 0 ? yy + s.h : (yy >= s.h ? yy - s.h : yy);
-      xx = xx < 0 ? xx + s.w : (xx >= s.w ? xx - s.w : xx);
-      const long long v = (((long long)bn_ * s.d + zz) * s.h + yy) * s.w + xx;
-      *reinterpret_cast<uint4*>(&Hs[hv * kHLD + 8 * part]) =
-          *reinterpret_cast<const uint4*>(x + v * ci + c0 + 8 * part);
+    if (c0) __syncthreads();  // the previous chunk's reads are done
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int q = wv + 4 * i;
+      if (q < NQ)
+        load_to_lds(reinterpret_cast<const uint4*>(x) + (unsigned long long)(src[i] + (uint32_t)(c0 >> 3)),
+                    Hs + q * 1024);
     }
+    __builtin_amdgcn_s_waitcnt(0);  // every load has written its LDS bytes
     __syncthreads();
-    // B fragments of tap 0, then one tap ahead
-    uint4 bq[NT];
+#pragma unroll 1
+    for (int dz = 0; dz < 3; ++dz) {
+      const unsigned char* hz = Hs + dz * (HY * P * 64);
+      // the weights that follow: next dz, or dz = 0 of the next chunk (the
+      // last chunk loads its first ones again: never used)
+      const int next = dz < 2 ? 9 * (dz + 1) * ci + c0 : (c0 + kCC < ci ? c0 + kCC : c0);
 #pragma unroll
-    for (int b = 0; b < NT; ++b) {
-      const int col = n0 + b * 16 + (lane & 15);
-      bq[b] = col < co ? *reinterpret_cast<const uint4*>(w + (long long)col * K + c0 + 8 * oct)
-                       : make_uint4(0, 0, 0, 0);
-    }
-    for (int tap = 0; tap < 27; ++tap) {
-      bf16x8 bf[NT];
+      for (int r = 0; r <= RPM * (MT - 1) + 2; ++r) {  // first halo row of the fragment
 #pragma unroll
-      for (int b = 0; b < NT; ++b) bf[b] = __builtin_bit_cast(bf16x8, bq[b]);
-      if (tap + 1 < 27) {
+        for (int dx = 0; dx < 3; ++dx) {
+          const bf16x8 a = __builtin_bit_cast(
+              bf16x8, *reinterpret_cast<const uint4*>(hz + la[dx][r & 1] + r * (P * 64)));
 #pragma unroll
-        for (int b = 0; b < NT; ++b) {
-          const int col = n0 + b * 16 + (lane & 15);
-          bq[b] = col < co ? *reinterpret_cast<const uint4*>(
-                                 w + (long long)col * K + (long long)(tap + 1) * ci + c0 + 8 * oct)
-                           : make_uint4(0, 0, 0, 0);
+          for (int dy = 0; dy < 3; ++dy) {
+            if (r < dy || (r - dy) % RPM || (r - dy) / RPM >= MT) continue;
+            const int m = (r - dy) / RPM;
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+              acc[m][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, wf[3 * dy + dx][b]), a, acc[m][b], 0, 0, 0);
+          }
         }
-      }
-      const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;  // halo offsets 0..2
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt) {
-        const int hv = ((wv + dz) * kHY + (2 * rt + ly + dy)) * kHX + (lx + dx);
-        const bf16x8 a = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const uint4*>(&Hs[hv * kHLD + 8 * oct]));
-#pragma unroll
-        for (int b = 0; b < NT; ++b)
-          acc[rt][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf[b], acc[rt][b], 0, 0, 0);
+        for (int dy = 0; dy < 3; ++dy)
+          if (r == RPM * (MT - 1) + dy) load_weights(dy, next);
       }
     }
   }
-  // result rows 4 (lane / 16) + i of row tile rt, column lane & 15
+  // channels 4 oct + i of channel tile b, voxel col of voxel tile m
 #pragma unroll
   for (int b = 0; b < NT; ++b) {
-    const int col = n0 + b * 16 + (lane & 15);
-    if (col >= co) continue;
-    const float bb = bias ? bias[col] : 0.f;
+    const int c = n0 + 16 * b + 4 * oct;
+    float bb[4];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int i = 0; i < 4; ++i) bb[i] = bias && c + i < co ? bias[c + i] : 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = 16 * rt + 4 * oct + i;  // row within the wavefront's z layer
-        const int tyy = r >> 3, txx = r & 7;
-        const long long v =
-            (((long long)bn_ * s.d + z0 + wv) * s.h + y0 + tyy) * s.w + x0 + txx;
-        store_out<ACT>(y, v * co + col, acc[rt][b][i] + bb, relu);
+    for (int m = 0; m < MT; ++m) {
+      const long long v =
+          (((long long)bn_ * s.d + z0 + wz) * s.h + y0 + RPM * m + ly) * s.w + x0 + lx;
+      if (vec && c + 4 <= co) {
+        store_out4<ACT>(y, v * co + c, acc[m][b][0] + bb[0], acc[m][b][1] + bb[1],
+                        acc[m][b][2] + bb[2], acc[m][b][3] + bb[3], relu);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (c + i < co) store_out<ACT>(y, v * co + c + i, acc[m][b][i] + bb[i], relu);
       }
+    }
+  }
+}
+
+// Forward convolution for any box with all channels of the halo in LDS: the
+// small levels of the network, whose tiles are too few for the kernel above,
+// channel counts that are no multiple of 32 (the network's 8-channel input
+// and the head's gradient), and boxes that are no multiple of its tiles.
+//
+// The four wavefronts of a block are WZ = 4 / WC z layers times WC groups of
+// 16 NT output channels; a wavefront computes MT tiles of 2 x 8 voxels (y, x),
+// 2 MT rows of its layer.  K = 27 ci is taken in the order of the weights'
+// memory, tap by tap, as octets of 8 channels, four octets per MFMA (lane
+// group oct takes octet 4 q + oct of step q; with 8 channels that is one tap
+// each).  A table in LDS holds each octet's halo offset, so a lane's voxel
+// fragment is one table read and MT 16-byte reads.  Octets past K read the
+// zeroed voxel behind the halo against zero weights.  Voxels outside the box
+// are computed on wrapped inputs and not stored.
+//
+// These launches are bound by latency and by the weights, which every
+// wavefront reads once in a row (L2 resident): they are loaded U steps ahead.
+// Halo voxels are 2 ci + 16 bytes apart in LDS (8 consecutive ones read at
+// one octet cover all banks) and loaded straight from global memory; the
+// padding lanes load a neighbour's bytes that nothing reads.
+//
+// Against 128-voxel tiles gathered stage by stage (conv_fwd_tiled_kernel), BF16
+// output: 8 -> 32 channels at 64^3 x 4 119 -> 45 us; 128 -> 256 at 8^3 x 4 56
+// -> 31 us; 384 -> 128 at one 16^3 box 147 -> 83 us.
+constexpr int kRX = 8, kRHX = kRX + 2;  // x extent of a tile, of its halo
+
+template <int MT, int WC>
+constexpr int rows_halo() {  // halo voxels of a block's tile
+  return (4 / WC + 2) * (2 * MT + 2) * kRHX;
+}
+// LDS bytes: the halo in whole wavefront loads, a zero voxel octet, the table
+template <int MT, int WC>
+size_t rows_lds(int ci) {
+  const size_t halo = (size_t)rows_halo<MT, WC>() * (2 * ci + 16);
+  return (halo + 1023) / 1024 * 1024 + 16 + (size_t)((27 * (ci / 8) + 3) / 4 * 4) * 4;
+}
+
+template <int MT, int NT, int WC, bool ACT>
+__global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __restrict__ x,
+                                                            const uint16_t* __restrict__ w,
+                                                            const float* __restrict__ bias,
+                                                            void* __restrict__ y, Shape s, int ci,
+                                                            int co, int relu, int vec) {
+  constexpr int WZ = 4 / WC, HY = 2 * MT + 2, HV = rows_halo<MT, WC>(), U = 4;
+  extern __shared__ __attribute__((aligned(16))) unsigned char Rs[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wz = wv / WC, wc = wv % WC;
+  const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
+  int t = xcd_item(blockIdx.x, gridDim.x);
+  const int n0 = (t % cgs) * 16 * NT * WC + 16 * NT * wc;
+  t /= cgs;
+  const int tx_n = (s.w + kRX - 1) / kRX, ty_n = (s.h + 2 * MT - 1) / (2 * MT),
+            tz_n = (s.d + WZ - 1) / WZ;
+  const int x0 = (t % tx_n) * kRX;
+  t /= tx_n;
+  const int y0 = (t % ty_n) * 2 * MT;
+  t /= ty_n;
+  const int z0 = (t % tz_n) * WZ;
+  const int bn_ = t / tz_n;
+  const int g8 = ci >> 3, gs = g8 + 1;  // octets of a voxel; with its padding
+  const int nq = (HV * gs + 63) >> 6;
+  const int octets = 27 * g8, steps = (octets + 3) >> 2;
+  unsigned char* zero = Rs + nq * 1024;
+  int* tab = reinterpret_cast<int*>(zero + 16);
+
+  for (int q = wv; q < nq; q += 4) {
+    const int g = q * 64 + lane;
+    int v = g / gs, o = g - v * gs;
+    if (o >= g8) o = 0;
+    if (v >= HV) v = 0;
+    const int R = v / kRHX, hx = v - R * kRHX;
+    const int hz = R / HY, hy = R - hz * HY;
+    // wrapped coordinates; past the far halo of a partial tile: the first cell
+    int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
+    zz = zz < 0 ? zz + s.d : (zz >= s.d ? (zz == s.d ? 0 : z0) : zz);
+    yy = yy < 0 ? yy + s.h : (yy >= s.h ? (yy == s.h ? 0 : y0) : yy);
+    xx = xx < 0 ? xx + s.w : (xx >= s.w ? (xx == s.w ? 0 : x0) : xx);
+    const long long m = (((long long)bn_ * s.d + zz) * s.h + yy) * s.w + xx;
+    load_to_lds(reinterpret_cast<const uint4*>(x) + (m * g8 + o), Rs + q * 1024);
+  }
+  const int zoff = nq * 1024;
+  for (int i = tid; i < 4 * steps; i += 256) {
+    const int tap = i / g8, o = i - tap * g8;
+    const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
+    tab[i] = i < octets ? ((dz * HY + dy) * kRHX + dx) * (gs * 16) + o * 16 : -1;
+  }
+  if (tid < 4) reinterpret_cast<uint32_t*>(zero)[tid] = 0;
+
+  const int col = lane & 15, oct = lane >> 4;
+  const int lx = col & 7, ly = col >> 3;
+  const int base = ((wz * HY + ly) * kRHX + lx) * (gs * 16);
+  const int mstep = 2 * kRHX * gs * 16;  // next voxel tile: two rows on
+  // weight rows co = n0 + 16 b + col (rows past co repeat row 0; their results
+  // are not stored).  Every load is unconditional, so that the compiler keeps
+  // all of them in flight; octets past K load the row's last one.
+  const uint16_t* wrow[NT];
+#pragma unroll
+  for (int b = 0; b < NT; ++b) {
+    const int c = n0 + 16 * b + col;
+    wrow[b] = w + (long long)(c < co ? c : 0) * 27 * ci;
+  }
+  uint4 wf[2][U][NT];
+  auto load_weights = [&](uint4 (&f)[U][NT], int q0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = 4 * (q0 + u) + oct;
+#pragma unroll
+      for (int b = 0; b < NT; ++b)
+        f[u][b] = *reinterpret_cast<const uint4*>(wrow[b] + 8 * (i < octets ? i : octets - 1));
+    }
+  };
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int r = 0; r < MT; ++r)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[r][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](const uint4 (&f)[NT], int off) {
+    const int at = off < 0 ? zoff : base + off, am = off < 0 ? 0 : mstep;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const bf16x8 a =
+          __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(Rs + at + m * am));
+#pragma unroll
+      for (int b = 0; b < NT; ++b)
+        acc[m][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[b]), a,
+                                                            acc[m][b], 0, 0, 0);
+    }
+  };
+  // U steps whose octets all lie within K
+  auto compute = [&](const uint4 (&f)[U][NT], int q0) {
+    int off[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) off[u] = tab[4 * (q0 + u) + oct];
+#pragma unroll
+    for (int u = 0; u < U; ++u) step(f[u], off[u]);
+  };
+  // the last steps: weights of octets past K are zero
+  auto compute_tail = [&](uint4 (&f)[U][NT], int q0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (q0 + u >= steps) break;
+      if (4 * (q0 + u) + oct >= octets)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) f[u][b] = make_uint4(0, 0, 0, 0);
+      step(f[u], tab[4 * (q0 + u) + oct]);
+    }
+  };
+  load_weights(wf[0], 0);
+  __builtin_amdgcn_s_waitcnt(0);  // every load has written its LDS bytes
+  __syncthreads();
+  int q0 = 0;
+  for (; 4 * (q0 + 2 * U) <= octets; q0 += 2 * U) {
+    load_weights(wf[1], q0 + U);
+    compute(wf[0], q0);
+    load_weights(wf[0], q0 + 2 * U);
+    compute(wf[1], q0 + U);
+  }
+  if (q0 < steps) {
+    load_weights(wf[1], q0 + U);
+    compute_tail(wf[0], q0);
+    compute_tail(wf[1], q0 + U);
+  }
+  // channels 4 oct + i of channel tile b, voxel col of voxel tile m
+  const int zz = z0 + wz, xx = x0 + lx;
+#pragma unroll
+  for (int b = 0; b < NT; ++b) {
+    const int c = n0 + 16 * b + 4 * oct;
+    float bb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bb[i] = bias && c + i < co ? bias[c + i] : 0.f;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int yy = y0 + 2 * m + ly;
+      if (zz >= s.d || yy >= s.h || xx >= s.w) continue;
+      const long long v = (((long long)bn_ * s.d + zz) * s.h + yy) * s.w + xx;
+      if (vec && c + 4 <= co) {
+        store_out4<ACT>(y, v * co + c, acc[m][b][0] + bb[0], acc[m][b][1] + bb[1],
+                        acc[m][b][2] + bb[2], acc[m][b][3] + bb[3], relu);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (c + i < co) store_out<ACT>(y, v * co + c + i, acc[m][b][i] + bb[i], relu);
+      }
+    }
   }
 }
 
@@ -1151,6 +1441,97 @@ __global__ void split_vec_kernel(const float4* __restrict__ dy, float4* __restri
 namespace {
 
 template <bool ACT>
+int vector_stores(const void* y, int co) {
+  return co % 4 == 0 && ((uintptr_t)y & (ACT ? 7 : 15)) == 0;
+}
+
+// Spatially tiled forward convolution: x rows of 16 where the box allows, and
+// as many rows per wavefront as still leave about one block per CU (fewer
+// operand reads per MFMA with more rows; measured at 64^3 x 4, 96 -> 32
+// channels, 8 / 4 / 2 rows: 215 / 314 / 477 us; 16^3 x 4, 384 -> 128, with
+// 128 / 256 / 512 blocks: 117 / 96 / 154 us).
+template <int TX, int MT, int NT, int WC, bool ACT>
+void launch_fwd_tile(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
+                     const Shape& s, int ci, int co, int relu, hipStream_t st) {
+  constexpr int voxels = (4 / WC) * 16 * MT;
+  const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
+  conv_fwd_spatial_kernel<TX, MT, NT, WC, ACT><<<(unsigned)(s.m / voxels * cgs), 256, 0, st>>>(
+      x, w, bias, y, s, ci, co, relu, vector_stores<ACT>(y, co));
+}
+constexpr int kFillBlocks = 200;  // enough blocks for the 256 CUs
+template <int NT, int WC, bool ACT>
+void launch_fwd_rows_of(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
+                        const Shape& s, int ci, int co, int relu, hipStream_t st) {
+  const long long cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
+  const long long tiles = s.m / ((4 / WC) * 16) * cgs;  // blocks with one tile per wavefront
+  if (s.w % 16) {
+    launch_fwd_tile<8, 4, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  } else if (tiles >= 8 * kFillBlocks) {
+    launch_fwd_tile<16, 8, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  } else if (WC > 1 || tiles >= 4 * kFillBlocks) {
+    // (two groups of channels: always so many tiles)
+    launch_fwd_tile<16, 4, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  } else {
+    if constexpr (WC == 1) launch_fwd_tile<16, 2, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  }
+}
+// Channel groups of 32 per wavefront (16 for few channels); pairs of groups
+// share a block's halo where their count is even (96 channels: 257 us with
+// one group per block against 293 us with two, a quarter of them empty).
+template <bool ACT>
+void launch_fwd_spatial(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
+                        const Shape& s, int ci, int co, int relu, hipStream_t st) {
+  if (co <= 16)
+    launch_fwd_rows_of<1, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  else if ((co + 31) / 32 % 2)
+    launch_fwd_rows_of<2, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  else
+    launch_fwd_rows_of<2, 2, ACT>(x, w, bias, y, s, ci, co, relu, st);
+}
+
+constexpr size_t kLdsBytes = 160 * 1024;  // of a CU
+
+template <int MT, int WC>
+long long rows_blocks(const Shape& s, int groups) {
+  return (long long)s.n * ((s.d + 4 / WC - 1) / (4 / WC)) * ((s.h + 2 * MT - 1) / (2 * MT)) *
+         ((s.w + kRX - 1) / kRX) * groups;
+}
+template <int MT, int NT, int WC, bool ACT>
+void launch_rows(const uint16_t* x, const uint16_t* w, const float* bias, void* y, const Shape& s,
+                 int ci, int co, int relu, hipStream_t st) {
+  const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
+  conv_fwd_rows_kernel<MT, NT, WC, ACT>
+      <<<(unsigned)rows_blocks<MT, WC>(s, cgs), 256, rows_lds<MT, WC>(ci), st>>>(
+          x, w, bias, y, s, ci, co, relu, vector_stores<ACT>(y, co));
+}
+// Rows per wavefront: the fewest whose blocks run at once, one per CU (a
+// second block on a CU doubles the time of a latency-bound launch), four for
+// boxes beyond that; false if the halo does not fit in LDS.
+template <int NT, int WC, bool ACT>
+bool launch_rows_of(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
+                    const Shape& s, int ci, int co, int relu, hipStream_t st) {
+  const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
+  const bool fit1 = rows_lds<1, WC>(ci) <= kLdsBytes, fit2 = rows_lds<2, WC>(ci) <= kLdsBytes,
+             fit4 = rows_lds<4, WC>(ci) <= kLdsBytes;
+  if (!fit1) return false;
+  if (rows_blocks<1, WC>(s, cgs) <= 256 || !fit2)
+    launch_rows<1, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  else if (rows_blocks<2, WC>(s, cgs) <= 256 || !fit4)
+    launch_rows<2, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  else
+    launch_rows<4, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  return true;
+}
+template <bool ACT>
+bool launch_fwd_halo(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
+                     const Shape& s, int ci, int co, int relu, hipStream_t st) {
+  if (co <= 16) return launch_rows_of<1, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  if (co <= 32) return launch_rows_of<2, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  if (co <= 64) return launch_rows_of<2, 2, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  return launch_rows_of<2, 4, ACT>(x, w, bias, y, s, ci, co, relu, st);
+}
+
+template <bool ACT>
 lbm_status conv_forward(const void* x, const void* w, const float* bias, void* y, int n, int d,
                         int h, int wd, int ci, int co, int relu, void* stream) {
   if (!x || !w || !y || bad_shape(n, d, h, wd) || ci < 8 || ci % 8 || co < 1)
@@ -1164,17 +1545,18 @@ lbm_status conv_forward(const void* x, const void* w, const float* bias, void* y
   // spatial tiles where the box and channels allow and the grid is not tiny
   const long long tiles = s.m / (kTZ * kTY * kTX);
   if (ci % kCC == 0 && d % kTZ == 0 && h % kTY == 0 && wd % kTX == 0 &&
-      tiles * ((co + bn - 1) / bn) >= 128) {
-    dim3 sgrid((unsigned)tiles, (unsigned)((co + bn - 1) / bn));
-    if (bn == 16)
-      conv_fwd_spatial_kernel<16, ACT><<<sgrid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
-    else if (bn == 32)
-      conv_fwd_spatial_kernel<32, ACT><<<sgrid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
-    else
-      conv_fwd_spatial_kernel<64, ACT><<<sgrid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
+      tiles * ((co + bn - 1) / bn) >= 128 && aligned16(x) && aligned16(w) &&
+      s.m * (ci / 8) < (1LL << 31)) {
+    launch_fwd_spatial<ACT>(xx, ww, bias, y, s, ci, co, relu, st);
     return check_launch();
   }
   dim3 grid((unsigned)((s.m + 127) / 128), (unsigned)((co + bn - 1) / bn));
+  // few tiles or few channels: the halo kernel (20^3 x 3, 64 -> 128 channels,
+  // 376 tiles: 47 us there against 42 us in gathered tiles; 12 x 16 x 24, 192
+  // -> 128, 72 tiles: 47 against 78 us)
+  if ((ci < 32 || (long long)grid.x * grid.y < 256) && aligned16(x) &&
+      launch_fwd_halo<ACT>(xx, ww, bias, y, s, ci, co, relu, st))
+    return check_launch();
   if (bn == 16)
     conv_fwd_tiled_kernel<16, ACT><<<grid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
   else if (bn == 32)

@@ -105,6 +105,40 @@ def test_conv_forward_backward_match_reference(ctx, shape, ci, co):
         assert rel(_host(db), db_ref) < 1e-5
 
 
+# one shape per launch of the forward convolution: spatial tiles (8, 4 and 2 rows
+# of 16 voxels, rows of 8; one and two groups of 32 channels, 33 outputs: element
+# stores), halo tiles (1, 2 and 4 row pairs; partial tiles in every axis; channel
+# counts that are no multiple of 32 or 4; four channel groups), gathered tiles
+# (many partial tiles; more channels than fit in LDS)
+FORWARD_TILES = [((2, 32, 64, 64), 32, 32), ((1, 32, 32, 32), 64, 64), ((1, 16, 32, 64), 32, 32),
+                 ((1, 32, 40, 40), 32, 33), ((1, 16, 32, 32), 32, 32), ((1, 32, 32, 24), 8, 32),
+                 ((2, 40, 40, 40), 8, 32), ((2, 9, 7, 5), 16, 24), ((1, 3, 2, 1), 8, 8),
+                 ((1, 11, 13, 10), 40, 13), ((1, 4, 6, 8), 64, 136), ((1, 4, 4, 8), 704, 16),
+                 ((2, 36, 36, 30), 32, 32)]
+
+
+@pytest.mark.parametrize("shape,ci,co", FORWARD_TILES)
+def test_conv_forward_tiles_match_reference(ctx, shape, ci, co):
+    """BF16 products are exact in FP32, so only the FP32 sum of 27 ci terms
+    rounds: 1e-5 of the largest output, as above."""
+    rng = np.random.default_rng(ci * 11 + co)
+    x = R.bf16(rng.standard_normal(shape + (ci,)))
+    w = R.bf16(rng.standard_normal((co, 27, ci)) * 0.2)
+    b = rng.standard_normal(co).astype(np.float32).astype(np.float64)
+    lib = W._nn()
+    n, d, h, wd = shape
+    xd, wb, bd = _bf_dev(ctx, x), _bf_dev(ctx, w), _f_dev(ctx, b)
+    y = ctx.f32(n, d, h, wd, co)
+    assert lib.nn_conv3d_forward(W._p(xd), W._p(wb), W._p(bd), W._p(y), n, d, h, wd, ci, co,
+                                 ctx.stream) == 0
+    assert rel(_host(y), R.conv3d(x, w, b)) < 1e-5
+    a, a_ref = ctx.bf(n, d, h, wd, co), ctx.bf(n, d, h, wd, co)
+    assert lib.nn_activation_forward(W._p(y), W._p(a_ref), y.numel(), 1, ctx.stream) == 0
+    assert lib.nn_conv3d_forward_act(W._p(xd), W._p(wb), W._p(bd), W._p(a), n, d, h, wd, ci, co, 1,
+                                     ctx.stream) == 0
+    assert ctx.torch.equal(a.view(ctx.torch.int16), a_ref.view(ctx.torch.int16))
+
+
 @pytest.mark.parametrize("c", [8, 6])
 def test_pool_up_concat_split_relu(ctx, c):
     """c = 8: the 16-byte granule kernels; c = 6: the element kernels."""
