@@ -251,7 +251,6 @@ __global__ __launch_bounds__(256) void conv_fwd_tiled_kernel(const uint16_t* __r
 // 101 us; 96 -> 32 at one 64^3 box: 105 -> 60 us.
 constexpr int kTZ = 4, kTY = 8, kTX = 8;
 constexpr int kHZ = kTZ + 2, kHY = kTY + 2, kHX = kTX + 2;
-constexpr int kHalo = kHZ * kHY * kHX;  // 600 voxels
 constexpr int kCC = 32;                 // channels per chunk
 
 // 16 bytes per lane from global memory to LDS: lane l's go to lds + 16 l (lds
@@ -607,132 +606,204 @@ __global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __re
 // 4 x 8 x 8 tile: dw[co][tap][ci] = sum over the voxels v of dy[v][co]
 // x[v + off(tap)][ci], an MFMA GEMM whose K runs over the 256 voxels of a
 // tile.  Block (g, chunk, co tile) adds up the tiles g, g + G, g + 2G, ...
-// (a fixed order) for 16 CT input and 16 RT output channels (channels past
-// ci or co are zero) and writes its sum to part[g]; fold_splits_kernel adds
-// the G partials in order, so the result is deterministic.  Per tile, LDS
-// holds dy transposed (Ds[co][voxel]) and three copies of the 6 x 10 x 10
-// input halo shifted by dx = 0, 1, 2, channel-major (Xs[dx][c][hz][hy][tx]),
-// so that both MFMA operands are 8 consecutive voxels (one x row of the
-// tile) read as one aligned 16-byte word.  Wavefront wv owns the taps wv,
-// wv + 4, ...
-constexpr int kXR = kHZ * kHY * kTX;       // halo positions of one shifted copy of a channel
-constexpr int kDLD = kTZ * kTY * kTX + 8;  // Ds row stride (halfs)
+// for 16 CT input and 16 RT output channels (channels past ci or co are
+// zero) and writes its sum to part[g]; fold_splits_kernel adds the G partials
+// in order, so the result is deterministic.
+//
+// Both operands need 8 consecutive voxels of one channel per lane, while
+// tensors (and the LDS tiles) are channels-last: gfx950's transposing LDS read
+// (ds_read_b64_tr_b16: 16 lanes read 4 voxels x 16 channels and each gets the
+// 4 voxels of one channel) does that without a transposed copy.  The 10
+// voxels of a halo row serve the three x shifts: shift 0 and 2 are register
+// pairs of the same reads, shift 1 takes four 16-bit funnel shifts, so a
+// wavefront reads 1.5 instead of 3 operands per (dz, dy).
+//
+// The eight wavefronts are CT input-channel tiles times 8 / CT parts of the
+// tile's voxels; each holds all 27 taps of its channels (27 RT accumulators),
+// so per 32 voxels it reads RT + 13.5 operands for 27 RT MFMAs.  The parts are
+// added in LDS at the end.  The next tile's halo (one 40-lane load per halo
+// row) and gradient go straight from global memory to the other LDS buffer
+// while the current tile is computed; one block of 2 wavefronts per SIMD
+// fills a CU.
+//
+// LDS: voxel v of a tile at 32 CT (32 RT) bytes; with 64 bytes the two 32-byte
+// halves are swapped where v & 2, so that the 4 voxels of a transposing read
+// cover all banks.
+//
+// With the transposed copies written to LDS two bytes at a time and the tiles
+// of the small levels on the general kernel (fold included): 96 -> 32 channels
+// at 64^3 x 4 642 -> 246 us (707 TFLOP/s), 192 -> 64 at 32^3 x 4 314 -> 120 us,
+// 384 -> 128 at 16^3 x 4 318 -> 71 us, 128 -> 256 at 8^3 x 4 49 -> 29 us.
+constexpr int kWRow = 16;                      // voxels from halo row to halo row in LDS
+constexpr int kWRows = kHZ * kHY;              // halo rows
+constexpr int kTileVox = kTZ * kTY * kTX;      // 256
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void unpack8(uint4 u, uint16_t (&h)[8]) {
-  h[0] = (uint16_t)u.x;
-  h[1] = (uint16_t)(u.x >> 16);
-  h[2] = (uint16_t)u.y;
-  h[3] = (uint16_t)(u.y >> 16);
-  h[4] = (uint16_t)u.z;
-  h[5] = (uint16_t)(u.z >> 16);
-  h[6] = (uint16_t)u.w;
-  h[7] = (uint16_t)(u.w >> 16);
+// Zeros for the channels past the last in partial channel tiles.
+__device__ const uint4 zero_octet = {0, 0, 0, 0};
+
+// 16 bytes per active lane from global memory to LDS byte address lds + 16
+// lane, not tracked by the compiler, which would otherwise wait for it before
+// any LDS read: lds_loads_done() before the barrier that publishes them.  M0
+// holds the LDS address; nothing else in the kernels that use this needs it.
+__device__ __forceinline__ void load_to_lds_async(const void* g, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :
+               : "s"(lds), "v"(g)
+               : "memory");
+}
+__device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
+// 4 voxels of one channel per lane (see above)
+__device__ __forceinline__ uint2 read_transposed(const unsigned char* p) {
+  return __builtin_bit_cast(
+      uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
 }
 
 template <int RT, int CT>
-__global__ __launch_bounds__(256) void conv_bwdw_spatial_kernel(const uint16_t* __restrict__ x,
-                                                                const uint16_t* __restrict__ dy,
-                                                                float* __restrict__ part, Shape s,
-                                                                int ci, int co, int tiles) {
-  constexpr int CC = 16 * CT, OC = 16 * RT;  // input / output channels of the block
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[3 * CC * kXR];
-  __shared__ __attribute__((aligned(16))) uint16_t Ds[OC * kDLD];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, oct = lane >> 4;
-  const int G = gridDim.x, c0 = blockIdx.y * CC, o0 = blockIdx.z * OC;
+__global__ __launch_bounds__(512, 2) void conv_bwdw_spatial_kernel(const uint16_t* __restrict__ x,
+                                                                   const uint16_t* __restrict__ dy,
+                                                                   float* __restrict__ part,
+                                                                   Shape s, int ci, int co,
+                                                                   int tiles) {
+  constexpr int XV = 32 * CT, DV = 32 * RT;              // bytes of a voxel in LDS
+  constexpr int XB = kWRows * kWRow * XV, DB = kTileVox * DV;
+  constexpr int KP = 8 / CT;                             // parts of the voxels
+  constexpr int KS = 8 / KP;                             // steps of 32 voxels per part
+  constexpr int RB = 9 * RT * 8 * 1024;                  // fold: 9 taps of 8 wavefronts
+  constexpr int LB = 2 * (XB + DB) > RB ? 2 * (XB + DB) : RB;
+  __shared__ __attribute__((aligned(16))) unsigned char Ls[LB];
+  const int tid = threadIdx.x, lane = tid & 63, oct = lane >> 4, i16 = lane & 15;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ct = wv % CT, kp = wv / CT;
+  const int G = gridDim.x, c0 = blockIdx.y * 16 * CT, o0 = blockIdx.z * 16 * RT;
   const int tx_n = s.w / kTX, ty_n = s.h / kTY, tz_n = s.d / kTZ;
-  f32x4 acc[7][RT][CT];
-#pragma unroll
-  for (int j = 0; j < 7; ++j)
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-      for (int c = 0; c < CT; ++c) acc[j][r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  for (int t = blockIdx.x; t < tiles; t += G) {
-    int q = t;
-    const int bx = q % tx_n;
-    q /= tx_n;
-    const int by = q % ty_n;
-    q /= ty_n;
-    const int bz = q % tz_n;
-    const int bn_ = q / tz_n;
-    const int x0 = bx * kTX, y0 = by * kTY, z0 = bz * kTZ;
-    __syncthreads();  // the previous tile's reads are done
-    for (int g = tid; g < kHalo * (CC / 8); g += 256) {
-      const int hv = g / (CC / 8), p8 = 8 * (g % (CC / 8));
-      const int hz = hv / (kHY * kHX), hy = (hv / kHX) % kHY, hx = hv % kHX;
-      int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
+  // this lane's voxel and channel octet of a staging load: a halo row (lanes
+  // 0..XL-1) and a run of consecutive gradient voxels
+  constexpr int XG = 2 * CT, DG = 2 * RT;                // octets of a voxel
+  constexpr int XL = kHX * XG;
+  const int xv = lane / XG, dv = lane / DG;
+  auto octet_of = [](int slot, int v, int g) {           // swapped halves (above)
+    return g == 4 ? (slot ^ (v & 2)) : slot;
+  };
+  const int xo = c0 + 8 * octet_of(lane % XG, xv, XG), od = o0 + 8 * octet_of(lane % DG, dv, DG);
+  const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_address(Ls));
+
+  auto stage = [&](int t, int buf) {
+    const int x0 = (t % tx_n) * kTX;
+    t /= tx_n;
+    const int y0 = (t % ty_n) * kTY;
+    t /= ty_n;
+    const int z0 = (t % tz_n) * kTZ;
+    const int bn_ = t / tz_n;
+    int xx = x0 + xv - 1;
+    xx = xx < 0 ? xx + s.w : (xx >= s.w ? xx - s.w : xx);
+    const uint32_t xl = lds + buf * (XB + DB), dl = xl + XB;
+    for (int r = wv; r < kWRows; r += 8) {               // (wavefront-uniform)
+      const int hz = r / kHY, hy = r - hz * kHY;
+      int zz = z0 + hz - 1, yy = y0 + hy - 1;
       zz = zz < 0 ? zz + s.d : (zz >= s.d ? zz - s.d : zz);
       yy = yy < 0 ? yy + s.h : (yy >= s.h ? yy - s.h : yy);
-      xx = xx < 0 ? xx + s.w : (xx >= s.w ? xx - s.w : xx);
-      const long long v = (((long long)bn_ * s.d + zz) * s.h + yy) * s.w + xx;
-      uint16_t h[8];
-      unpack8(c0 + p8 < ci ? *reinterpret_cast<const uint4*>(x + v * ci + c0 + p8)
-                           : make_uint4(0, 0, 0, 0),
-              h);
-      const int pos = (hz * kHY + hy) * kTX;
-#pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        const int tx = hx - dx;
-        if (tx < 0 || tx >= kTX) continue;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) Xs[(dx * CC + p8 + i) * kXR + pos + tx] = h[i];
-      }
+      const long long row = (((long long)bn_ * s.d + zz) * s.h + yy) * s.w;
+      const void* g = xo < ci ? (const void*)(x + (row + xx) * ci + xo) : (const void*)&zero_octet;
+      if (lane < XL) load_to_lds_async(g, xl + r * (kWRow * XV));
     }
-    for (int g = tid; g < kTZ * kTY * kTX * (OC / 8); g += 256) {
-      const int r = g / (OC / 8), p8 = 8 * (g % (OC / 8));
-      const int tz = r >> 6, ty = (r >> 3) & 7, tx = r & 7;
-      const long long v = (((long long)bn_ * s.d + z0 + tz) * s.h + y0 + ty) * s.w + x0 + tx;
-      uint16_t h[8];
-      unpack8(o0 + p8 < co ? *reinterpret_cast<const uint4*>(dy + v * co + o0 + p8)
-                           : make_uint4(0, 0, 0, 0),
-              h);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) Ds[(p8 + i) * kDLD + r] = h[i];
+    constexpr int VL = 64 / DG;                          // gradient voxels per load
+    for (int q = wv; q < kTileVox / VL; q += 8) {
+      const int v = q * VL + dv;
+      const int tz = v >> 6, ty = (v >> 3) & 7, tx = v & 7;
+      const long long m = (((long long)bn_ * s.d + z0 + tz) * s.h + y0 + ty) * s.w + x0 + tx;
+      const void* g = od < co ? (const void*)(dy + m * co + od) : (const void*)&zero_octet;
+      load_to_lds_async(g, dl + q * 1024);
     }
+  };
+
+  f32x4 acc[27][RT];
+#pragma unroll
+  for (int j = 0; j < 27; ++j)
+#pragma unroll
+    for (int r = 0; r < RT; ++r) acc[j][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // LDS bytes of this lane's transposing reads at step 0 of the part: voxel
+  // i16 / 4 of a row, channels 4 (i16 % 4) of the 16-channel half
+  const int half = (i16 >> 3) & 1;
+  const int sub = (i16 & 3) * 8;
+  const int xbase = (oct * kWRow + (i16 >> 2)) * XV + (CT == 2 ? (ct ^ half) * 32 : 0) + sub;
+  const int dbase = (oct * 8 + (i16 >> 2)) * DV + sub;
+
+  int buf = 0;
+  if ((int)blockIdx.x < tiles) stage(blockIdx.x, 0);
+  for (int t = blockIdx.x; t < tiles; t += G, buf ^= 1) {
+    lds_loads_done();
     __syncthreads();
-#pragma unroll 2
-    for (int ks = 0; ks < 8; ++ks) {
-      const int vr = 4 * ks + oct;  // x row (tz, ty) of this lane's 8 voxels
-      const int tz = vr >> 3, ty = vr & 7;
+    if (t + G < tiles) stage(t + G, buf ^ 1);
+    const unsigned char* xs = Ls + buf * (XB + DB);
+    const unsigned char* ds = xs + XB;
+#pragma unroll 1
+    for (int k = 0; k < KS; ++k) {
+      const int ks = kp * KS + k;                        // x rows 4 ks + oct of the tile
+      const unsigned char* xr =
+          xs + xbase + ((ks >> 1) * kHY + 4 * (ks & 1)) * (kWRow * XV);
+      const unsigned char* dr = ds + dbase + ks * (32 * DV);
       bf16x8 a[RT];
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-        a[rt] = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const uint4*>(&Ds[(16 * rt + (lane & 15)) * kDLD + 8 * vr]));
+      for (int r = 0; r < RT; ++r) {
+        const unsigned char* q = dr + (RT == 2 ? (r ^ half) * 32 : 0);
+        const uint2 lo = read_transposed(q), hi = read_transposed(q + 4 * DV);
+        a[r] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+      }
 #pragma unroll
-      for (int j = 0; j < 7; ++j) {
-        const int tap = wv + 4 * j;
-        if (tap >= 27) continue;
-        const int dz = tap / 9, dyy = (tap / 3) % 3, dx = tap % 3;
-        const int pos = ((tz + dz) * kHY + ty + dyy) * kTX;
+      for (int p = 0; p < 9; ++p) {
+        const unsigned char* q = xr + ((p / 3) * kHY + p % 3) * (kWRow * XV);
+        const uint2 v0 = read_transposed(q), v4 = read_transposed(q + 4 * XV),
+                    v8 = read_transposed(q + 8 * XV);
+        const uint4 b[3] = {
+            make_uint4(v0.x, v0.y, v4.x, v4.y),
+            make_uint4(__builtin_amdgcn_alignbit(v0.y, v0.x, 16),
+                       __builtin_amdgcn_alignbit(v4.x, v0.y, 16),
+                       __builtin_amdgcn_alignbit(v4.y, v4.x, 16),
+                       __builtin_amdgcn_alignbit(v8.x, v4.y, 16)),
+            make_uint4(v0.y, v4.x, v4.y, v8.x)};
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const bf16x8 b = __builtin_bit_cast(
-              bf16x8, *reinterpret_cast<const uint4*>(
-                          &Xs[(dx * CC + 16 * ct + (lane & 15)) * kXR + pos]));
+        for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-            acc[j][rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt], b, acc[j][rt][ct], 0, 0, 0);
-        }
+          for (int r = 0; r < RT; ++r)
+            acc[3 * p + dx][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                a[r], __builtin_bit_cast(bf16x8, b[dx]), acc[3 * p + dx][r], 0, 0, 0);
       }
     }
   }
-  // result rows (co) 4 (lane / 16) + i of row tile rt, column (ci) lane & 15
+  // Add the parts, 9 taps at a time, and store: rows (co) 4 oct + i of row
+  // tile r, column (ci) lane & 15.
+  f32x4* fold = reinterpret_cast<f32x4*>(Ls);            // [wavefront][9 RT][lane]
   const long long base = (long long)blockIdx.x * co * 27 * ci;
 #pragma unroll
-  for (int j = 0; j < 7; ++j) {
-    const int tap = wv + 4 * j;
-    if (tap >= 27) continue;
+  for (int j0 = 0; j0 < 27; j0 += 9) {
+    __syncthreads();
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int j = 0; j < 9; ++j)
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
+      for (int r = 0; r < RT; ++r) fold[(wv * 9 * RT + j * RT + r) * 64 + lane] = acc[j0 + j][r];
+    __syncthreads();
+    for (int q = wv; q < 9 * RT * CT; q += 8) {          // (wavefront-uniform)
+      const int c = q % CT, jr = q / CT;
+      f32x4 v = fold[(c * 9 * RT + jr) * 64 + lane];
+      for (int k = 1; k < KP; ++k) {
+        const f32x4 u = fold[((k * CT + c) * 9 * RT + jr) * 64 + lane];
+        for (int e = 0; e < 4; ++e) v[e] += u[e];
+      }
+      const int tap = j0 + jr / RT, r = jr % RT;
+      const int cc = c0 + 16 * c + i16;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int o = o0 + 16 * rt + 4 * oct + i, c = c0 + 16 * ct + (lane & 15);
-          if (o < co && c < ci) part[base + ((long long)o * 27 + tap) * ci + c] = acc[j][rt][ct][i];
-        }
+      for (int e = 0; e < 4; ++e) {
+        const int o = o0 + 16 * r + 4 * oct + e;
+        if (o < co && cc < ci) part[base + ((long long)o * 27 + tap) * ci + cc] = v[e];
+      }
+    }
   }
 }
 
@@ -1593,15 +1664,14 @@ NN_API lbm_status nn_conv3d_backward_data(const void* dy, const void* wt, float*
   return nn_conv3d_forward(dy, wt, nullptr, dx, n, d, h, wd, co, ci, stream);
 }
 
-// The spatially tiled weight gradient applies (and with how many splits).
+// The spatially tiled weight gradient applies (and with how many splits): one
+// block per CU over the channel tiles.
 static bool bwdw_spatial(int n, int d, int h, int wd, int ci, int co, int* splits) {
-  const long long tiles = (long long)n * d * h * wd / (kTZ * kTY * kTX);
-  if (d % kTZ || h % kTY || wd % kTX || tiles < 256) return false;
-  // about 512 blocks over the channel tiles, at least two voxel tiles each
+  const long long tiles = (long long)n * d * h * wd / kTileVox;
+  if (d % kTZ || h % kTY || wd % kTX || tiles > (1 << 30)) return false;
   const int ct = ci % 32 == 0 ? 32 : 16, rt = co % 32 == 0 ? 32 : 16;
   const long long chan_tiles = (long long)((ci + ct - 1) / ct) * ((co + rt - 1) / rt);
-  *splits = (int)std::max<long long>(
-      1, std::min<long long>({256, tiles / 2, 512 / std::max<long long>(chan_tiles, 1)}));
+  *splits = (int)std::max<long long>(1, std::min<long long>(tiles, 256 / chan_tiles));
   return true;
 }
 
@@ -1638,7 +1708,7 @@ NN_API lbm_status nn_conv3d_backward_weight(const void* x, const void* dy, float
   const long long nw = (long long)co * 27 * ci;
   int ssp = 0;
   if (bwdw_spatial(n, d, h, wd, ci, co, &ssp)) {
-    const int tiles = (int)(s.m / (kTZ * kTY * kTX));
+    const int tiles = (int)(s.m / kTileVox);
     // channel tiles: 32 where the count is a multiple of 32, else 16 (zero padded)
     const int ct = ci % 32 == 0 ? 2 : 1, rt = co % 32 == 0 ? 2 : 1;
     dim3 sgrid((unsigned)ssp, (unsigned)((ci + 16 * ct - 1) / (16 * ct)),
@@ -1648,13 +1718,13 @@ NN_API lbm_status nn_conv3d_backward_weight(const void* x, const void* dy, float
     float* pp = (float*)ws;
     const hipStream_t st = (hipStream_t)stream;
     if (rt == 2 && ct == 2)
-      conv_bwdw_spatial_kernel<2, 2><<<sgrid, 256, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
+      conv_bwdw_spatial_kernel<2, 2><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
     else if (rt == 2)
-      conv_bwdw_spatial_kernel<2, 1><<<sgrid, 256, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
+      conv_bwdw_spatial_kernel<2, 1><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
     else if (ct == 2)
-      conv_bwdw_spatial_kernel<1, 2><<<sgrid, 256, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
+      conv_bwdw_spatial_kernel<1, 2><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
     else
-      conv_bwdw_spatial_kernel<1, 1><<<sgrid, 256, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
+      conv_bwdw_spatial_kernel<1, 1><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
     fold_splits_kernel<<<grid_for(nw), 256, 0, (hipStream_t)stream>>>((const float*)ws, dw, nw,
                                                                        ssp);
     return check_launch();

@@ -139,6 +139,31 @@ def test_conv_forward_tiles_match_reference(ctx, shape, ci, co):
     assert ctx.torch.equal(a.view(ctx.torch.int16), a_ref.view(ctx.torch.int16))
 
 
+# spatially tiled weight gradient: one tile, more tiles than splits (125 over 64,
+# uneven), and a partial channel tile on each side
+@pytest.mark.parametrize("shape,ci,co", [((1, 4, 8, 8), 32, 32), ((1, 20, 40, 40), 64, 64),
+                                         ((1, 12, 16, 8), 24, 40)])
+def test_conv_weight_gradient_tiles_match_reference(ctx, shape, ci, co):
+    """Exact products, FP32 sums over the voxels: 1e-5 of the largest weight's
+    gradient, as above."""
+    import ctypes as C
+
+    rng = np.random.default_rng(ci * 13 + co)
+    x = R.bf16(rng.standard_normal(shape + (ci,)))
+    dy = R.bf16(rng.standard_normal(shape + (co,)))
+    lib = W._nn()
+    n, d, h, wd = shape
+    nb, sp = C.c_size_t(), C.c_int()
+    assert lib.nn_conv3d_backward_weight_workspace(n, d, h, wd, ci, co, C.byref(nb),
+                                                   C.byref(sp)) == 0
+    ws = ctx.torch.empty(nb.value, dtype=ctx.torch.uint8, device=ctx.dev)
+    dw = ctx.f32(co, 27, ci)
+    assert lib.nn_conv3d_backward_weight(W._p(_bf_dev(ctx, x)), W._p(_bf_dev(ctx, dy)), W._p(dw),
+                                         W._p(ws), nb.value, n, d, h, wd, ci, co, ctx.stream) == 0
+    ref = R.conv3d_backward(x, np.zeros((co, 27, ci)), dy)[1]
+    assert rel(_host(dw), ref) < 1e-5
+
+
 @pytest.mark.parametrize("c", [8, 6])
 def test_pool_up_concat_split_relu(ctx, c):
     """c = 8: the 16-byte granule kernels; c = 6: the element kernels."""
