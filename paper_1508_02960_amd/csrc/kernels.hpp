@@ -567,32 +567,67 @@ struct Nbr {
 // Weight class of direction k: 0 rest, 1 axis, 2 diagonal.
 __device__ __host__ constexpr int wclass(int k) { return k == 0 ? 0 : (k < 7 ? 1 : 2); }
 
-// Cell m steps from (x, y, z) along e_k, wrapped into the box; cross = +1
-// when the unwrapped x is >= nx, -1 when < 0 (the read crosses the
+// Lattice vector, opposite and weight class of a direction known at run time
+// (the tables above are compile-time constants of unrolled loops): components
+// in two bits each (value + 1), opposites by their position in the order of
+// make_lattice, checked below.
+constexpr uint64_t pack_components(const int (&e)[kQ]) {
+  uint64_t v = 0;
+  for (int k = 0; k < kQ; ++k) v |= (uint64_t)(e[k] + 1) << (2 * k);
+  return v;
+}
+constexpr uint64_t kPackX = pack_components(kLat.ex), kPackY = pack_components(kLat.ey),
+                   kPackZ = pack_components(kLat.ez);
+__device__ __host__ constexpr int component(uint64_t pack, int k) {
+  return (int)((pack >> (2 * k)) & 3) - 1;
+}
+__device__ __host__ constexpr int opposite(int k) {  // k >= 1
+  return k < 7 ? ((k - 1) ^ 1) + 1 : ((k - 7) ^ 3) + 7;
+}
+constexpr bool opposites_hold() {
+  for (int k = 1; k < kQ; ++k)
+    if (opposite(k) != kLat.opp[k]) return false;
+  return true;
+}
+static_assert(opposites_hold(), "opposite() does not match the lattice order");
+
+// Cell m steps (m = -1, 1, 2) from (x, y, z) along e_k, wrapped into the box;
+// cross = +1 when the unwrapped x is >= nx, -1 when < 0 (the read crosses the
 // x-periodic plane and carries the density jump).
 struct FarNode {
   int c;
   int cross;
 };
-__device__ __forceinline__ int wrap_into(int i, int n) { return ((i % n) + n) % n; }
+__device__ __forceinline__ int wrap_into(int i, int n) {  // -2 <= i <= n + 1, n >= 1
+  i = i < 0 ? i + n : (i >= n ? i - n : i);
+  return i < 0 ? i + n : (i >= n ? i - n : i);
+}
 __device__ __forceinline__ FarNode far_node(const StepParams& p, int x, int y, int z, int k,
                                             int m) {
-  const int X = x + m * kLat.ex[k];
+  const int X = x + m * component(kPackX, k);
   FarNode f;
   f.cross = X >= p.nx ? 1 : (X < 0 ? -1 : 0);
-  f.c = p.t.at(wrap_into(X, p.nx), wrap_into(y + m * kLat.ey[k], p.ny),
-               wrap_into(z + m * kLat.ez[k], p.nz));
+  f.c = p.t.at(wrap_into(X, p.nx), wrap_into(y + m * component(kPackY, k), p.ny),
+               wrap_into(z + m * component(kPackZ, k), p.nz));
   return f;
 }
 
-// Population kk at a far node, with the jump of a crossing read.
-template <typename S, typename C>
-__device__ __forceinline__ C far_value(const S* __restrict__ src, const StepParams& p, FarNode f,
-                                       int kk) {
-  C v = (C)Storage<S>::to_float(src[state_slot<S>(p.t, kk, f.c)]);
-  const C jw = (C)(wclass(kk) == 1 ? p.jump_axis : p.jump_diag);
-  if (f.cross > 0) v -= jw;
-  if (f.cross < 0) v += jw;
+// A parameter in the compute precision: FP64 kernels use the double, the
+// others the FP32 copy that the host rounded.
+template <typename C>
+__device__ __forceinline__ C prm(double d, float f) {
+  if constexpr (sizeof(C) == sizeof(float))
+    return f;
+  else
+    return d;
+}
+
+// A population read at a far node, with the jump of a crossing read.
+template <typename C>
+__device__ __forceinline__ C with_jump(C v, const StepParams& p, int cross, int k) {
+  const C jw = wclass(k) == 1 ? prm<C>(p.jump_axis, p.jump_axisf) : prm<C>(p.jump_diag, p.jump_diagf);
+  if (cross > 0) v -= jw;
+  if (cross < 0) v += jw;
   return v;
 }
 
@@ -622,32 +657,40 @@ __device__ __forceinline__ void stored_moments(const S* __restrict__ src, const 
 // rule that needs a solid node falls back: x_f2 solid -> bounce-back (LIBB
 // and QIBB with q >= 1/2 keep LIBB's q >= 1/2 branch, which needs x_f1
 // only); x_f3 solid -> LIBB (from QIBB) or CLI (from MR).  Unscaled storage
-// (FP32, FP64) only.  m1 holds the density deviation and velocity of the
-// stored state at x (IEBB only), own_j and own_k the stored g_j and g_k at x
-// (the caller loads them once per node).
+// (FP32, FP64) only.  fl is the flag word of x; m1 holds the density
+// deviation and velocity of the stored state at x (IEBB only).
+//
+// Everything the rule may need is requested before the first use, for one
+// memory round trip per link: the wall distance in the solid source's slot,
+// the node's own g_j and g_k, g_j at x_f2, and where the rule uses x_f3 (MR,
+// QIBB) g_j at x_f3, g_k at x_f2 and x_f2's flag word, whose bit j says
+// whether x_f3 = x_f2 - e_j is solid (as bit j of fl does for x_f2).
 template <typename S, typename C>
-__device__ C general_wall_value(const S* __restrict__ src, const uint32_t* __restrict__ flags,
-                                const StepParams& p, int x, int y, int z, int c, int k, C q,
-                                uint32_t fl, const C (&m1)[4], C pulled_j, C own_j, C own_k) {
-  const int j = kLat.opp[k];
+__device__ __forceinline__ C general_wall_value(const S* __restrict__ src,
+                                                const uint32_t* __restrict__ flags,
+                                                const StepParams& p, int x, int y, int z, int c,
+                                                int k, uint32_t fl, const C (&m1)[4]) {
+  const int j = opposite(k);
+  const FarNode n0 = far_node(p, x, y, z, k, -1);
   const FarNode n2 = far_node(p, x, y, z, k, 1);
   const FarNode n3 = far_node(p, x, y, z, k, 2);
-  // x_f2 = x - e_j is the pull source of direction j here, and x_f3 that of
-  // direction j at x_f2, so the flag bits j of x and of x_f2 tell if they
-  // are solid
   const bool f2 = !(fl & (1u << j));
   int rule = p.wall;
-  // x_f3's flag word is read only by the rules that use x_f3
-  const bool wants_f3 = rule == kRuleMR || (rule == kRuleQIBB && q < (C)0.5);
-  const bool f3 = f2 && wants_f3 && !(flags[n2.c] & (1u << j));
-  // g_j at x_f2 is this node's pull in direction j (pulled_j, raw); with the
-  // jump of a read across the x-periodic plane
-  C f2_j = pulled_j;
-  {
-    const C jw = (C)(wclass(j) == 1 ? p.jump_axis : p.jump_diag);
-    if (n2.cross > 0) f2_j -= jw;
-    if (n2.cross < 0) f2_j += jw;
+  const bool far = rule == kRuleMR || rule == kRuleQIBB;
+  const C q = (C)Storage<S>::to_float(src[state_slot<S>(p.t, k, n0.c)]);
+  const C own_j = (C)Storage<S>::to_float(src[state_slot<S>(p.t, j, c)]);
+  const C own_k = (C)Storage<S>::to_float(src[state_slot<S>(p.t, k, c)]);
+  C f2_j = (C)Storage<S>::to_float(src[state_slot<S>(p.t, j, n2.c)]);
+  C f2_k = (C)0, f3_j = (C)0;
+  bool f3 = false;
+  if (far) {
+    f2_k = (C)Storage<S>::to_float(src[state_slot<S>(p.t, k, n2.c)]);
+    f3_j = (C)Storage<S>::to_float(src[state_slot<S>(p.t, j, n3.c)]);
+    f3 = f2 && !(flags[n2.c] & (1u << j));
   }
+  f2_j = with_jump(f2_j, p, n2.cross, j);
+  f2_k = with_jump(f2_k, p, n2.cross, k);
+  f3_j = with_jump(f3_j, p, n3.cross, j);
   if (rule == kRuleMR && !f3) rule = kRuleCLI;
   if (rule == kRuleQIBB && (q < (C)0.5 ? !f3 : !f2)) rule = kRuleLIBB;
   const C one = (C)1, two = (C)2;
@@ -667,9 +710,9 @@ __device__ C general_wall_value(const S* __restrict__ src, const uint32_t* __res
       if (q < (C)0.5)
         return q * (one + two * q) * own_j +
                (one - (C)4 * q * q) * f2_j -
-               q * (one - two * q) * far_value<S, C>(src, p, n3, j);
+               q * (one - two * q) * f3_j;
       return (two * q - one) / q * own_k + own_j / (q * (two * q + one)) +
-             (one - two * q) / (two * q + one) * far_value<S, C>(src, p, n2, k);
+             (one - two * q) / (two * q + one) * f2_k;
     case kRuleIEBB: {
       const C drho1 = m1[0], u1[3] = {m1[1], m1[2], m1[3]};
       C ubf[3], X;
@@ -694,34 +737,97 @@ __device__ C general_wall_value(const S* __restrict__ src, const uint32_t* __res
         ubf[2] = f * u1[2];
         X = (two * q - one) / (tau + (C)0.5);
       }
-      const C eub = (C)kLat.ex[j] * ubf[0] + (C)kLat.ey[j] * ubf[1] + (C)kLat.ez[j] * ubf[2];
-      const C eu1 = (C)kLat.ex[j] * u1[0] + (C)kLat.ey[j] * u1[1] + (C)kLat.ez[j] * u1[2];
+      const C ejx = (C)component(kPackX, j), ejy = (C)component(kPackY, j),
+              ejz = (C)component(kPackZ, j);
+      const C wj = wclass(j) == 1 ? (C)kLat.w[1] : (C)kLat.w[7];
+      const C eub = ejx * ubf[0] + ejy * ubf[1] + ejz * ubf[2];
+      const C eu1 = ejx * u1[0] + ejy * u1[1] + ejz * u1[2];
       const C uu = u1[0] * u1[0] + u1[1] * u1[1] + u1[2] * u1[2];
       const C fstar =
-          (C)kLat.w[j] * (drho1 + (C)3 * eub + (C)4.5 * eu1 * eu1 - (C)1.5 * uu);
+          wj * (drho1 + (C)3 * eub + (C)4.5 * eu1 * eu1 - (C)1.5 * uu);
       return (one - X) * own_j + X * fstar;
     }
     case kRuleMR: {
       if (!f2) return own_j;
       const C d = (one + q) * (one + q);
       const C k1 = (one - two * q - two * q * q) / d, k2 = q * q / d;
-      return k1 * f2_j + k2 * far_value<S, C>(src, p, n3, j) -
-             k1 * own_k - k2 * far_value<S, C>(src, p, n2, k) + own_j;
+      return k1 * f2_j + k2 * f3_j -
+             k1 * own_k - k2 * f2_k + own_j;
     }
     default:
       return own_j;
   }
 }
 
+// The general rules for the wall links of a wavefront's nodes, one link per
+// lane.  Only some lanes of a wavefront have links, and each only in some
+// directions; with the rule run per direction under a branch, every direction
+// that any lane links in cost the whole wavefront the rule's instructions and
+// a memory round trip of its own (18 in a pack of small spheres).  Here the
+// wavefront lists its links in LDS, direction by direction (neighbouring
+// links of one direction then read neighbouring addresses), takes 64 of them
+// per round, and each lane fetches its results back: 160^3 pack of 12
+// spheres (porosity 0.5), MR, FP32: 364 -> 150 us per step; 512^3 block, LIBB /
+// QIBB / IEBB / MR: 2.56 / 3.21 / 2.94 / 3.18 -> 2.52 / 2.58 / 2.78 / 2.58 ms.
+// links is 0 in lanes without links (solid cells, lanes outside the box);
+// every lane of the wavefront must call.  list: kQ * 64 values of LDS of the
+// wavefront's own.
+template <typename S, typename C>
+__device__ __forceinline__ void general_walls(const S* __restrict__ src,
+                                              const uint32_t* __restrict__ flags,
+                                              const StepParams& p, int x, int y, int z, int c,
+                                              uint32_t links, const C (&m1)[4], C* list) {
+  const int lane = (int)__lane_id();
+  uint32_t* entry = reinterpret_cast<uint32_t*>(list);
+  constexpr int W = sizeof(C) / 4;  // entries sit where their results go
+  int total = 0;                    // wavefront-uniform
+#pragma unroll
+  for (int k = 1; k < kQ; ++k) {
+    const unsigned long long m = __ballot((links >> k) & 1u);
+    if (!m) continue;
+    const int at = total + (int)__builtin_amdgcn_mbcnt_hi(
+                               (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if ((links >> k) & 1u) entry[at * W] = (uint32_t)lane | ((uint32_t)k << 8);
+    total += __popcll(m);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (int i0 = 0; i0 < total; i0 += 64) {
+    const int i = i0 + lane;
+    const uint32_t e = i < total ? entry[i * W] : (uint32_t)lane;
+    const int from = (int)(e & 63u), k = (int)(e >> 8);
+    // the node of the link: tiles and cells are this wavefront's
+    const int lx = __shfl(x, from, 64), ly = __shfl(y, from, 64), lc = __shfl(c, from, 64);
+    const uint32_t lf = (uint32_t)__shfl((int)links, from, 64);
+    C lm[4] = {(C)0, (C)0, (C)0, (C)0};
+    if (p.wall == kRuleIEBB) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) lm[q] = __shfl(m1[q], from, 64);
+    }
+    if (i < total) list[i] = general_wall_value<S, C>(src, flags, p, lx, ly, z, lc, k, lf, lm);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
-// A parameter in the compute precision: FP64 kernels use the double, the
-// others the FP32 copy that the host rounded.
+// The results of general_walls into the pulled values of the links' nodes.
 template <typename C>
-__device__ __forceinline__ C prm(double d, float f) {
-  if constexpr (sizeof(C) == sizeof(float))
-    return f;
-  else
-    return d;
+__device__ __forceinline__ void take_walls(uint32_t links, const C* list, C (&g)[kQ]) {
+  int total = 0;
+#pragma unroll
+  for (int k = 1; k < kQ; ++k) {
+    const unsigned long long m = __ballot((links >> k) & 1u);
+    if (!m) continue;
+    const int at = total + (int)__builtin_amdgcn_mbcnt_hi(
+                               (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if ((links >> k) & 1u) g[k] = list[at];
+    total += __popcll(m);
+  }
+}
+
+// LDS bytes of general_walls for a workgroup of `waves` wavefronts.
+inline size_t general_walls_lds(int waves, size_t compute_bytes) {
+  return (size_t)waves * kQ * 64 * compute_bytes;
 }
 
 // Pressure jump of direction k in the units of the stored values (g units
@@ -862,21 +968,16 @@ __device__ __forceinline__ void finish_node(typename ComputeOf<S>::type (&g)[kQ]
   round_node<S>(g, p, c, out);
 }
 
-// One time step for the node (x, y, z), fluid, with flag word fl: pull (one
-// lane, one node), the general wall rules, then finish_node (edge_x as
-// there).  SPLIT selects pulls from scalar per-direction bases plus 32-bit
-// lane offsets (state_at); without it every lane forms 64-bit addresses.
-// The split form needs about 40 more scalar registers; in the kernels with
-// the general wall rules it made the compiler spill scalar registers (5-11%
-// slower at 512^3), and the batch kernel, whose cell base comes from a table,
-// got no scalar-base loads from it and was 1% slower, so only the
-// single-domain SBB / CLI kernels use it.
-template <typename S, int COLL, int WALL, bool SPLIT>
-__device__ __forceinline__ void update_node(const S* __restrict__ src, S (&out)[kQ],
-                                            const uint32_t* __restrict__ flags,
-                                            const StepParams& p, int x, int y, int z, int c,
-                                            uint32_t fl, bool edge_x,
-                                            typename ComputeOf<S>::type (&mom)[5]) {
+// The 19 pulled raw stored values of a node.  SPLIT selects pulls from scalar
+// per-direction bases plus 32-bit lane offsets (state_at); without it every
+// lane forms 64-bit addresses.  The split form needs about 40 more scalar
+// registers; in the kernels with the general wall rules it made the compiler
+// spill scalar registers (5-11% slower at 512^3), and the batch kernel, whose
+// cell base comes from a table, got no scalar-base loads from it and was 1%
+// slower, so only the single-domain SBB / CLI kernels use it.
+template <typename S, bool SPLIT>
+__device__ __forceinline__ void pull_node(const S* __restrict__ src, const StepParams& p, int x,
+                                          int y, int z, typename ComputeOf<S>::type (&g)[kQ]) {
   using C = typename ComputeOf<S>::type;
   using St = Storage<S>;
   const int nx = p.nx, plane = p.t.plane;
@@ -890,9 +991,7 @@ __device__ __forceinline__ void update_node(const S* __restrict__ src, S (&out)[
   n.zs[0] = (z == 0 ? p.nz - 1 : z - 1) * plane;
   n.zs[1] = z * plane;
   n.zs[2] = (z == p.nz - 1 ? 0 : z + 1) * plane;
-
-  C g[kQ];
-  // pull: direction k arrives from x - e_k (raw stored values)
+  // direction k arrives from x - e_k
 #pragma unroll
   for (int k = 0; k < kQ; ++k) {
     if constexpr (SPLIT)
@@ -902,47 +1001,64 @@ __device__ __forceinline__ void update_node(const S* __restrict__ src, S (&out)[
       g[k] = (C)St::to_float(
           *state_ptr<S>(src, p.t, k, n.at(-kLat.ex[k], -kLat.ey[k], -kLat.ez[k])));
   }
+}
 
-  // wall links: the pulled raw value is the stored coefficient a (CLI) or
-  // the wall distance q (general rules)
+// One time step for the node (x, y, z), fluid, with flag word fl, SBB and CLI
+// walls: pull (one lane, one node), then finish_node (edge_x as there).
+template <typename S, int COLL, int WALL, bool SPLIT>
+__device__ __forceinline__ void update_node(const S* __restrict__ src, S (&out)[kQ],
+                                            const StepParams& p, int x, int y, int z, int c,
+                                            uint32_t fl, bool edge_x,
+                                            typename ComputeOf<S>::type (&mom)[5]) {
+  static_assert(WALL != kGEN, "the general rules take update_node_general");
+  typename ComputeOf<S>::type g[kQ];
+  pull_node<S, SPLIT>(src, p, x, y, z, g);
+  // wall links: the pulled raw value is the stored coefficient a (CLI)
   S own[kQ];
   if (fl & kLinkMask) {
     // The node's own stored values of every moving direction (the wall rules
     // need g_j and g_k at x), all requested before the first use: one memory
     // round trip per boundary node instead of one per link direction (512^3
-    // sphere pack, FP32 CLI: 2.84 -> 2.56 ms per step).  IEBB's moments at x
-    // come from the same values.  (64-bit lane addresses: with scalar bases
-    // per direction as for the pulls, the boundary wavefronts' extra scalar
-    // work made the 512^3 sphere-pack step 3% slower.)
+    // sphere pack, FP32 CLI: 2.84 -> 2.56 ms per step).  (64-bit lane
+    // addresses: with scalar bases per direction as for the pulls, the
+    // boundary wavefronts' extra scalar work made the 512^3 sphere-pack step
+    // 3% slower.)
 #pragma unroll
     for (int k = 1; k < kQ; ++k) own[k] = *state_ptr<S>(src, p.t, k, c);
-    if constexpr (WALL == kGEN) {
-      C m1[4] = {(C)0, (C)0, (C)0, (C)0};
-      if (p.wall == kRuleIEBB) {
-        own[0] = src[state_slot<S>(p.t, 0, c)];
-#pragma unroll
-        for (int kk = 0; kk < kQ; ++kk) {
-          const C v = (C)St::to_float(own[kk]);
-          m1[0] += v;
-          m1[1] += (C)kLat.ex[kk] * v;
-          m1[2] += (C)kLat.ey[kk] * v;
-          m1[3] += (C)kLat.ez[kk] * v;
-        }
-      }
-      // the pulled raw value is the link's wall distance q.  g[j] may already
-      // hold a wall value when direction j is a link too; the rules use the
-      // pull g[j] only when x_f2 = x - e_j is fluid, i.e. j is no link.
-#pragma unroll
-      for (int k = 1; k < kQ; ++k) {
-        if (fl & (1u << k)) {
-          const int j = kLat.opp[k];
-          g[k] = general_wall_value<S, C>(src, flags, p, x, y, z, c, k, g[k], fl, m1, g[j],
-                                          (C)St::to_float(own[j]), (C)St::to_float(own[k]));
-        }
-      }
-    }
   }
   finish_node<S, COLL, WALL>(g, own, out, p, x, c, fl, edge_x, mom);
+}
+
+// update_node for the general wall rules.  Every lane of the wavefront calls;
+// fluid says whether the lane's cell is stepped (out and mom are set then).
+template <typename S, int COLL>
+__device__ __forceinline__ void update_node_general(
+    const S* __restrict__ src, S (&out)[kQ], const uint32_t* __restrict__ flags,
+    const StepParams& p, int x, int y, int z, int c, uint32_t fl, bool fluid, bool edge_x,
+    typename ComputeOf<S>::type (&mom)[5], typename ComputeOf<S>::type* list) {
+  using C = typename ComputeOf<S>::type;
+  const uint32_t links = fluid ? fl & kLinkMask : 0u;
+  const bool walls = __ballot(links != 0) != 0;
+  // The links' values first, while the node's own 19 values take no registers
+  // (FP64 batches spilled with the pulls before them).
+  if (walls) {
+    C m1[4] = {(C)0, (C)0, (C)0, (C)0};
+    if (p.wall == kRuleIEBB && links) {
+      C u1[3];
+      stored_moments<S, C>(src, p.t, c, m1[0], u1);
+      m1[1] = u1[0];
+      m1[2] = u1[1];
+      m1[3] = u1[2];
+    }
+    general_walls<S, C>(src, flags, p, x, y, z, c, links, m1, list);
+  }
+  C g[kQ];
+  if (fluid) pull_node<S, false>(src, p, x, y, z, g);
+  if (walls) take_walls<C>(links, list, g);
+  if (fluid) {
+    const S own[kQ] = {};
+    finish_node<S, COLL, kGEN>(g, own, out, p, x, c, fl, edge_x, mom);
+  }
 }
 
 // The 19 values a solid cell writes: its wall-link slots (flag bit k: the
@@ -1097,29 +1213,31 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(const S* __restrict_
                                                             const StepParams p,
                                                             double* __restrict__ partials) {
   using C = typename ComputeOf<S>::type;
-  constexpr bool kSplit = WALL != kGEN;  // (update_node)
+  constexpr bool kSplit = WALL != kGEN;  // (pull_node)
   const int z = blockIdx.z;
   const TileCell tc = step_tile_cell(p, z);
   const uint8_t k = tc.inside ? cls[tc.c] : kClsSolid;
+  const bool fluid = !(k & kClsSolid);
   const bool edge_x = __ballot(tc.x == 0 || tc.x == p.nx - 1) != 0;
-  if constexpr (!RED) {
-    if (k & kClsSolid) return;
-    const uint32_t fl = flag_word(k, flags, tc.c);
-    S out[kQ];
-    C mom[5];
-    update_node<S, COLL, WALL, kSplit>(src, out, flags, p, tc.x, tc.y, z, tc.c, fl, edge_x, mom);
+  double v[kRedVals] = {0, 0, 0, 0, 0, 0, 0, 0};
+  S out[kQ];
+  C mom[5];
+  if constexpr (WALL == kGEN) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char wall_lds[];
+    if (__ballot(fluid) != 0) {
+      const uint32_t fl = fluid ? flag_word(k, flags, tc.c) : 0u;
+      update_node_general<S, COLL>(src, out, flags, p, tc.x, tc.y, z, tc.c, fl, fluid, edge_x,
+                                   mom, reinterpret_cast<C*>(wall_lds) + threadIdx.y * kQ * 64);
+    }
+  } else {
+    if (fluid)
+      update_node<S, COLL, WALL, kSplit>(src, out, p, tc.x, tc.y, z, tc.c,
+                                         flag_word(k, flags, tc.c), edge_x, mom);
+  }
+  if (fluid) {
     store_node<S, NT, kSplit>(dst, out, p.t, (long long)z * p.t.plane, tc.r);
     if constexpr (WALL == kGEN) store_side<C>(p, k, tc.c, mom);
-  } else {
-    double v[kRedVals] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (!(k & kClsSolid)) {
-      const uint32_t fl = flag_word(k, flags, tc.c);
-      S out[kQ];
-      C mom[5];
-      update_node<S, COLL, WALL, kSplit>(src, out, flags, p, tc.x, tc.y, z, tc.c, fl, edge_x,
-                                         mom);
-      store_node<S, NT, kSplit>(dst, out, p.t, (long long)z * p.t.plane, tc.r);
-      if constexpr (WALL == kGEN) store_side<C>(p, k, tc.c, mom);
+    if constexpr (RED) {
       const double rho = mom[0], ux = mom[1], uy = mom[2], uz = mom[3];
       const double u2 = ux * ux + uy * uy + uz * uz;
       v[0] = ux;
@@ -1132,6 +1250,8 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(const S* __restrict_
         v[5] = 1.0;
       v[6] = isfinite((double)mom[4]) ? (double)mom[4] : 0.0;
     }
+  }
+  if constexpr (RED) {
     const int kind[kRedVals] = {0, 0, 0, 0, 1, 0, 1, 0};
     block_reduce<kRedVals>(v, kind, partials + step_block_id() * kRedVals);
   }
@@ -1426,13 +1546,22 @@ __global__ __launch_bounds__(kBatchThreads) void batch_step_kernel(
     const uint32_t fl = tc.inside ? flag_word(k, f, c) : kSolid;
     const unsigned long long fluid = __ballot(!solid);
     const bool edge_x = __ballot(tc.x == 0 || tc.x == p.nx - 1) != 0;
-    if (!solid_stores<S>(p.solid_writes, solid, fluid)) continue;
+    const bool stores = solid_stores<S>(p.solid_writes, solid, fluid);
     S out[kQ];
     C mom[5];
-    if (solid)
+    if constexpr (WALL == kGEN) {
+      extern __shared__ __attribute__((aligned(16))) unsigned char wall_lds[];
+      if (fluid != 0)
+        update_node_general<S, COLL>(s, out, f, p, tc.x, tc.y, z, c, fl, !solid, edge_x, mom,
+                                     reinterpret_cast<C*>(wall_lds) + threadIdx.y * kQ * 64);
+    }
+    if (!stores) continue;
+    if (solid) {
       solid_node<S>(s, out, p.t, c, fl);
-    else
-      update_node<S, COLL, WALL, false>(s, out, f, p, tc.x, tc.y, z, c, fl, edge_x, mom);
+    } else {
+      if constexpr (WALL != kGEN)
+        update_node<S, COLL, WALL, false>(s, out, p, tc.x, tc.y, z, c, fl, edge_x, mom);
+    }
     if (tc.inside) store_node<S, NT, false>(d, out, p.t, (long long)z * p.t.plane, tc.r);
     if (solid) continue;
     if constexpr (RED) {
@@ -1647,23 +1776,45 @@ __global__ __launch_bounds__(kRedThreads) void reduce_state_kernel(const S* __re
 }
 
 // Momentum-exchange force over the wall links (f = g + w), same wall rule as
-// the step kernel.  Threads walk the tiled addresses; padding cells are solid.
+// the step kernel.  One thread takes one link of the list that bind laid out
+// (the element of the solid pull source's slot, in cell order): direction and
+// node follow from the element's place in the state.  Bound by the gathers of
+// a link (own values and x_f2, a cache line each); against one thread per
+// cell walking its links one after the other, 512^3 block (8.3 M links), CLI
+// FP32: 2.30 -> 0.23 ms.
 template <typename S, int WALL>
 __global__ __launch_bounds__(kRedThreads) void drag_kernel(const S* __restrict__ src,
                                                            const uint32_t* __restrict__ flags,
                                                            const StepParams p,
+                                                           const long long* __restrict__ slot,
+                                                           long long n_links,
                                                            double* __restrict__ partials) {
   double v[kRedVals] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const int naddr = p.t.plane * p.nz;
-  for (long long cc = blockIdx.x * kRedThreads + threadIdx.x; cc < naddr;
-       cc += (long long)gridDim.x * kRedThreads) {
-    const int c = (int)cc;
-    const uint32_t fl = flags[c];
-    if ((fl & kSolid) || !(fl & kLinkMask)) continue;
-    int x, y, z;
-    p.t.coords(c, x, y, z);
-    double m1[4] = {0, 0, 0, 0};
+  for (long long i = blockIdx.x * (long long)kRedThreads + threadIdx.x; i < n_links;
+       i += (long long)gridDim.x * kRedThreads) {
+    // element -> direction k and address of the solid source (Tiling::slot)
+    const long long e = slot[i];
+    int k, a;
+    if (sizeof(S) == 2) {  // direction planes
+      k = (int)(e / p.t.run_pitch);
+      a = (int)(e - k * p.t.run_pitch);
+    } else {
+      const unsigned long long r = (unsigned long long)e >> p.t.run_log2;
+      const unsigned long long run = r / (unsigned)kQ;
+      k = (int)(r - run * kQ);
+      a = (int)((run << p.t.run_log2) | ((unsigned long long)e & ((1ull << p.t.run_log2) - 1)));
+    }
+    int sx, sy, sz;
+    p.t.coords(a, sx, sy, sz);
+    const int j = opposite(k);
+    const int x = wrap_into(sx + component(kPackX, k), p.nx),
+              y = wrap_into(sy + component(kPackY, k), p.ny),
+              z = wrap_into(sz + component(kPackZ, k), p.nz);
+    const int c = p.t.at(x, y, z);
+    const double own_j = stored_to_g<S>(src[state_slot<S>(p.t, j, c)], j, p.sigma);
+    double back = own_j;
     if constexpr (WALL == kGEN) {
+      double m1[4] = {0, 0, 0, 0};
       if (p.wall == kRuleIEBB) {
         double u1[3];
         stored_moments<S, double>(src, p.t, c, m1[0], u1);
@@ -1671,39 +1822,19 @@ __global__ __launch_bounds__(kRedThreads) void drag_kernel(const S* __restrict__
         m1[2] = u1[1];
         m1[3] = u1[2];
       }
+      back = general_wall_value<S, double>(src, flags, p, x, y, z, c, k, flags[c], m1);
+    } else if constexpr (WALL == kCLI) {
+      const FarNode n2 = far_node(p, x, y, z, k, 1);
+      const double coef = (double)Storage<S>::to_float(src[e]);
+      const double far_j = with_jump(
+          stored_to_g<S>(src[state_slot<S>(p.t, j, n2.c)], j, p.sigma), p, n2.cross, j);
+      back = coef * far_j - coef * stored_to_g<S>(src[state_slot<S>(p.t, k, c)], k, p.sigma) + own_j;
     }
-    for (int k = 1; k < kQ; ++k) {
-      if (!(fl & (1u << k))) continue;
-      const int j = kLat.opp[k];
-      const double own_j = stored_to_g<S>(src[state_slot<S>(p.t, j, c)], j, p.sigma);
-      double back = own_j;
-      if constexpr (WALL == kGEN) {
-        const int sx = (x - kLat.ex[k] + p.nx) % p.nx, sy = (y - kLat.ey[k] + p.ny) % p.ny,
-                  sz = (z - kLat.ez[k] + p.nz) % p.nz;
-        const double q = (double)Storage<S>::to_float(src[state_slot<S>(p.t, k, p.t.at(sx, sy, sz))]);
-        const FarNode n2 = far_node(p, x, y, z, k, 1);
-        back = general_wall_value<S, double>(src, flags, p, x, y, z, c, k, q, fl, m1,
-                                             (double)Storage<S>::to_float(src[state_slot<S>(p.t, j, n2.c)]),
-                                             (double)Storage<S>::to_float(src[state_slot<S>(p.t, j, c)]),
-                                             (double)Storage<S>::to_float(src[state_slot<S>(p.t, k, c)]));
-      } else if (WALL == kCLI) {
-        const int sx = (x - kLat.ex[k] + p.nx) % p.nx, sy = (y - kLat.ey[k] + p.ny) % p.ny,
-                  sz = (z - kLat.ez[k] + p.nz) % p.nz;
-        const double a = (double)Storage<S>::to_float(src[state_slot<S>(p.t, k, p.t.at(sx, sy, sz))]);
-        const int tx = x + kLat.ex[k];
-        const int fx = (tx + p.nx) % p.nx, fy = (y + kLat.ey[k] + p.ny) % p.ny,
-                  fz = (z + kLat.ez[k] + p.nz) % p.nz;
-        double far_j = stored_to_g<S>(src[state_slot<S>(p.t, j, p.t.at(fx, fy, fz))], j, p.sigma);
-        const double jw = kLat.w[k] == 1.0 / 18.0 ? p.jump_axis : p.jump_diag;
-        if (tx >= p.nx) far_j -= jw;
-        if (tx < 0) far_j += jw;
-        back = a * far_j - a * stored_to_g<S>(src[state_slot<S>(p.t, k, c)], k, p.sigma) + own_j;
-      }
-      const double tot = (own_j + kLat.w[j]) + (back + kLat.w[k]);
-      v[0] += kLat.ex[j] * tot;
-      v[1] += kLat.ey[j] * tot;
-      v[2] += kLat.ez[j] * tot;
-    }
+    const double wk = wclass(k) == 1 ? kLat.w[1] : kLat.w[7];
+    const double tot = (own_j + wk) + (back + wk);
+    v[0] += component(kPackX, j) * tot;
+    v[1] += component(kPackY, j) * tot;
+    v[2] += component(kPackZ, j) * tot;
   }
   const int kind[kRedVals] = {0, 0, 0, 0, 0, 0, 0, 0};
   block_reduce<kRedVals>(v, kind, partials + blockIdx.x * kRedVals);

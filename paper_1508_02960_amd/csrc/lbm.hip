@@ -353,6 +353,11 @@ StepParams step_params(lbm_domain d) {
 // interpolated rules share the general one (FP32/FP64 storage only).
 int wall_template(int wall) { return wall <= LBM_WALL_CLI ? wall : kGEN; }
 
+// LDS bytes of a step workgroup of `waves` wavefronts (general wall rules).
+size_t walls_lds(lbm_domain d, int waves) {
+  return wall_template(d->p.wall) == kGEN ? general_walls_lds(waves, d->elem == 8 ? 8 : 4) : 0;
+}
+
 const void* step_function(lbm_domain d, bool red) {
   return with_storage(d->p.storage, [&](auto tag) -> const void* {
     using S = decltype(tag);
@@ -383,7 +388,8 @@ lbm_status launch_step(lbm_domain d, bool red) {
   double* part = d->partials;
   void* args[] = {(void*)&src, (void*)&dst, (void*)&cl, (void*)&fl, (void*)&sp, (void*)&part};
   const dim3 grid = step_grid(d), block = step_block(d);
-  HIP_OK(d, hipLaunchKernel(step_function(d, red), grid, block, args, 0, d->stream));
+  HIP_OK(d, hipLaunchKernel(step_function(d, red), grid, block, args, walls_lds(d, d->waves),
+                            d->stream));
   d->cur = 1 - d->cur;
   ++d->step_count;
   return LBM_OK;
@@ -411,7 +417,7 @@ lbm_status build_graph(lbm_domain d, int from) {
     kp.func = const_cast<void*>(fn);
     kp.gridDim = grid;
     kp.blockDim = block;
-    kp.sharedMemBytes = 0;
+    kp.sharedMemBytes = (unsigned)walls_lds(d, d->waves);
     kp.kernelParams = args;
     kp.extra = nullptr;
     hipGraphNode_t node;
@@ -517,8 +523,8 @@ struct BatchArgs {
 lbm_status launch_batch_step(lbm_domain d, bool red, const int* act) {
   BatchArgs a;
   a.fill(d, d->cur, act, false);
-  HIP_OK(d, hipLaunchKernel(batch_function(d, red), batch_grid(d), batch_block(d), a.ptrs, 0,
-                            d->stream));
+  HIP_OK(d, hipLaunchKernel(batch_function(d, red), batch_grid(d), batch_block(d), a.ptrs,
+                            walls_lds(d, d->bby), d->stream));
   d->cur = 1 - d->cur;
   ++d->step_count;
   return LBM_OK;
@@ -542,12 +548,12 @@ lbm_status build_batch_graph(lbm_domain d, int from, int reps, int interval, dou
   hipGraph_t g = nullptr;
   HIP_OK(d, hipGraphCreate(&g, 0));
   hipGraphNode_t prev = nullptr;
-  auto add = [&](const void* fn, dim3 grid, dim3 block, void** args) -> hipError_t {
+  auto add = [&](const void* fn, dim3 grid, dim3 block, size_t lds, void** args) -> hipError_t {
     hipKernelNodeParams kp{};
     kp.func = const_cast<void*>(fn);
     kp.gridDim = grid;
     kp.blockDim = block;
-    kp.sharedMemBytes = 0;
+    kp.sharedMemBytes = (unsigned)lds;
     kp.kernelParams = args;
     kp.extra = nullptr;
     hipGraphNode_t node;
@@ -565,7 +571,7 @@ lbm_status build_batch_graph(lbm_domain d, int from, int reps, int interval, dou
       const bool red = i == interval - 1;
       BatchArgs a;
       a.fill(d, parity, d->d_active, true);
-      e = add(batch_function(d, red), grid, block, a.ptrs);
+      e = add(batch_function(d, red), grid, block, walls_lds(d, d->bby), a.ptrs);
       parity = 1 - parity;
     }
     if (e != hipSuccess) break;
@@ -574,7 +580,7 @@ lbm_status build_batch_graph(lbm_domain d, int from, int reps, int interval, dou
     const int* act = d->d_active;
     double* res = d->d_results;
     void* rargs[] = {(void*)&part, (void*)&bpc, (void*)&act, (void*)&res};
-    e = add((const void*)cell_reduce_kernel, dim3(d->batch), dim3(kRedThreads), rargs);
+    e = add((const void*)cell_reduce_kernel, dim3(d->batch), dim3(kRedThreads), 0, rargs);
     if (e != hipSuccess) break;
     const double* resc = d->d_results;
     CellStatus* st = d->d_status;
@@ -589,7 +595,7 @@ lbm_status build_batch_graph(lbm_domain d, int from, int reps, int interval, dou
     int pn = parity;
     void* cargs[] = {(void*)&resc, (void*)&st, (void*)&actw, (void*)&lst, (void*)&nact,
                      (void*)&ncells, (void*)&inv, (void*)&t, (void*)&ms, (void*)&iv, (void*)&pn};
-    e = add((const void*)batch_check_kernel, dim3(1), dim3(1024), cargs);
+    e = add((const void*)batch_check_kernel, dim3(1), dim3(1024), 0, cargs);
   }
   if (e != hipSuccess) {
     (void)hipGraphDestroy(g);
@@ -1408,22 +1414,23 @@ LBM_API lbm_status lbm_drag(lbm_domain d, double F[3]) {
   // the drag kernel computes in FP64 and sums IEBB's x_f2 values itself
   sp.side_in = sp.side_out = nullptr;
   const bool cli = d->p.wall == LBM_WALL_CLI;
+  const long long nl = (long long)d->geo.link_cell.size();
   const bool gen = wall_template(d->p.wall) == kGEN;
   with_storage(d->p.storage, [&](auto tag) {
     using S = decltype(tag);
     if constexpr (kUnscaledStorage<S>) {
       if (gen) {
         drag_kernel<S, kGEN><<<kRedBlocks, kRedThreads, 0, d->stream>>>(
-            (const S*)d->buf[d->cur], d->flags, sp, d->partials);
+            (const S*)d->buf[d->cur], d->flags, sp, d->link_slot, nl, d->partials);
         return 0;
       }
     }
     if (cli)
       drag_kernel<S, kCLI><<<kRedBlocks, kRedThreads, 0, d->stream>>>(
-          (const S*)d->buf[d->cur], d->flags, sp, d->partials);
+          (const S*)d->buf[d->cur], d->flags, sp, d->link_slot, nl, d->partials);
     else
       drag_kernel<S, kSBB><<<kRedBlocks, kRedThreads, 0, d->stream>>>(
-          (const S*)d->buf[d->cur], d->flags, sp, d->partials);
+          (const S*)d->buf[d->cur], d->flags, sp, d->link_slot, nl, d->partials);
     return 0;
   });
   reduce_final_kernel<<<1, kRedThreads, 0, d->stream>>>(d->partials, kRedBlocks, 0, d->result);
