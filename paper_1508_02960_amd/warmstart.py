@@ -58,6 +58,7 @@ def _nn():
         "nn_concat_channels": [vp, vp, vp, i64, i32, i32, vp],
         "nn_split_channels": [vp, vp, vp, i64, i32, i32, vp],
         "nn_add": [vp, vp, i64, vp],
+        "nn_coarse_pack_input": [vp, i32, i32, vp, vp],
         "nn_prolongate2": [vp, vp, i32, i32, i32, i32, i32, i32, vp, vp],
         "nn_warm_start_fields": [vp, i32, vp, vp, i32, i32, i32, i32, f64, f64, vp],
         "nn_masked_mse": [vp, vp, vp, vp, vp, i32, i64, i32, i32, f64, vp],
@@ -80,7 +81,7 @@ NN_EXPORTS = (
     "nn_pool2_forward",
     "nn_pool2_backward", "nn_upsample2_forward", "nn_upsample2_backward", "nn_concat_channels",
     "nn_split_channels", "nn_add", "nn_masked_mse", "nn_adam", "nn_prolongate2",
-    "nn_warm_start_fields",
+    "nn_warm_start_fields", "nn_coarse_pack_input",
 )
 
 
@@ -99,7 +100,8 @@ class _Ctx:
 
         self.torch = torch
         self.dev = torch.device(device if device is not None else "cuda")
-        self.stream = C.c_void_p(torch.cuda.current_stream(self.dev).cuda_stream)
+        self.torch_stream = torch.cuda.current_stream(self.dev)
+        self.stream = C.c_void_p(self.torch_stream.cuda_stream)
 
     def f32(self, *shape):
         return self.torch.empty(shape, dtype=self.torch.float32, device=self.dev)
@@ -213,6 +215,7 @@ class UNet:
         self.head.refresh()
         self.step_count = 0
         self.scale = 1.0  # target units per output unit
+        self._target_scale = (None, None)
 
     def layers(self):
         return self.enc + self.dec + [self.head]
@@ -314,6 +317,17 @@ class UNet:
         return (float(total.item()) if sync else total), grad
 
     # ------------------------------------------------------ use and storage
+    def target_scale(self, used: int):
+        """Device factors of the first `used` output channels in the two-grid
+        prolongation: the output scale times 4 (velocity) or 2 (density)."""
+        key = (self.scale, used)
+        if self._target_scale[0] != key:
+            lengths = [4.0] * min(used, 3) + [2.0] * max(used - 3, 0)
+            t = self.ctx.torch
+            self._target_scale = (key, t.tensor([self.scale * s for s in lengths],
+                                                dtype=t.float32, device=self.ctx.dev))
+        return self._target_scale[1]
+
     def predict(self, fluid: np.ndarray, used: int = 4) -> np.ndarray:
         """Targets (nz, ny, nx, used) for one fluid mask (edges multiples of
         8), in target units (the output times self.scale)."""
@@ -492,18 +506,23 @@ def prolongate2(t: np.ndarray) -> np.ndarray:
 
 
 def predict_two_grid_device(net, spheres, edge: int, out=None, used: int = 4):
-    """Two-grid prediction of a pack of edge^3 (edge a multiple of 16): the
-    network on coarse_fluid's grid, then the prolongation of prolongate2 on
-    the device (nn_prolongate2, with the network's output scale and the
-    doubled lengths in the channel scale); target units, a device tensor
-    (edge,)*3 + (used,), written into out if given."""
+    """Two-grid prediction of a pack of edge^3 (edge a multiple of 16), on the
+    device: the mask of coarse_fluid (nn_coarse_pack_input), the network, and
+    the prolongation of prolongate2 (nn_prolongate2, with the network's output
+    scale and the doubled lengths in the channel scale); target units, a device
+    tensor (edge,)*3 + (used,), written into out if given."""
     lib = _nn()
     ctx = net.ctx
-    t = ctx.torch
     ec = edge // 2
-    y = net.forward(network_input(ctx, coarse_fluid(spheres, edge)[None].astype(np.uint8)))
-    lengths = [4.0] * min(used, 3) + [2.0] * max(used - 3, 0)
-    scale = t.tensor([net.scale * s for s in lengths], dtype=t.float32, device=ctx.dev)
+    if edge % 2 or edge > 2048:
+        x = network_input(ctx, coarse_fluid(spheres, edge)[None].astype(np.uint8))
+    else:
+        sp = np.ascontiguousarray(np.reshape(spheres, (-1, 4)), np.float64)
+        x = ctx.bf(1, ec, ec, ec, IN_CH)
+        _chk(lib.nn_coarse_pack_input(sp.ctypes.data_as(C.c_void_p), len(sp), edge, _p(x),
+                                      ctx.stream), "coarse input")
+    y = net.forward(x)
+    scale = net.target_scale(used)
     fine = out if out is not None else ctx.f32(edge, edge, edge, used)
     _chk(lib.nn_prolongate2(_p(y), _p(fine), 1, ec, ec, ec, int(y.shape[-1]), used, _p(scale),
                             ctx.stream), "prolongate2")
@@ -527,7 +546,13 @@ def warm_fields_device(ctx, t, fluid, delta_rho: float, tau: float):
     if (tuple(t.shape[:-1]) != (n, d, h, w) or t.shape[-1] < 3 or t.dtype != th.float32
             or not t.is_contiguous() or not t.is_cuda):
         raise ValueError(f"targets {tuple(t.shape)} do not match the masks {fluid.shape}")
-    f = th.from_numpy(np.ascontiguousarray(fluid, np.uint8)).to(ctx.dev)
+    # the masks through pinned memory on the kernels' own stream: the copy to the
+    # device then waits there, not here, and the host's copy of the masks runs
+    # beside the network's kernels
+    host = th.empty(fluid.shape, dtype=th.uint8, pin_memory=True)
+    host.numpy()[...] = fluid
+    with th.cuda.stream(ctx.torch_stream):
+        f = host.to(ctx.dev, non_blocking=True)
     fields = th.empty((4, n * d * h * w), dtype=th.float64, device=ctx.dev)
     factor = observables.pressure_gradient(delta_rho, w) / observables.viscosity(tau)
     _chk(lib.nn_warm_start_fields(_p(t), int(t.shape[-1]), _p(f), _p(fields), n, d, h, w,

@@ -132,3 +132,24 @@ def test_warm_start_fields_kernel_matches_host():
         assert np.array_equal(got[1:, b], u)
     with pytest.raises(ValueError):
         W.warm_fields_device(ctx, torch.from_numpy(t[:1]).to(ctx.dev), fluid, delta_rho, tau)
+
+
+@pytest.mark.parametrize("edge,n", [(2, 1), (16, 1), (32, 27), (48, 64), (48, 65), (36, 150)])
+def test_coarse_pack_input_matches_host(edge, n):
+    """nn_coarse_pack_input against warmstart.coarse_fluid, node by node, for
+    one launch (up to 64 spheres) and several, spheres across the box's faces."""
+    import ctypes as C
+
+    ctx = W._Ctx("cuda")
+    rng = np.random.default_rng(edge + n)
+    r = rng.uniform(0.05, 0.3, (n, 1)) * edge / max(1.0, (n / 8) ** (1 / 3))
+    sp = np.hstack([rng.uniform(0.0, edge, (n, 3)), r])
+    ec = edge // 2
+    x = ctx.bf(1, ec, ec, ec, W.IN_CH)
+    x.fill_(7.0)
+    assert W._nn().nn_coarse_pack_input(sp.ctypes.data_as(C.c_void_p), n, edge, W._p(x),
+                                        ctx.stream) == 0
+    want = W.network_input(ctx, W.coarse_fluid(sp, edge)[None].astype(np.uint8))
+    assert ctx.torch.equal(x, want)
+    assert W._nn().nn_coarse_pack_input(sp.ctypes.data_as(C.c_void_p), n, edge + 1, W._p(x),
+                                        ctx.stream) != 0
