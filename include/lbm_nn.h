@@ -106,14 +106,6 @@ lbm_status nn_pool2_backward(const float* dy, float* dx, int n, int d, int h, in
 lbm_status nn_prolongate2(const float* x, float* y, int n, int d, int h, int w_, int cx, int c,
                           const float* scale, void* stream);
 
-/* Network input of a periodic pack of spheres on the grid of half the
- * resolution (the two-grid start): x (bf16, ec,ec,ec,8 with ec = edge / 2) is 1
- * in channel 0 where the coarse node at fine position 2j + 1/2 lies in no sphere
- * or periodic image (strictly inside is solid), 0 elsewhere.  spheres: host
- * double[4 * n], rows cx, cy, cz, r in fine lattice units, read before the call
- * returns; box edge `edge` (even). */
-lbm_status nn_coarse_pack_input(const double* spheres, int n, int edge, void* x, void* stream);
-
 /* Start fields of a warm start for lbm_init_equilibrium_device, from the
  * predicted targets t (float, n,d,h,w,cx; velocity targets in channels 0-2,
  * cx >= 3) and the fluid mask (uint8, n,d,h,w; nonzero = fluid).  fields

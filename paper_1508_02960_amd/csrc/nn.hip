@@ -12,7 +12,7 @@
 #include <cstdint>
 #include <cstring>
 
-#include "lbm_nn.h"
+#include "lbm_nn_prepared.h"
 
 #define NN_API extern "C" __attribute__((visibility("default")))
 
@@ -85,6 +85,17 @@ __device__ __forceinline__ long long neighbour(int n, int z, int y, int x, int t
   return (((long long)n * s.d + zz) * s.h + yy) * s.w + xx;
 }
 
+// Packed weights of a convolution (nn_conv3d_pack_weights): the MFMA weight
+// operands in the order the forward kernels read them.  Fragment (row tile ct,
+// step q) holds the 16 rows 16 ct.. of output channels and the four octets
+// 4 q.. of K = 27 ci, lane l's 16 bytes (row l % 16, octet l / 16) at 16 l; zeros
+// past the last row or octet.  A fragment is then one 1 KB run, where the
+// rows of w[co][27][ci] give 16 segments of 64 bytes (the
+// weight reads of the spatial kernel: 192 -> 64 channels at 32^3 x 4 101 -> 70 us,
+// 1250 TFLOP/s; 96 -> 32 at 64^3 x 4 215 -> 190 us; of the halo kernel: 128 -> 256 at
+// 8^3 x 4 31 -> 14 us, 384 -> 128 at one 16^3 box 83 -> 34 us).
+__host__ __device__ __forceinline__ int k_steps(int ci) { return (27 * (ci >> 3) + 3) >> 2; }
+
 // ---------------------------------------------------------------- forward
 // y[m][co] = bias[co] + sum_{tap, ci} x[m + off(tap)][ci] * w[co][tap][ci]:
 // an implicit GEMM with M = voxels, N = co and K = 27 ci (ci % 8 == 0).  MFMA
@@ -103,7 +114,7 @@ constexpr int kPad = 8;
 // the tap/channel position of the thread's 8-element granule, advanced
 // incrementally.  The next stage's global loads are issued into registers
 // before the current stage's MFMAs (one stage of prefetch).
-template <int BN, bool ACT>
+template <int BN, bool PK, bool ACT>
 __global__ __launch_bounds__(256) void conv_fwd_tiled_kernel(const uint16_t* __restrict__ x,
                                                              const uint16_t* __restrict__ w,
                                                              const float* __restrict__ bias,
@@ -157,8 +168,14 @@ __global__ __launch_bounds__(256) void conv_fwd_tiled_kernel(const uint16_t* __r
       const int g = tid + 256 * i;
       const int col = n0 + (g >> 3);
       rb[i] = make_uint4(0, 0, 0, 0);
-      if (g < NBG && kin && col < co)
-        rb[i] = *reinterpret_cast<const uint4*>(w + (long long)col * K + k0 + koff);
+      if (g < NBG && kin && col < co) {
+        const int o = (k0 + koff) >> 3;
+        const uint16_t* src =
+            PK ? w + ((long long)(col >> 4) * k_steps(ci) + (o >> 2)) * 512 +
+                     ((o & 3) * 16 + (col & 15)) * 8
+               : w + (long long)col * K + k0 + koff;
+        rb[i] = *reinterpret_cast<const uint4*>(src);
+      }
     }
   };
   f32x4 acc[2][NT];
@@ -247,8 +264,8 @@ __global__ __launch_bounds__(256) void conv_fwd_tiled_kernel(const uint16_t* __r
 // read at one octet cover all banks.
 //
 // 96 -> 32 channels at 64^3 x 4 (174 GFLOP), BF16 output: 323 -> 215 us (808
-// TFLOP/s) against one LDS read per tap and row; 192 -> 64 at 32^3 x 4: 172 ->
-// 101 us; 96 -> 32 at one 64^3 box: 105 -> 60 us.
+// TFLOP/s) against one LDS read per tap and row, 190 us (916) from packed
+// weights; 192 -> 64 at 32^3 x 4: 172 -> 101, packed 70 us (1250 TFLOP/s).
 constexpr int kTZ = 4, kTY = 8, kTX = 8;
 constexpr int kHZ = kTZ + 2, kHY = kTY + 2, kHX = kTX + 2;
 constexpr int kCC = 32;                 // channels per chunk
@@ -267,7 +284,7 @@ __device__ __forceinline__ int xcd_item(int b, int n) {
   return n % 8 ? b : (b % 8) * (n / 8) + b / 8;
 }
 
-template <int TX, int MT, int NT, int WC, bool ACT>
+template <int TX, int MT, int NT, int WC, bool PK, bool ACT>
 __global__ __launch_bounds__(256, 2) void conv_fwd_spatial_kernel(const uint16_t* __restrict__ x,
                                                                   const uint16_t* __restrict__ w,
                                                                   const float* __restrict__ bias,
@@ -327,12 +344,13 @@ __global__ __launch_bounds__(256, 2) void conv_fwd_spatial_kernel(const uint16_t
                     16 * (oct ^ (((lx + dx) >> 1) & 3) ^ (((ly + par) & 1) << 1));
 
   // weight fragments: row co = n0 + 16 b + col, channels c0 + 8 oct
-  // (rows past co repeat row 0; their results are not stored)
+  // (rows past co repeat others; their results are not stored)
   const uint16_t* wrow[NT];
 #pragma unroll
   for (int b = 0; b < NT; ++b) {
-    const int c = n0 + 16 * b + col;
-    wrow[b] = w + (long long)(c < co ? c : 0) * 27 * ci + 8 * oct;
+    const int c = n0 + 16 * b + col, ct = (n0 >> 4) + b;
+    wrow[b] = PK ? w + (long long)(16 * ct < co ? ct : 0) * k_steps(ci) * 512 + lane * 8
+                 : w + (long long)(c < co ? c : 0) * 27 * ci + 8 * oct;
   }
   uint4 wf[9][NT];
   auto load_weights = [&](int dy, int off) {  // taps (dz, dy, 0..2) at off = 9 dz ci + c0
@@ -341,7 +359,7 @@ __global__ __launch_bounds__(256, 2) void conv_fwd_spatial_kernel(const uint16_t
 #pragma unroll
       for (int b = 0; b < NT; ++b)
         wf[3 * dy + dx][b] =
-            *reinterpret_cast<const uint4*>(wrow[b] + off + (3 * dy + dx) * ci);
+            *reinterpret_cast<const uint4*>(wrow[b] + (off + (3 * dy + dx) * ci) * (PK ? 16 : 1));
   };
 
   f32x4 acc[MT][NT];
@@ -437,7 +455,7 @@ __global__ __launch_bounds__(256, 2) void conv_fwd_spatial_kernel(const uint16_t
 //
 // Against 128-voxel tiles gathered stage by stage (conv_fwd_tiled_kernel), BF16
 // output: 8 -> 32 channels at 64^3 x 4 119 -> 45 us; 128 -> 256 at 8^3 x 4 56
-// -> 31 us; 384 -> 128 at one 16^3 box 147 -> 83 us.
+// -> 31 us, 14 from packed weights; 384 -> 128 at one 16^3 box 147 -> 83, 34 us.
 constexpr int kRX = 8, kRHX = kRX + 2;  // x extent of a tile, of its halo
 
 template <int MT, int WC>
@@ -451,7 +469,7 @@ size_t rows_lds(int ci) {
   return (halo + 1023) / 1024 * 1024 + 16 + (size_t)((27 * (ci / 8) + 3) / 4 * 4) * 4;
 }
 
-template <int MT, int NT, int WC, bool ACT>
+template <int MT, int NT, int WC, bool PK, bool ACT>
 __global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __restrict__ x,
                                                             const uint16_t* __restrict__ w,
                                                             const float* __restrict__ bias,
@@ -513,8 +531,9 @@ __global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __re
   const uint16_t* wrow[NT];
 #pragma unroll
   for (int b = 0; b < NT; ++b) {
-    const int c = n0 + 16 * b + col;
-    wrow[b] = w + (long long)(c < co ? c : 0) * 27 * ci;
+    const int c = n0 + 16 * b + col, ct = (n0 >> 4) + b;
+    wrow[b] = PK ? w + (long long)(16 * ct < co ? ct : 0) * steps * 512 + lane * 8
+                 : w + (long long)(c < co ? c : 0) * 27 * ci;
   }
   uint4 wf[2][U][NT];
   auto load_weights = [&](uint4 (&f)[U][NT], int q0) {
@@ -523,7 +542,9 @@ __global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __re
       const int i = 4 * (q0 + u) + oct;
 #pragma unroll
       for (int b = 0; b < NT; ++b)
-        f[u][b] = *reinterpret_cast<const uint4*>(wrow[b] + 8 * (i < octets ? i : octets - 1));
+        f[u][b] = *reinterpret_cast<const uint4*>(
+            wrow[b] + (PK ? 512 * (q0 + u < steps ? q0 + u : 0)
+                          : 8 * (i < octets ? i : octets - 1)));
     }
   };
   f32x4 acc[MT][NT];
@@ -820,6 +841,36 @@ __global__ void flip_weights_kernel(const uint16_t* __restrict__ w, uint16_t* __
     const int c = (int)(r / 27);
     wt[i] = w[((long long)o * 27 + (26 - t)) * ci + c];
   }
+}
+
+// Packed weights (see k_steps above) of the forward convolution (FLIP false)
+// or of its backward-data convolution, whose weights are flip_weights_kernel's
+// (rows ci, K = 27 co); one thread per 16 bytes.  The convolution packed has
+// ki input and ko output channels.
+template <bool FLIP>
+__global__ __launch_bounds__(256) void pack_weights_kernel(const uint16_t* __restrict__ w,
+                                                           uint4* __restrict__ out, int ki, int ko,
+                                                           int total) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= total) return;
+  const int lane = i & 63, f = i >> 6, steps = k_steps(ki);
+  const int row = (f / steps) * 16 + (lane & 15), o = (f % steps) * 4 + (lane >> 4);
+  const int g8 = ki >> 3;
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (row < ko && o < 27 * g8) {
+    if constexpr (!FLIP) {
+      v = *reinterpret_cast<const uint4*>(w + ((long long)row * 27 * g8 + o) * 8);
+    } else {
+      // value j: w[c][26 - tap][row], c = channel 8 (o % g8) + j of the tap o / g8
+      const int tap = o / g8, c = 8 * (o - tap * g8);
+      uint32_t h[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) h[j] = w[((long long)(c + j) * 27 + (26 - tap)) * ko + row];
+      v = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
+                     h[6] | (h[7] << 16));
+    }
+  }
+  out[i] = v;
 }
 
 // ------------------------------------------------------- backward weights
@@ -1521,43 +1572,44 @@ int vector_stores(const void* y, int co) {
 // operand reads per MFMA with more rows; measured at 64^3 x 4, 96 -> 32
 // channels, 8 / 4 / 2 rows: 215 / 314 / 477 us; 16^3 x 4, 384 -> 128, with
 // 128 / 256 / 512 blocks: 117 / 96 / 154 us).
-template <int TX, int MT, int NT, int WC, bool ACT>
+template <int TX, int MT, int NT, int WC, bool PK, bool ACT>
 void launch_fwd_tile(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                      const Shape& s, int ci, int co, int relu, hipStream_t st) {
   constexpr int voxels = (4 / WC) * 16 * MT;
   const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
-  conv_fwd_spatial_kernel<TX, MT, NT, WC, ACT><<<(unsigned)(s.m / voxels * cgs), 256, 0, st>>>(
+  conv_fwd_spatial_kernel<TX, MT, NT, WC, PK, ACT><<<(unsigned)(s.m / voxels * cgs), 256, 0, st>>>(
       x, w, bias, y, s, ci, co, relu, vector_stores<ACT>(y, co));
 }
 constexpr int kFillBlocks = 200;  // enough blocks for the 256 CUs
-template <int NT, int WC, bool ACT>
+template <int NT, int WC, bool PK, bool ACT>
 void launch_fwd_rows_of(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                         const Shape& s, int ci, int co, int relu, hipStream_t st) {
   const long long cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
   const long long tiles = s.m / ((4 / WC) * 16) * cgs;  // blocks with one tile per wavefront
   if (s.w % 16) {
-    launch_fwd_tile<8, 4, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    launch_fwd_tile<8, 4, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   } else if (tiles >= 8 * kFillBlocks) {
-    launch_fwd_tile<16, 8, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    launch_fwd_tile<16, 8, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   } else if (WC > 1 || tiles >= 4 * kFillBlocks) {
     // (two groups of channels: always so many tiles)
-    launch_fwd_tile<16, 4, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    launch_fwd_tile<16, 4, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   } else {
-    if constexpr (WC == 1) launch_fwd_tile<16, 2, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    if constexpr (WC == 1)
+      launch_fwd_tile<16, 2, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   }
 }
 // Channel groups of 32 per wavefront (16 for few channels); pairs of groups
 // share a block's halo where their count is even (96 channels: 257 us with
 // one group per block against 293 us with two, a quarter of them empty).
-template <bool ACT>
+template <bool PK, bool ACT>
 void launch_fwd_spatial(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                         const Shape& s, int ci, int co, int relu, hipStream_t st) {
   if (co <= 16)
-    launch_fwd_rows_of<1, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    launch_fwd_rows_of<1, 1, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   else if ((co + 31) / 32 % 2)
-    launch_fwd_rows_of<2, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    launch_fwd_rows_of<2, 1, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   else
-    launch_fwd_rows_of<2, 2, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    launch_fwd_rows_of<2, 2, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
 }
 
 constexpr size_t kLdsBytes = 160 * 1024;  // of a CU
@@ -1567,42 +1619,54 @@ long long rows_blocks(const Shape& s, int groups) {
   return (long long)s.n * ((s.d + 4 / WC - 1) / (4 / WC)) * ((s.h + 2 * MT - 1) / (2 * MT)) *
          ((s.w + kRX - 1) / kRX) * groups;
 }
-template <int MT, int NT, int WC, bool ACT>
+template <int MT, int NT, int WC, bool PK, bool ACT>
 void launch_rows(const uint16_t* x, const uint16_t* w, const float* bias, void* y, const Shape& s,
                  int ci, int co, int relu, hipStream_t st) {
   const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
-  conv_fwd_rows_kernel<MT, NT, WC, ACT>
+  conv_fwd_rows_kernel<MT, NT, WC, PK, ACT>
       <<<(unsigned)rows_blocks<MT, WC>(s, cgs), 256, rows_lds<MT, WC>(ci), st>>>(
           x, w, bias, y, s, ci, co, relu, vector_stores<ACT>(y, co));
 }
 // Rows per wavefront: the fewest whose blocks run at once, one per CU (a
 // second block on a CU doubles the time of a latency-bound launch), four for
-// boxes beyond that; false if the halo does not fit in LDS.
-template <int NT, int WC, bool ACT>
+// boxes beyond that.  False where gathered tiles are the better kernel: the
+// halo does not fit in LDS; or more than 32 channels in boxes of more blocks,
+// for unpacked weights, whose scattered rows then bound the launch (20^3 x 3,
+// 64 -> 128: 47 against 42 us), and for packed ones where only two rows fit
+// (20^3 x 4, 384 -> 128: 204 against 194 us; with up to 256 channels packed
+// weights win, 20^3 x 3, 64 -> 128: 30 against 42 us).
+template <int NT, int WC, bool PK, bool ACT>
 bool launch_rows_of(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                     const Shape& s, int ci, int co, int relu, hipStream_t st) {
   const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
   const bool fit1 = rows_lds<1, WC>(ci) <= kLdsBytes, fit2 = rows_lds<2, WC>(ci) <= kLdsBytes,
              fit4 = rows_lds<4, WC>(ci) <= kLdsBytes;
   if (!fit1) return false;
-  if (rows_blocks<1, WC>(s, cgs) <= 256 || !fit2)
-    launch_rows<1, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
-  else if (rows_blocks<2, WC>(s, cgs) <= 256 || !fit4)
-    launch_rows<2, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  const int mt = rows_blocks<1, WC>(s, cgs) <= 256 || !fit2   ? 1
+                 : rows_blocks<2, WC>(s, cgs) <= 256 || !fit4 ? 2
+                                                              : 4;
+  const long long blocks = mt == 1   ? rows_blocks<1, WC>(s, cgs)
+                           : mt == 2 ? rows_blocks<2, WC>(s, cgs)
+                                     : rows_blocks<4, WC>(s, cgs);
+  if (PK ? ci > 256 && blocks > 512 : ci >= 32 && blocks > 256) return false;
+  if (mt == 1)
+    launch_rows<1, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  else if (mt == 2)
+    launch_rows<2, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   else
-    launch_rows<4, NT, WC, ACT>(x, w, bias, y, s, ci, co, relu, st);
+    launch_rows<4, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   return true;
 }
-template <bool ACT>
+template <bool PK, bool ACT>
 bool launch_fwd_halo(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                      const Shape& s, int ci, int co, int relu, hipStream_t st) {
-  if (co <= 16) return launch_rows_of<1, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
-  if (co <= 32) return launch_rows_of<2, 1, ACT>(x, w, bias, y, s, ci, co, relu, st);
-  if (co <= 64) return launch_rows_of<2, 2, ACT>(x, w, bias, y, s, ci, co, relu, st);
-  return launch_rows_of<2, 4, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  if (co <= 16) return launch_rows_of<1, 1, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  if (co <= 32) return launch_rows_of<2, 1, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  if (co <= 64) return launch_rows_of<2, 2, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  return launch_rows_of<2, 4, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
 }
 
-template <bool ACT>
+template <bool PK, bool ACT>
 lbm_status conv_forward(const void* x, const void* w, const float* bias, void* y, int n, int d,
                         int h, int wd, int ci, int co, int relu, void* stream) {
   if (!x || !w || !y || bad_shape(n, d, h, wd) || ci < 8 || ci % 8 || co < 1)
@@ -1618,22 +1682,18 @@ lbm_status conv_forward(const void* x, const void* w, const float* bias, void* y
   if (ci % kCC == 0 && d % kTZ == 0 && h % kTY == 0 && wd % kTX == 0 &&
       tiles * ((co + bn - 1) / bn) >= 128 && aligned16(x) && aligned16(w) &&
       s.m * (ci / 8) < (1LL << 31)) {
-    launch_fwd_spatial<ACT>(xx, ww, bias, y, s, ci, co, relu, st);
+    launch_fwd_spatial<PK, ACT>(xx, ww, bias, y, s, ci, co, relu, st);
     return check_launch();
   }
   dim3 grid((unsigned)((s.m + 127) / 128), (unsigned)((co + bn - 1) / bn));
-  // few tiles or few channels: the halo kernel (20^3 x 3, 64 -> 128 channels,
-  // 376 tiles: 47 us there against 42 us in gathered tiles; 12 x 16 x 24, 192
-  // -> 128, 72 tiles: 47 against 78 us)
-  if ((ci < 32 || (long long)grid.x * grid.y < 256) && aligned16(x) &&
-      launch_fwd_halo<ACT>(xx, ww, bias, y, s, ci, co, relu, st))
+  if (aligned16(x) && launch_fwd_halo<PK, ACT>(xx, ww, bias, y, s, ci, co, relu, st))
     return check_launch();
   if (bn == 16)
-    conv_fwd_tiled_kernel<16, ACT><<<grid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
+    conv_fwd_tiled_kernel<16, PK, ACT><<<grid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
   else if (bn == 32)
-    conv_fwd_tiled_kernel<32, ACT><<<grid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
+    conv_fwd_tiled_kernel<32, PK, ACT><<<grid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
   else
-    conv_fwd_tiled_kernel<64, ACT><<<grid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
+    conv_fwd_tiled_kernel<64, PK, ACT><<<grid, 256, 0, st>>>(xx, ww, bias, y, s, ci, co, relu);
   return check_launch();
 }
 
@@ -1641,14 +1701,14 @@ lbm_status conv_forward(const void* x, const void* w, const float* bias, void* y
 
 NN_API lbm_status nn_conv3d_forward(const void* x, const void* w, const float* bias, float* y,
                                     int n, int d, int h, int wd, int ci, int co, void* stream) {
-  return conv_forward<false>(x, w, bias, y, n, d, h, wd, ci, co, 0, stream);
+  return conv_forward<false, false>(x, w, bias, y, n, d, h, wd, ci, co, 0, stream);
 }
 
 NN_API lbm_status nn_conv3d_forward_act(const void* x, const void* w, const float* bias, void* a,
                                         int n, int d, int h, int wd, int ci, int co, int relu,
                                         void* stream) {
   if (relu != 0 && relu != 1) return LBM_ERR_INVALID_ARG;
-  return conv_forward<true>(x, w, bias, a, n, d, h, wd, ci, co, relu, stream);
+  return conv_forward<false, true>(x, w, bias, a, n, d, h, wd, ci, co, relu, stream);
 }
 
 NN_API lbm_status nn_conv3d_flip_weights(const void* w, void* wt, int ci, int co, void* stream) {
@@ -1656,6 +1716,40 @@ NN_API lbm_status nn_conv3d_flip_weights(const void* w, void* wt, int ci, int co
   flip_weights_kernel<<<grid_for(27LL * ci * co), 256, 0, (hipStream_t)stream>>>(
       (const uint16_t*)w, (uint16_t*)wt, ci, co);
   return check_launch();
+}
+
+NN_API lbm_status nn_conv3d_packed_bytes(int ci, int co, size_t* bytes) {
+  if (!bytes || ci < 8 || ci % 8 || co < 1) return LBM_ERR_INVALID_ARG;
+  *bytes = (size_t)((co + 15) / 16) * k_steps(ci) * 1024;
+  return LBM_OK;
+}
+
+NN_API lbm_status nn_conv3d_pack_weights(const void* w, void* packed, int ci, int co, int flip,
+                                         void* stream) {
+  if (!w || !packed || ci < 1 || co < 1 || (flip != 0 && flip != 1)) return LBM_ERR_INVALID_ARG;
+  // channels of the convolution that reads them
+  const int ki = flip ? co : ci, ko = flip ? ci : co;
+  size_t bytes = 0;
+  if (nn_conv3d_packed_bytes(ki, ko, &bytes) != LBM_OK || bytes / 16 >= (1ULL << 31) - 256)
+    return LBM_ERR_INVALID_ARG;
+  const int total = (int)(bytes / 16);
+  const unsigned blocks = (unsigned)((total + 255) / 256);
+  if (flip)
+    pack_weights_kernel<true><<<blocks, 256, 0, (hipStream_t)stream>>>(
+        (const uint16_t*)w, (uint4*)packed, ki, ko, total);
+  else
+    pack_weights_kernel<false><<<blocks, 256, 0, (hipStream_t)stream>>>(
+        (const uint16_t*)w, (uint4*)packed, ki, ko, total);
+  return check_launch();
+}
+
+NN_API lbm_status nn_conv3d_forward_packed(const void* x, const void* packed, const float* bias,
+                                           void* out, int out_kind, int n, int d, int h, int wd,
+                                           int ci, int co, void* stream) {
+  if (!aligned16(packed) || out_kind < 0 || out_kind > 2) return LBM_ERR_INVALID_ARG;
+  if (out_kind == 0)
+    return conv_forward<true, false>(x, packed, bias, out, n, d, h, wd, ci, co, 0, stream);
+  return conv_forward<true, true>(x, packed, bias, out, n, d, h, wd, ci, co, out_kind - 1, stream);
 }
 
 NN_API lbm_status nn_conv3d_backward_data(const void* dy, const void* wt, float* dx, int n, int d,

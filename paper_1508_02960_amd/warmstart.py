@@ -41,6 +41,9 @@ def _nn():
         "nn_conv3d_forward": [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp],
         "nn_conv3d_forward_act": [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp],
         "nn_conv3d_flip_weights": [vp, vp, i32, i32, vp],
+        "nn_conv3d_packed_bytes": [i32, i32, C.POINTER(sz)],
+        "nn_conv3d_pack_weights": [vp, vp, i32, i32, i32, vp],
+        "nn_conv3d_forward_packed": [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp],
         "nn_conv3d_backward_data": [vp, vp, vp, i32, i32, i32, i32, i32, i32, vp],
         "nn_conv3d_backward_weight_workspace": [i32, i32, i32, i32, i32, i32, C.POINTER(sz),
                                                 C.POINTER(i32)],
@@ -81,7 +84,12 @@ NN_EXPORTS = (
     "nn_pool2_forward",
     "nn_pool2_backward", "nn_upsample2_forward", "nn_upsample2_backward", "nn_concat_channels",
     "nn_split_channels", "nn_add", "nn_masked_mse", "nn_adam", "nn_prolongate2",
-    "nn_warm_start_fields", "nn_coarse_pack_input",
+    "nn_warm_start_fields",
+)
+
+NN_PREPARED_EXPORTS = (  # include/lbm_nn_prepared.h
+    "nn_conv3d_packed_bytes", "nn_conv3d_forward_packed", "nn_conv3d_pack_weights",
+    "nn_coarse_pack_input",
 )
 
 
@@ -115,7 +123,8 @@ class _Ctx:
 
 class Conv:
     """3x3x3 periodic convolution ci -> co with bias; FP32 master weights,
-    BF16 copies for the kernels, Adam moments."""
+    BF16 copies (as they are, and packed for the forward and the
+    backward-data convolution), Adam moments."""
 
     def __init__(self, ctx: _Ctx, ci: int, co: int, rng: np.random.Generator):
         self.ctx, self.ci, self.co = ctx, ci, co
@@ -125,7 +134,7 @@ class Conv:
         self.w = t.from_numpy(w).to(ctx.dev)
         self.b = ctx.zeros(co)
         self.wb = ctx.bf(co, 27, ci)
-        self.wt = ctx.bf(ci, 27, co)
+        self.wp, self.wtp = self._packed(ci, co), self._packed(co, ci)
         self.gw = ctx.zeros(co, 27, ci)
         self.gb = ctx.zeros(co)
         self.mw, self.vw = ctx.zeros(co, 27, ci), ctx.zeros(co, 27, ci)
@@ -135,26 +144,47 @@ class Conv:
     def n_params(self) -> int:
         return self.co * 27 * self.ci + self.co
 
+    def _packed(self, ci: int, co: int):
+        """Buffer of the packed weights of a convolution; None where no kernel
+        reads them (channel counts that are no multiple of 8)."""
+        if ci % 8:
+            return None
+        nb = C.c_size_t()
+        _chk(_nn().nn_conv3d_packed_bytes(ci, co, C.byref(nb)), "packed bytes")
+        return self.ctx.bf(int(nb.value) // 2)
+
+    def _pack(self):
+        for buf, flip in ((self.wp, 0), (self.wtp, 1)):
+            if buf is not None:
+                _chk(_nn().nn_conv3d_pack_weights(_p(self.wb), _p(buf), self.ci, self.co, flip,
+                                                  self.ctx.stream), "pack")
+
+    @property
+    def wt(self):
+        """The flipped weights wt[ci][tap][co] of the backward-data convolution."""
+        wt = self.ctx.bf(self.ci, 27, self.co)
+        _chk(_nn().nn_conv3d_flip_weights(_p(self.wb), _p(wt), self.ci, self.co,
+                                          self.ctx.stream), "flip")
+        return wt
+
     def refresh(self):
-        lib = _nn()
-        _chk(lib.nn_cast_bf16(_p(self.w), _p(self.wb), self.w.numel(), self.ctx.stream), "cast")
-        _chk(lib.nn_conv3d_flip_weights(_p(self.wb), _p(self.wt), self.ci, self.co,
-                                        self.ctx.stream), "flip")
+        _chk(_nn().nn_cast_bf16(_p(self.w), _p(self.wb), self.w.numel(), self.ctx.stream), "cast")
+        self._pack()
 
     def forward(self, x_bf, shape):
         n, d, h, w = shape
         y = self.ctx.f32(n, d, h, w, self.co)
-        _chk(_nn().nn_conv3d_forward(_p(x_bf), _p(self.wb), _p(self.b), _p(y), n, d, h, w,
-                                     self.ci, self.co, self.ctx.stream), "conv forward")
+        _chk(_nn().nn_conv3d_forward_packed(_p(x_bf), _p(self.wp), _p(self.b), _p(y), 0, n, d, h, w,
+                                            self.ci, self.co, self.ctx.stream), "conv forward")
         return y
 
     def forward_act(self, x_bf, shape, relu=True):
         """bf16(relu(conv(x))): the convolution and the activation in one kernel."""
         n, d, h, w = shape
         a = self.ctx.bf(n, d, h, w, self.co)
-        _chk(_nn().nn_conv3d_forward_act(_p(x_bf), _p(self.wb), _p(self.b), _p(a), n, d, h, w,
-                                         self.ci, self.co, 1 if relu else 0, self.ctx.stream),
-             "conv forward + activation")
+        _chk(_nn().nn_conv3d_forward_packed(_p(x_bf), _p(self.wp), _p(self.b), _p(a),
+                                            2 if relu else 1, n, d, h, w, self.ci, self.co,
+                                            self.ctx.stream), "conv forward + activation")
         return a
 
     def backward(self, x_bf, dy32, shape, need_dx=True, act=None):
@@ -185,8 +215,8 @@ class Conv:
         if not need_dx:
             return None
         dx = self.ctx.f32(n, d, h, w, self.ci)
-        _chk(lib.nn_conv3d_backward_data(_p(dy), _p(self.wt), _p(dx), n, d, h, w, self.ci,
-                                         self.co, self.ctx.stream), "conv backward data")
+        _chk(lib.nn_conv3d_forward_packed(_p(dy), _p(self.wtp), None, _p(dx), 0, n, d, h, w, self.co,
+                                          self.ci, self.ctx.stream), "conv backward data")
         return dx
 
     def adam(self, lr, step, b1=0.9, b2=0.999, eps=1e-8):
@@ -195,8 +225,7 @@ class Conv:
                          self.w.numel(), lr, b1, b2, eps, step, self.ctx.stream), "adam")
         _chk(lib.nn_adam(_p(self.b), _p(self.gb), _p(self.mb), _p(self.vb), None, self.co, lr,
                          b1, b2, eps, step, self.ctx.stream), "adam")
-        _chk(lib.nn_conv3d_flip_weights(_p(self.wb), _p(self.wt), self.ci, self.co,
-                                        self.ctx.stream), "flip")
+        self._pack()
 
 
 class UNet:

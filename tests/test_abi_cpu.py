@@ -38,6 +38,22 @@ def test_library_exports_every_network_function():
     assert set(names) == set(warmstart.NN_EXPORTS)
 
 
+def test_library_exports_every_prepared_function():
+    from paper_1508_02960_amd import warmstart
+
+    lib = warmstart._nn()
+    names = _header_functions("lbm_nn_prepared.h", "nn_")
+    assert set(names) == set(warmstart.NN_PREPARED_EXPORTS)
+    for name in names:
+        assert hasattr(lib, name), name
+    # one row tile of 16, K = 27 octets in 7 steps of four, 1 KB each
+    nb = C.c_size_t()
+    assert lib.nn_conv3d_packed_bytes(8, 5, C.byref(nb)) == 0 and nb.value == 7 * 1024
+    assert lib.nn_conv3d_packed_bytes(12, 8, C.byref(nb)) == 1
+    assert lib.nn_conv3d_forward_packed(None, None, None, None, 0, 1, 4, 4, 4, 8, 8, None) == 1
+    assert lib.nn_coarse_pack_input(None, 1, 8, C.c_void_p(16), None) == 1
+
+
 def test_network_entry_points_validate_without_a_gpu():
     from paper_1508_02960_amd import warmstart
 

@@ -139,6 +139,55 @@ def test_conv_forward_tiles_match_reference(ctx, shape, ci, co):
     assert ctx.torch.equal(a.view(ctx.torch.int16), a_ref.view(ctx.torch.int16))
 
 
+@pytest.mark.parametrize("shape,ci,co", FORWARD_TILES)
+def test_packed_weights_give_the_same_bits(ctx, shape, ci, co):
+    """nn_conv3d_forward_packed against the unpacked calls, and the packed
+    backward-data weights against the flipped ones, bit for bit (the same
+    products in the same order)."""
+    import ctypes as C
+
+    t, lib = ctx.torch, W._nn()
+    n, d, h, wd = shape
+    g = t.Generator(device=ctx.dev).manual_seed(ci + co)
+
+    def bf(*s):
+        return t.randn(s, generator=g, device=ctx.dev).to(t.bfloat16)
+
+    def packed(ki, ko, flip):
+        nb = C.c_size_t()
+        assert lib.nn_conv3d_packed_bytes(ki, ko, C.byref(nb)) == 0
+        buf = ctx.bf(nb.value // 2)
+        assert lib.nn_conv3d_pack_weights(W._p(wb), W._p(buf), ci, co, flip, ctx.stream) == 0
+        return buf
+
+    x, wb, b = bf(n, d, h, wd, ci), bf(co, 27, ci), t.randn(co, generator=g, device=ctx.dev)
+    wp = packed(ci, co, 0)
+    for kind, y in ((0, ctx.f32(n, d, h, wd, co)), (1, ctx.bf(n, d, h, wd, co)),
+                    (2, ctx.bf(n, d, h, wd, co))):
+        ref = t.empty_like(y)
+        if kind == 0:
+            assert lib.nn_conv3d_forward(W._p(x), W._p(wb), W._p(b), W._p(ref), n, d, h, wd, ci,
+                                         co, ctx.stream) == 0
+        else:
+            assert lib.nn_conv3d_forward_act(W._p(x), W._p(wb), W._p(b), W._p(ref), n, d, h, wd,
+                                             ci, co, kind - 1, ctx.stream) == 0
+        assert lib.nn_conv3d_forward_packed(W._p(x), W._p(wp), W._p(b), W._p(y), kind, n, d, h,
+                                            wd, ci, co, ctx.stream) == 0
+        assert t.equal(y, ref), kind
+    assert lib.nn_conv3d_forward_packed(W._p(x), W._p(wp), W._p(b), W._p(y), 3, n, d, h, wd, ci,
+                                        co, ctx.stream) != 0
+    if co % 8 == 0:
+        dy, wt = bf(n, d, h, wd, co), ctx.bf(ci, 27, co)
+        wtp = packed(co, ci, 1)
+        dx, ref = ctx.f32(n, d, h, wd, ci), ctx.f32(n, d, h, wd, ci)
+        assert lib.nn_conv3d_flip_weights(W._p(wb), W._p(wt), ci, co, ctx.stream) == 0
+        assert lib.nn_conv3d_backward_data(W._p(dy), W._p(wt), W._p(ref), n, d, h, wd, ci, co,
+                                           ctx.stream) == 0
+        assert lib.nn_conv3d_forward_packed(W._p(dy), W._p(wtp), None, W._p(dx), 0, n, d, h, wd,
+                                            co, ci, ctx.stream) == 0
+        assert t.equal(dx, ref)
+
+
 # spatially tiled weight gradient: one tile, more tiles than splits (125 over 64,
 # uneven), and a partial channel tile on each side
 @pytest.mark.parametrize("shape,ci,co", [((1, 4, 8, 8), 32, 32), ((1, 20, 40, 40), 64, 64),
