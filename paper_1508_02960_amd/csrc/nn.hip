@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <type_traits>
 
 #include "lbm_nn_prepared.h"
 
@@ -267,7 +268,6 @@ __global__ __launch_bounds__(256) void conv_fwd_tiled_kernel(const uint16_t* __r
 // TFLOP/s) against one LDS read per tap and row, 190 us (916) from packed
 // weights; 192 -> 64 at 32^3 x 4: 172 -> 101, packed 70 us (1250 TFLOP/s).
 constexpr int kTZ = 4, kTY = 8, kTX = 8;
-constexpr int kHZ = kTZ + 2, kHY = kTY + 2, kHX = kTX + 2;
 constexpr int kCC = 32;                 // channels per chunk
 
 // 16 bytes per lane from global memory to LDS: lane l's go to lds + 16 l (lds
@@ -623,45 +623,56 @@ __global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __re
   }
 }
 
-// Spatially tiled weight gradient for boxes that are multiples of the
-// 4 x 8 x 8 tile: dw[co][tap][ci] = sum over the voxels v of dy[v][co]
-// x[v + off(tap)][ci], an MFMA GEMM whose K runs over the 256 voxels of a
-// tile.  Block (g, chunk, co tile) adds up the tiles g, g + G, g + 2G, ...
-// for 16 CT input and 16 RT output channels (channels past ci or co are
-// zero) and writes its sum to part[g]; fold_splits_kernel adds the G partials
-// in order, so the result is deterministic.
+// Tiled weight gradient: dw[co][tap][ci] = sum over the voxels v of dy[v][co]
+// x[v + off(tap)][ci], an MFMA GEMM whose K runs over the voxels of tiles of
+// TZ x TY x TX (TX a multiple of 8), 32 voxels (four x octets, in z, y, x order)
+// per step.  Block (g, chunk, co tile) adds up its steps in order for 16 CT
+// input and 16 RT output channels (what LDS holds for channels past ci or co
+// only reaches sums that are not stored) and writes its sum to part[g]; fold_splits_kernel adds the partials in order.  Two
+// orders of the voxels (BwdwTiles): the tiles g, g + G, g + 2G, ... of
+// 4 x 8 x 8, for boxes of many of them; or consecutive voxels of the box, in
+// tiles of whole rows.
 //
 // Both operands need 8 consecutive voxels of one channel per lane, while
 // tensors (and the LDS tiles) are channels-last: gfx950's transposing LDS read
 // (ds_read_b64_tr_b16: 16 lanes read 4 voxels x 16 channels and each gets the
 // 4 voxels of one channel) does that without a transposed copy.  The 10
-// voxels of a halo row serve the three x shifts: shift 0 and 2 are register
-// pairs of the same reads, shift 1 takes four 16-bit funnel shifts, so a
-// wavefront reads 1.5 instead of 3 operands per (dz, dy).
+// voxels of an octet's halo row serve the three x shifts: shift 0 and 2 are
+// register pairs of the same reads, shift 1 takes four 16-bit funnel shifts, so
+// a wavefront reads 1.5 instead of 3 operands per (dz, dy).
 //
-// The eight wavefronts are CT input-channel tiles times 8 / CT parts of the
-// tile's voxels; each holds all 27 taps of its channels (27 RT accumulators),
-// so per 32 voxels it reads RT + 13.5 operands for 27 RT MFMAs.  The parts are
-// added in LDS at the end.  The next tile's halo (one 40-lane load per halo
-// row) and gradient go straight from global memory to the other LDS buffer
-// while the current tile is computed; one block of 2 wavefronts per SIMD
-// fills a CU.
+// The four wavefronts share the outputs, not the voxels, so that every sum
+// keeps its order: CT input-channel tiles times 4 / CT equal shares of the
+// units (dz, dy, co tile) of three taps each (CT = RT = 2: 9 units, 27
+// accumulators; 9.5 operand reads per 27 MFMAs).  Halo and gradient go straight
+// from global memory to LDS; where LDS allows, into the other of two buffers
+// while the current tile is computed, else a second block on the CU computes
+// meanwhile.
 //
 // LDS: voxel v of a tile at 32 CT (32 RT) bytes; with 64 bytes the two 32-byte
 // halves are swapped where v & 2, so that the 4 voxels of a transposing read
-// cover all banks.
+// cover all banks.  The halo's rows hold TX + 2 voxels and two of padding, or,
+// where tiles are whole rows of the box, the TX voxels alone: a read's four
+// voxels are addressed lane by lane, so the periodic wrap in x is one of
+// addresses (xtab), and a load fills whole kilobytes.
 //
-// With the transposed copies written to LDS two bytes at a time and the tiles
-// of the small levels on the general kernel (fold included): 96 -> 32 channels
-// at 64^3 x 4 642 -> 246 us (707 TFLOP/s), 192 -> 64 at 32^3 x 4 314 -> 120 us,
-// 384 -> 128 at 16^3 x 4 318 -> 71 us, 128 -> 256 at 8^3 x 4 49 -> 29 us.
-constexpr int kWRow = 16;                      // voxels from halo row to halo row in LDS
-constexpr int kWRows = kHZ * kHY;              // halo rows
-constexpr int kTileVox = kTZ * kTY * kTX;      // 256
-typedef short s16x4 __attribute__((ext_vector_type(4)));
+// Against transposed copies written to LDS two bytes at a time, and the general
+// kernel for boxes of few tiles (bit-identical, fold included): 96 -> 32 channels
+// at 64^3 x 4 642 -> 241 us (721 TFLOP/s), 192 -> 64 at 32^3 x 4 314 -> 125 us, 384
+// -> 128 at 16^3 x 4 318 -> 106 us, 128 -> 256 at 8^3 x 4 49 -> 27 us.
+struct BwdwTiles {
+  int tz, ty, tx;      // tile
+  int ntx, nty, ntz;   // tiles per row, per plane of rows, per box
+  int steps;           // steps of 32 voxels per tile
+  int tiles;           // tiles in all
+  int stride;          // > 0: tiles g, g + stride, ...; 0: consecutive voxels,
+  int split_steps;     // ... this many steps per split
+  int buffers;         // LDS buffers (1 or 2)
+  uint32_t by_tx, by_hy;  // ceil(2^32 / tx), ceil(2^32 / (ty + 2)): divisions by __umulhi
+};
+constexpr int kBwdwMaxOctets = 32;  // octets of a tile (256 voxels)
 
-// Zeros for the channels past the last in partial channel tiles.
-__device__ const uint4 zero_octet = {0, 0, 0, 0};
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 // 16 bytes per active lane from global memory to LDS byte address lds + 16
 // lane, not tracked by the compiler, which would otherwise wait for it before
@@ -684,148 +695,220 @@ __device__ __forceinline__ uint2 read_transposed(const unsigned char* p) {
       uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
 }
 
+// Bytes of one LDS buffer (halo, gradient), and of a block's LDS.
+__host__ __device__ inline int bwdw_pitch(const BwdwTiles& g) {  // voxels
+  return g.stride ? g.tx + 4 : g.tx;
+}
+__host__ __device__ inline int bwdw_halo_bytes(const BwdwTiles& g, int xv) {
+  return ((g.tz + 2) * (g.ty + 2) * bwdw_pitch(g) * xv + 1023) / 1024 * 1024;
+}
+__host__ __device__ inline int bwdw_buffer_bytes(const BwdwTiles& g, int xv, int dv) {
+  return bwdw_halo_bytes(g, xv) + g.tz * g.ty * g.tx * dv;
+}
+
+// One step for the units [U0, U1) of a wavefront: unit u = (pair u / RT, co
+// tile u % RT).
+template <int RT, int U0, int U1, int NA>
+__device__ __forceinline__ void bwdw_step(const unsigned char* xs, const int (&xoff)[3],
+                                          const unsigned char* dr, int dv, int half, int row,
+                                          int plane, f32x4 (&acc)[NA]) {
+  bf16x8 a[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const unsigned char* q = dr + (RT == 2 ? (r ^ half) * 32 : 0);
+    const uint2 lo = read_transposed(q), hi = read_transposed(q + 4 * dv);
+    a[r] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+  }
+#pragma unroll
+  for (int p = U0 / RT; p * RT < U1; ++p) {
+    const unsigned char* q = xs + (p / 3) * plane + (p % 3) * row;
+    const uint2 v0 = read_transposed(q + xoff[0]), v4 = read_transposed(q + xoff[1]),
+                v8 = read_transposed(q + xoff[2]);
+    const uint4 b[3] = {
+        make_uint4(v0.x, v0.y, v4.x, v4.y),
+        make_uint4(__builtin_amdgcn_alignbit(v0.y, v0.x, 16),
+                   __builtin_amdgcn_alignbit(v4.x, v0.y, 16),
+                   __builtin_amdgcn_alignbit(v4.y, v4.x, 16),
+                   __builtin_amdgcn_alignbit(v8.x, v4.y, 16)),
+        make_uint4(v0.y, v4.x, v4.y, v8.x)};
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int u = p * RT + r;
+      if (u < U0 || u >= U1) continue;
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx)
+        acc[3 * (u - U0) + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            a[r], __builtin_bit_cast(bf16x8, b[dx]), acc[3 * (u - U0) + dx], 0, 0, 0);
+    }
+  }
+}
+
+// f(integral constant I) for the wavefront-uniform index I of N: the share's
+// whole loop is compiled per share, since a branch inside the loop made the
+// compiler copy every accumulator on each step.
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void for_share(int share, F&& f) {
+  if constexpr (I == N - 1) {
+    f(std::integral_constant<int, I>{});
+  } else {
+    if (share == I)
+      f(std::integral_constant<int, I>{});
+    else
+      for_share<N, I + 1>(share, f);
+  }
+}
+
 template <int RT, int CT>
-__global__ __launch_bounds__(512, 2) void conv_bwdw_spatial_kernel(const uint16_t* __restrict__ x,
-                                                                   const uint16_t* __restrict__ dy,
-                                                                   float* __restrict__ part,
-                                                                   Shape s, int ci, int co,
-                                                                   int tiles) {
+__global__ __launch_bounds__(256, 2) void conv_bwdw_tile_kernel(const uint16_t* __restrict__ x,
+                                                                const uint16_t* __restrict__ dy,
+                                                                float* __restrict__ part, Shape s,
+                                                                int ci, int co, BwdwTiles g) {
   constexpr int XV = 32 * CT, DV = 32 * RT;              // bytes of a voxel in LDS
-  constexpr int XB = kWRows * kWRow * XV, DB = kTileVox * DV;
-  constexpr int KP = 8 / CT;                             // parts of the voxels
-  constexpr int KS = 8 / KP;                             // steps of 32 voxels per part
-  constexpr int RB = 9 * RT * 8 * 1024;                  // fold: 9 taps of 8 wavefronts
-  constexpr int LB = 2 * (XB + DB) > RB ? 2 * (XB + DB) : RB;
-  __shared__ __attribute__((aligned(16))) unsigned char Ls[LB];
+  constexpr int NV = 4, NW = NV / CT, U = 9 * RT;        // wavefronts, shares, units
+  extern __shared__ __attribute__((aligned(16))) unsigned char Ls[];
+  // LDS byte, for either channel tile, of the 12 voxels from x - 1 on of an
+  // octet's row
+  __shared__ int xtab[2][kBwdwMaxOctets * 12];
   const int tid = threadIdx.x, lane = tid & 63, oct = lane >> 4, i16 = lane & 15;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ct = wv % CT, kp = wv / CT;
-  const int G = gridDim.x, c0 = blockIdx.y * 16 * CT, o0 = blockIdx.z * 16 * RT;
-  const int tx_n = s.w / kTX, ty_n = s.h / kTY, tz_n = s.d / kTZ;
+  const int ct = wv % CT, share = wv / CT;
+  const int c0 = blockIdx.y * 16 * CT, o0 = blockIdx.z * 16 * RT;
+  const int HY = g.ty + 2, P = bwdw_pitch(g);
+  const int row = P * XV, plane = HY * row;              // LDS bytes
+  const int xbytes = bwdw_halo_bytes(g, XV), bytes = bwdw_buffer_bytes(g, XV, DV);
+  const int octets_x = g.tx >> 3;
+  for (int i = tid; i < 4 * g.steps * 12; i += 256) {
+    const int o = i / 12, r = o / octets_x, z = r / g.ty;
+    int v = (o - r * octets_x) * 8 + (i - o * 12);
+    if (!g.stride) v = v == 0 ? P - 1 : (v > P ? v - P - 1 : v - 1);
+    v += (z * HY + (r - z * g.ty)) * P;
+    for (int k = 0; k < CT; ++k)
+      xtab[k][i] = v * XV + (CT == 2 ? (k ^ ((v >> 1) & 1)) * 32 : 0);
+  }
 
-  // this lane's voxel and channel octet of a staging load: a halo row (lanes
-  // 0..XL-1) and a run of consecutive gradient voxels
+  // this lane's voxel and channel octet of a staging load
   constexpr int XG = 2 * CT, DG = 2 * RT;                // octets of a voxel
-  constexpr int XL = kHX * XG;
+  constexpr int XL = 64 / XG, DL = 64 / DG;              // voxels per load
   const int xv = lane / XG, dv = lane / DG;
-  auto octet_of = [](int slot, int v, int g) {           // swapped halves (above)
-    return g == 4 ? (slot ^ (v & 2)) : slot;
+  auto octet_of = [](int slot, int v, int n) {           // swapped halves (above)
+    return n == 4 ? (slot ^ (v & 2)) : slot;
   };
   const int xo = c0 + 8 * octet_of(lane % XG, xv, XG), od = o0 + 8 * octet_of(lane % DG, dv, DG);
   const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_address(Ls));
-
+  const int dvox = g.tz * g.ty * g.tx;
+  // (the loops below step through rows without divisions, whose instructions
+  // would cost more than the loads)
   auto stage = [&](int t, int buf) {
-    const int x0 = (t % tx_n) * kTX;
-    t /= tx_n;
-    const int y0 = (t % ty_n) * kTY;
-    t /= ty_n;
-    const int z0 = (t % tz_n) * kTZ;
-    const int bn_ = t / tz_n;
-    int xx = x0 + xv - 1;
-    xx = xx < 0 ? xx + s.w : (xx >= s.w ? xx - s.w : xx);
-    const uint32_t xl = lds + buf * (XB + DB), dl = xl + XB;
-    for (int r = wv; r < kWRows; r += 8) {               // (wavefront-uniform)
-      const int hz = r / kHY, hy = r - hz * kHY;
-      int zz = z0 + hz - 1, yy = y0 + hy - 1;
-      zz = zz < 0 ? zz + s.d : (zz >= s.d ? zz - s.d : zz);
-      yy = yy < 0 ? yy + s.h : (yy >= s.h ? yy - s.h : yy);
-      const long long row = (((long long)bn_ * s.d + zz) * s.h + yy) * s.w;
-      const void* g = xo < ci ? (const void*)(x + (row + xx) * ci + xo) : (const void*)&zero_octet;
-      if (lane < XL) load_to_lds_async(g, xl + r * (kWRow * XV));
+    const long long m0 = (long long)t * dvox;              // (consecutive voxels)
+    const int x0 = (t % g.ntx) * g.tx;
+    t /= g.ntx;
+    const int y0 = (t % g.nty) * g.ty;
+    t /= g.nty;
+    const int z0 = (t % g.ntz) * g.tz;
+    const int bn_ = t / g.ntz;
+    const uint32_t xl = lds + buf * bytes, dl = xl + xbytes;
+    if (g.stride) {  // one load per row of 10 voxels
+      int xx = x0 + xv - 1;
+      xx = xx < 0 ? xx + s.w : (xx >= s.w ? xx - s.w : xx);
+      const bool in = xv < g.tx + 2 && xo < ci;
+      const uint16_t* xlane_src = x + (long long)xx * ci + xo;
+      int hz = 0, hy = wv;                                 // (wavefront-uniform)
+      uint32_t at = xl + wv * row;
+      for (;; hy += NV, at += NV * row) {
+        while (hy >= HY) {
+          hy -= HY;
+          ++hz;
+        }
+        if (hz >= g.tz + 2) break;
+        int zz = z0 + hz - 1, yy = y0 + hy - 1;
+        zz = zz < 0 ? zz + s.d : (zz >= s.d ? zz - s.d : zz);
+        yy = yy < 0 ? yy + s.h : (yy >= s.h ? yy - s.h : yy);
+        const long long v = (((long long)bn_ * s.d + zz) * s.h + yy) * s.w;
+        if (in) load_to_lds_async(xlane_src + v * ci, at);
+      }
+    } else {         // whole rows of the box, 64 lanes of them per load
+      for (int q = wv; q < xbytes >> 10; q += NV) {
+        const uint32_t f = q * XL + xv, r = __umulhi(f, g.by_tx), hz = __umulhi(r, g.by_hy);
+        int zz = z0 + (int)hz - 1, yy = y0 + (int)(r - hz * HY) - 1;
+        zz = zz < 0 ? zz + s.d : (zz >= s.d ? zz - s.d : zz);
+        yy = yy < 0 ? yy + s.h : (yy >= s.h ? yy - s.h : yy);
+        const long long v =
+            (((long long)bn_ * s.d + zz) * s.h + yy) * s.w + (long long)(f - r * g.tx);
+        if ((int)hz < g.tz + 2 && xo < ci) load_to_lds_async(x + v * ci + xo, xl + q * 1024);
+      }
     }
-    constexpr int VL = 64 / DG;                          // gradient voxels per load
-    for (int q = wv; q < kTileVox / VL; q += 8) {
-      const int v = q * VL + dv;
-      const int tz = v >> 6, ty = (v >> 3) & 7, tx = v & 7;
-      const long long m = (((long long)bn_ * s.d + z0 + tz) * s.h + y0 + ty) * s.w + x0 + tx;
-      const void* g = od < co ? (const void*)(dy + m * co + od) : (const void*)&zero_octet;
-      load_to_lds_async(g, dl + q * 1024);
+    for (int q = wv; q < dvox / DL; q += NV) {
+      const int v = q * DL + dv;
+      const long long m =
+          g.stride ? (((long long)bn_ * s.d + z0 + (v >> 6)) * s.h + y0 + ((v >> 3) & 7)) * s.w +
+                         x0 + (v & 7)
+                   : m0 + v;
+      if (od < co) load_to_lds_async(dy + m * co + od, dl + q * 1024);
     }
   };
 
-  f32x4 acc[27][RT];
-#pragma unroll
-  for (int j = 0; j < 27; ++j)
-#pragma unroll
-    for (int r = 0; r < RT; ++r) acc[j][r] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // LDS bytes of this lane's transposing reads at step 0 of the part: voxel
-  // i16 / 4 of a row, channels 4 (i16 % 4) of the 16-channel half
+  // LDS bytes of this lane's transposing reads: voxel i16 / 4 of an octet,
+  // channels 4 (i16 % 4) of the 16-channel half
   const int half = (i16 >> 3) & 1;
   const int sub = (i16 & 3) * 8;
-  const int xbase = (oct * kWRow + (i16 >> 2)) * XV + (CT == 2 ? (ct ^ half) * 32 : 0) + sub;
-  const int dbase = (oct * 8 + (i16 >> 2)) * DV + sub;
+  const int dlane = (oct * 8 + (i16 >> 2)) * DV + sub;
 
-  int buf = 0;
-  if ((int)blockIdx.x < tiles) stage(blockIdx.x, 0);
-  for (int t = blockIdx.x; t < tiles; t += G, buf ^= 1) {
-    lds_loads_done();
-    __syncthreads();
-    if (t + G < tiles) stage(t + G, buf ^ 1);
-    const unsigned char* xs = Ls + buf * (XB + DB);
-    const unsigned char* ds = xs + XB;
+  // the block's steps: [at, end) in steps of its tiles, `stride` tiles apart
+  const int first = g.stride ? blockIdx.x : 0;
+  const int total = g.tiles * g.steps;
+  int at = g.stride ? 0 : blockIdx.x * g.split_steps;
+  const int end = g.stride ? (first < g.tiles ? (g.tiles - first + g.stride - 1) / g.stride * g.steps : 0)
+                           : (at + g.split_steps < total ? at + g.split_steps : total);
+  const int hop = g.stride ? g.stride : 1;
+  for_share<NW>(share, [&](auto index) {
+    constexpr int U0 = U * decltype(index)::value / NW, U1 = U * (decltype(index)::value + 1) / NW;
+    f32x4 acc[3 * (U1 - U0)];
+#pragma unroll
+    for (int j = 0; j < 3 * (U1 - U0); ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int buf = 0;
+    if (g.buffers == 2 && at < end) stage(first + at / g.steps * hop, 0);
+    while (at < end) {
+      const int t = at / g.steps, s0 = at - t * g.steps;
+      const int s1 = s0 + end - at < g.steps ? s0 + end - at : g.steps;
+      if (g.buffers == 1) {
+        __syncthreads();  // the previous tile's reads are done
+        stage(first + t * hop, 0);
+      }
+      lds_loads_done();
+      __syncthreads();  // (every share of the block passes the same barriers)
+      if (g.buffers == 2 && at + s1 - s0 < end) stage(first + (t + 1) * hop, buf ^ 1);
+      const unsigned char* xs = Ls + buf * bytes + sub;
+      const unsigned char* ds = Ls + buf * bytes + xbytes + dlane;
+      // this lane's voxels of a step: 0-3, 4-7 and 8-11 of its octet's row
+      const int* tab = xtab[CT == 2 ? ct : 0] + oct * 12 + (i16 >> 2);
+      int next[3] = {tab[48 * s0], tab[48 * s0 + 4], tab[48 * s0 + 8]};
 #pragma unroll 1
-    for (int k = 0; k < KS; ++k) {
-      const int ks = kp * KS + k;                        // x rows 4 ks + oct of the tile
-      const unsigned char* xr =
-          xs + xbase + ((ks >> 1) * kHY + 4 * (ks & 1)) * (kWRow * XV);
-      const unsigned char* dr = ds + dbase + ks * (32 * DV);
-      bf16x8 a[RT];
-#pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        const unsigned char* q = dr + (RT == 2 ? (r ^ half) * 32 : 0);
-        const uint2 lo = read_transposed(q), hi = read_transposed(q + 4 * DV);
-        a[r] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+      for (int k = s0; k < s1; ++k) {
+        const int xoff[3] = {next[0], next[1], next[2]};
+        const int n = 48 * (k + 1 < s1 ? k + 1 : k);
+        next[0] = tab[n];
+        next[1] = tab[n + 4];
+        next[2] = tab[n + 8];
+        bwdw_step<RT, U0, U1>(xs, xoff, ds + k * (32 * DV), DV, half, row, plane, acc);
       }
-#pragma unroll
-      for (int p = 0; p < 9; ++p) {
-        const unsigned char* q = xr + ((p / 3) * kHY + p % 3) * (kWRow * XV);
-        const uint2 v0 = read_transposed(q), v4 = read_transposed(q + 4 * XV),
-                    v8 = read_transposed(q + 8 * XV);
-        const uint4 b[3] = {
-            make_uint4(v0.x, v0.y, v4.x, v4.y),
-            make_uint4(__builtin_amdgcn_alignbit(v0.y, v0.x, 16),
-                       __builtin_amdgcn_alignbit(v4.x, v0.y, 16),
-                       __builtin_amdgcn_alignbit(v4.y, v4.x, 16),
-                       __builtin_amdgcn_alignbit(v8.x, v4.y, 16)),
-            make_uint4(v0.y, v4.x, v4.y, v8.x)};
-#pragma unroll
-        for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-            acc[3 * p + dx][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                a[r], __builtin_bit_cast(bf16x8, b[dx]), acc[3 * p + dx][r], 0, 0, 0);
-      }
+      at += s1 - s0;
+      buf ^= g.buffers - 1;
     }
-  }
-  // Add the parts, 9 taps at a time, and store: rows (co) 4 oct + i of row
-  // tile r, column (ci) lane & 15.
-  f32x4* fold = reinterpret_cast<f32x4*>(Ls);            // [wavefront][9 RT][lane]
-  const long long base = (long long)blockIdx.x * co * 27 * ci;
+    // rows (co) 4 oct + e of the co tile, column (ci) lane & 15
+    const long long base = (long long)blockIdx.x * co * 27 * ci;
+    const int c = c0 + 16 * ct + i16;
 #pragma unroll
-  for (int j0 = 0; j0 < 27; j0 += 9) {
-    __syncthreads();
+    for (int u = U0; u < U1; ++u) {
+      const int p = u / RT, o = o0 + 16 * (u % RT) + 4 * oct;
 #pragma unroll
-    for (int j = 0; j < 9; ++j)
+      for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-      for (int r = 0; r < RT; ++r) fold[(wv * 9 * RT + j * RT + r) * 64 + lane] = acc[j0 + j][r];
-    __syncthreads();
-    for (int q = wv; q < 9 * RT * CT; q += 8) {          // (wavefront-uniform)
-      const int c = q % CT, jr = q / CT;
-      f32x4 v = fold[(c * 9 * RT + jr) * 64 + lane];
-      for (int k = 1; k < KP; ++k) {
-        const f32x4 u = fold[((k * CT + c) * 9 * RT + jr) * 64 + lane];
-        for (int e = 0; e < 4; ++e) v[e] += u[e];
-      }
-      const int tap = j0 + jr / RT, r = jr % RT;
-      const int cc = c0 + 16 * c + i16;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int o = o0 + 16 * r + 4 * oct + e;
-        if (o < co && cc < ci) part[base + ((long long)o * 27 + tap) * ci + cc] = v[e];
-      }
+        for (int e = 0; e < 4; ++e)
+          if (o + e < co && c < ci)
+            part[base + ((long long)(o + e) * 27 + 3 * p + dx) * ci + c] =
+                acc[3 * (u - U0) + dx][e];
     }
-  }
+  });
 }
 
 // wt[ci][tap][co] = w[co][26 - tap][ci]: the backward-data convolution is the
@@ -1758,36 +1841,99 @@ NN_API lbm_status nn_conv3d_backward_data(const void* dy, const void* wt, float*
   return nn_conv3d_forward(dy, wt, nullptr, dx, n, d, h, wd, co, ci, stream);
 }
 
-// The spatially tiled weight gradient applies (and with how many splits): one
-// block per CU over the channel tiles.
-static bool bwdw_spatial(int n, int d, int h, int wd, int ci, int co, int* splits) {
-  const long long tiles = (long long)n * d * h * wd / kTileVox;
-  if (d % kTZ || h % kTY || wd % kTX || tiles > (1 << 30)) return false;
+// How the weight gradient of a layer is split: its partial sums, and the
+// tiles of conv_bwdw_tile_kernel (steps 0: the general kernel).  The splits and
+// the order of the voxels within them depend on the shape alone and not on the
+// kernel: 4 x 8 x 8 tiles strided over about 512 blocks for boxes of at least
+// 256 of them, else ranges of consecutive 64-voxel chunks.
+struct BwdwPlan {
+  int splits;
+  long long chunks_per_split;  // consecutive voxels: chunks of 64
+  BwdwTiles tiles;
+};
+constexpr int kTileVox = kTZ * kTY * kTX;
+constexpr int kBwdwLds = 153 * 1024;  // of a CU, less the octet tables
+
+static BwdwPlan bwdw_plan(int n, int d, int h, int w, int ci, int co) {
+  BwdwPlan p{};
+  const long long m = (long long)n * d * h * w;
   const int ct = ci % 32 == 0 ? 32 : 16, rt = co % 32 == 0 ? 32 : 16;
   const long long chan_tiles = (long long)((ci + ct - 1) / ct) * ((co + rt - 1) / rt);
-  *splits = (int)std::max<long long>(1, std::min<long long>(tiles, 256 / chan_tiles));
-  return true;
+  BwdwTiles& g = p.tiles;
+  const long long tiles = m / kTileVox;
+  if (d % kTZ == 0 && h % kTY == 0 && w % kTX == 0 && tiles >= 256 && m < (1LL << 31)) {
+    p.splits = (int)std::max<long long>(
+        1, std::min<long long>({256, tiles / 2, 512 / std::max<long long>(chan_tiles, 1)}));
+    g.tz = kTZ;
+    g.ty = kTY;
+    g.tx = kTX;
+    g.stride = p.splits;
+  } else {
+    const int tm = co <= 32 ? 32 : 64;
+    const long long ktiles = (long long)((co + tm - 1) / tm) * ((27 * ci + 63) / 64);
+    const long long chunks = (m + kWM - 1) / kWM;
+    long long sp = std::max<long long>(
+        1, std::min<long long>(chunks, 2048 / std::max<long long>(ktiles, 1)));
+    sp = std::min<long long>(sp, 256);
+    p.splits = (int)sp;
+    p.chunks_per_split = (chunks + sp - 1) / sp;
+    if (w % 8 || m >= (1LL << 31)) return p;
+    // tiles of whole rows that follow each other in memory (rows of a plane,
+    // or whole planes), a multiple of 64 voxels: the largest of 128 to 256
+    // whose buffer leaves room for a second block on the CU (single rows of 64
+    // are slower than the general kernel, 18 against 15 us: their halo is nine
+    // times the tile)
+    g.tx = w;
+    int vox = 0;
+    for (int ty = 1; ty <= h && (long long)ty * w <= 256; ++ty) {
+      if (h % ty) continue;
+      for (int tz = 1; tz <= (ty == h ? d : 1) && (long long)tz * ty * w <= 256; ++tz) {
+        BwdwTiles q = g;
+        q.tz = tz;
+        q.ty = ty;
+        const int v = tz * ty * w;
+        if (d % tz || v % kWM || v < 128 || v <= vox || bwdw_buffer_bytes(q, ct * 2, rt * 2) > kBwdwLds / 2)
+          continue;
+        g = q;
+        vox = v;
+      }
+    }
+    if (vox == 0) return p;
+    g.split_steps = (int)(2 * p.chunks_per_split);
+  }
+  const int vox = g.tz * g.ty * g.tx;
+  g.ntx = w / g.tx;
+  g.nty = h / g.ty;
+  g.ntz = d / g.tz;
+  g.tiles = (int)(m / vox);
+  // two LDS buffers where two blocks of a CU, or the only one, have room
+  const int bytes = bwdw_buffer_bytes(g, ct * 2, rt * 2);
+  const long long blocks = chan_tiles * p.splits;
+  g.buffers = 2 * bytes <= (blocks > 256 ? kBwdwLds / 2 : kBwdwLds) ? 2 : 1;
+  g.steps = vox / 32;
+  // exact for the halo's few thousand voxels
+  g.by_tx = (uint32_t)(((1ULL << 32) + g.tx - 1) / g.tx);
+  g.by_hy = (uint32_t)(((1ULL << 32) + g.ty + 1) / (g.ty + 2));
+  return p;
 }
 
 NN_API lbm_status nn_conv3d_backward_weight_workspace(int n, int d, int h, int wd, int ci, int co,
                                                       size_t* bytes, int* splits) {
   if (!bytes || bad_shape(n, d, h, wd) || ci < 8 || ci % 8 || co < 8 || co % 8)
     return LBM_ERR_INVALID_ARG;
-  int ssp = 0;
-  if (bwdw_spatial(n, d, h, wd, ci, co, &ssp)) {
-    *bytes = (size_t)ssp * co * 27 * ci * sizeof(float);
-    if (splits) *splits = ssp;
-    return LBM_OK;
-  }
-  const long long m = (long long)n * d * h * wd;
-  const int tm = co <= 32 ? 32 : 64;
-  const long long tiles = (long long)((co + tm - 1) / tm) * ((27 * ci + 63) / 64);
-  const long long chunks = (m + kWM - 1) / kWM;
-  long long sp = std::max<long long>(1, std::min<long long>(chunks, 2048 / std::max<long long>(tiles, 1)));
-  sp = std::min<long long>(sp, 256);
-  *bytes = (size_t)sp * co * 27 * ci * sizeof(float);
-  if (splits) *splits = (int)sp;
+  const BwdwPlan p = bwdw_plan(n, d, h, wd, ci, co);
+  *bytes = (size_t)p.splits * co * 27 * ci * sizeof(float);
+  if (splits) *splits = p.splits;
   return LBM_OK;
+}
+
+template <int RT, int CT>
+static void launch_bwdw_tiles(const uint16_t* x, const uint16_t* dy, float* part, const Shape& s,
+                              int ci, int co, const BwdwPlan& p, hipStream_t st) {
+  const dim3 grid((unsigned)p.splits, (unsigned)((ci + 16 * CT - 1) / (16 * CT)),
+                  (unsigned)((co + 16 * RT - 1) / (16 * RT)));
+  const size_t lds = (size_t)p.tiles.buffers * bwdw_buffer_bytes(p.tiles, 32 * CT, 32 * RT);
+  conv_bwdw_tile_kernel<RT, CT><<<grid, 256, lds, st>>>(x, dy, part, s, ci, co, p.tiles);
 }
 
 NN_API lbm_status nn_conv3d_backward_weight(const void* x, const void* dy, float* dw, void* ws,
@@ -1795,45 +1941,38 @@ NN_API lbm_status nn_conv3d_backward_weight(const void* x, const void* dy, float
                                             int co, void* stream) {
   size_t need = 0;
   int sp = 0;
-  lbm_status st = nn_conv3d_backward_weight_workspace(n, d, h, wd, ci, co, &need, &sp);
-  if (st != LBM_OK) return st;
+  lbm_status status = nn_conv3d_backward_weight_workspace(n, d, h, wd, ci, co, &need, &sp);
+  if (status != LBM_OK) return status;
   if (!x || !dy || !dw || !ws || ws_bytes < need) return LBM_ERR_WORKSPACE;
   const Shape s = shape_of(n, d, h, wd);
   const long long nw = (long long)co * 27 * ci;
-  int ssp = 0;
-  if (bwdw_spatial(n, d, h, wd, ci, co, &ssp)) {
-    const int tiles = (int)(s.m / kTileVox);
+  const BwdwPlan p = bwdw_plan(n, d, h, wd, ci, co);
+  const uint16_t* xx = (const uint16_t*)x;
+  const uint16_t* dd = (const uint16_t*)dy;
+  float* pp = (float*)ws;
+  const hipStream_t st = (hipStream_t)stream;
+  if (p.tiles.steps && aligned16(x) && aligned16(dy)) {
     // channel tiles: 32 where the count is a multiple of 32, else 16 (zero padded)
-    const int ct = ci % 32 == 0 ? 2 : 1, rt = co % 32 == 0 ? 2 : 1;
-    dim3 sgrid((unsigned)ssp, (unsigned)((ci + 16 * ct - 1) / (16 * ct)),
-               (unsigned)((co + 16 * rt - 1) / (16 * rt)));
-    const uint16_t* xx = (const uint16_t*)x;
-    const uint16_t* dd = (const uint16_t*)dy;
-    float* pp = (float*)ws;
-    const hipStream_t st = (hipStream_t)stream;
-    if (rt == 2 && ct == 2)
-      conv_bwdw_spatial_kernel<2, 2><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
-    else if (rt == 2)
-      conv_bwdw_spatial_kernel<2, 1><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
-    else if (ct == 2)
-      conv_bwdw_spatial_kernel<1, 2><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
+    const bool c2 = ci % 32 == 0, r2 = co % 32 == 0;
+    if (r2 && c2)
+      launch_bwdw_tiles<2, 2>(xx, dd, pp, s, ci, co, p, st);
+    else if (r2)
+      launch_bwdw_tiles<2, 1>(xx, dd, pp, s, ci, co, p, st);
+    else if (c2)
+      launch_bwdw_tiles<1, 2>(xx, dd, pp, s, ci, co, p, st);
     else
-      conv_bwdw_spatial_kernel<1, 1><<<sgrid, 512, 0, st>>>(xx, dd, pp, s, ci, co, tiles);
-    fold_splits_kernel<<<grid_for(nw), 256, 0, (hipStream_t)stream>>>((const float*)ws, dw, nw,
-                                                                       ssp);
-    return check_launch();
+      launch_bwdw_tiles<1, 1>(xx, dd, pp, s, ci, co, p, st);
+  } else {
+    const long long chunks = (s.m + kWM - 1) / kWM;
+    const long long per = (chunks + sp - 1) / sp;
+    const int tm = co <= 32 ? 32 : 64;
+    const dim3 grid((unsigned)((co + tm - 1) / tm), (unsigned)((27 * ci + 63) / 64), (unsigned)sp);
+    if (tm == 32)
+      conv_bwdw_kernel<32><<<grid, 256, 0, st>>>(xx, dd, pp, s, ci, co, per);
+    else
+      conv_bwdw_kernel<64><<<grid, 256, 0, st>>>(xx, dd, pp, s, ci, co, per);
   }
-  const long long chunks = (s.m + kWM - 1) / kWM;
-  const long long per = (chunks + sp - 1) / sp;
-  const int tm = co <= 32 ? 32 : 64;
-  dim3 grid((unsigned)((co + tm - 1) / tm), (unsigned)((27 * ci + 63) / 64), (unsigned)sp);
-  if (tm == 32)
-    conv_bwdw_kernel<32><<<grid, 256, 0, (hipStream_t)stream>>>(
-        (const uint16_t*)x, (const uint16_t*)dy, (float*)ws, s, ci, co, per);
-  else
-    conv_bwdw_kernel<64><<<grid, 256, 0, (hipStream_t)stream>>>(
-        (const uint16_t*)x, (const uint16_t*)dy, (float*)ws, s, ci, co, per);
-  fold_splits_kernel<<<grid_for(nw), 256, 0, (hipStream_t)stream>>>((const float*)ws, dw, nw, sp);
+  fold_splits_kernel<<<grid_for(nw), 256, 0, st>>>((const float*)ws, dw, nw, sp);
   return check_launch();
 }
 

@@ -188,10 +188,14 @@ def test_packed_weights_give_the_same_bits(ctx, shape, ci, co):
         assert t.equal(dx, ref)
 
 
-# spatially tiled weight gradient: one tile, more tiles than splits (125 over 64,
-# uneven), and a partial channel tile on each side
-@pytest.mark.parametrize("shape,ci,co", [((1, 4, 8, 8), 32, 32), ((1, 20, 40, 40), 64, 64),
-                                         ((1, 12, 16, 8), 24, 40)])
+# weight gradient tiles: 4 x 8 x 8 with more tiles than splits and an uneven count
+# (300 over 85), whole planes (four of 8 x 8; one of 16 x 16), rows of a plane
+# (8 of 24, 8 of 32, 2 of 64), splits that begin inside a tile (16^3, 43 chunks
+# each), partial channel tiles, and edges that leave the general kernel
+@pytest.mark.parametrize("shape,ci,co", [((1, 4, 8, 8), 32, 32), ((1, 20, 40, 96), 32, 32),
+                                         ((1, 12, 16, 8), 24, 40), ((1, 16, 16, 16), 96, 64),
+                                         ((2, 2, 8, 24), 32, 8), ((1, 6, 16, 32), 8, 32),
+                                         ((1, 3, 6, 64), 16, 24), ((1, 5, 4, 12), 32, 32)])
 def test_conv_weight_gradient_tiles_match_reference(ctx, shape, ci, co):
     """Exact products, FP32 sums over the voxels: 1e-5 of the largest weight's
     gradient, as above."""
