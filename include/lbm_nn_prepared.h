@@ -1,7 +1,8 @@
 /*
  * lbm_nn_prepared.h - C ABI of the network's calls on prepared operands
- * (liblbm.so): convolutions from weights packed once for the kernels, and the
- * network input of a sphere pack formed on the device.  Conventions as in
+ * (liblbm.so): convolutions from weights packed once for the kernels, steps of
+ * the network fused with their neighbours, and the network input of a sphere
+ * pack formed on the device.  Conventions as in
  * lbm_nn.h.
  */
 #ifndef LBM_NN_PREPARED_H
@@ -36,6 +37,31 @@ lbm_status nn_conv3d_pack_weights(const void* w, void* packed, int ci, int co, i
  * double[4 * n], rows cx, cy, cz, r in fine lattice units, read before the call
  * returns; box edge `edge` (even). */
 lbm_status nn_coarse_pack_input(const double* spheres, int n, int edge, void* x, void* stream);
+
+/* y = [u | b] along channels (bf16, n,2d,2h,2w,ca+cb), u the upsampled coarse a
+ * (bf16, n,d,h,w,ca) and b (bf16, n,2d,2h,2w,cb): nn_upsample2_forward and
+ * nn_concat_channels without the upsampled tensor.  ca and cb multiples of 8,
+ * 16-byte aligned pointers, fewer than 2^31 output elements. */
+lbm_status nn_upsample_concat(const void* a, const void* b, void* y, int n, int d, int h, int w_,
+                              int ca, int cb, void* stream);
+
+/* The gradient of a of nn_upsample_concat (float da n,d,h,w,ca) from that of y
+ * (float dcat n,2d,2h,2w,ca+cb): nn_split_channels' first part through
+ * nn_upsample2_backward.  ca and cb multiples of 4, limits as above. */
+lbm_status nn_concat_upsample_backward(const float* dcat, float* da, int n, int d, int h, int w_,
+                                       int ca, int cb, void* stream);
+
+/* nn_relu_backward_bias for a layer whose output (n,d,h,w,c) feeds a pooling and
+ * the skip part of a concatenation: its gradient is nn_pool2_backward(pooled) +
+ * the last c channels of cat, pooled float (n,d/2,h/2,w/2,c) and cat float
+ * (n,d,h,w,ca+c) the gradients of the pooled and the concatenated tensor; it is
+ * never stored.  Bit-identical to nn_pool2_backward, nn_split_channels, nn_add
+ * and nn_relu_backward_bias.  Even d, h, w; c a multiple of 4 up to 1024, ca of
+ * 4; n d h w max(d, h, w) up to 2^32, fewer than 2^31 elements in cat, 16-byte
+ * aligned pointers (a and dz 8). */
+lbm_status nn_pooled_backward_bias(const float* pooled, const float* cat, int ca, const void* a,
+                                   void* dz, float* db, void* ws, size_t ws_bytes, int n, int d,
+                                   int h, int w_, int c, int relu, void* stream);
 
 #ifdef __cplusplus
 }

@@ -1109,13 +1109,25 @@ __global__ __launch_bounds__(256) void conv_bwdw_kernel(const uint16_t* __restri
   }
 }
 
-__global__ void fold_splits_kernel(const float* __restrict__ part, float* __restrict__ dw,
-                                   long long n, int splits) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
+// dw[i] = the splits' partials of i, added in order.  A thread's adds are a
+// serial chain, but their loads are not: kFold of them are in flight (64^3 x 4
+// training step, all sixteen folds: 121 us, 188 with eight at a time).
+constexpr int kFold = 32;
+__global__ __launch_bounds__(256) void fold_splits_kernel(const float* __restrict__ part,
+                                                          float* __restrict__ dw, long long n,
+                                                          int splits) {
+  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += gridDim.x * 256LL) {
     float a = 0.f;
+    int s = 0;
+    for (; s + kFold <= splits; s += kFold) {
+      float v[kFold];
+#pragma unroll
+      for (int j = 0; j < kFold; ++j) v[j] = part[(long long)(s + j) * n + i];
+#pragma unroll
+      for (int j = 0; j < kFold; ++j) a += v[j];
+    }
 #pragma unroll 8
-    for (int s = 0; s < splits; ++s) a += part[(long long)s * n + i];
+    for (; s < splits; ++s) a += part[(long long)s * n + i];
     dw[i] = a;
   }
 }
@@ -1165,78 +1177,118 @@ constexpr int kBiasSplits = 512;
 // Both nn_bias_grad (dz given, FUSED false) and nn_relu_backward_bias (dz =
 // relu'(a) da, stored as BF16, FUSED true) sum in this order, so their db
 // agree bit for bit.  vec selects 16-byte FP32 and 8-byte BF16 accesses when
-// the pointers allow them (the order is the same either way).  Against one
-// channel per thread with 4-byte loads, whose 512 workgroups waited on each
-// load in turn: 158 -> 73 us for the largest layer of a 64^3 x 4 training
-// step (81 -> 35 us on average).
-template <bool FUSED>
+// the pointers allow them (the order is the same either way).
+//
+// Bound by memory.  A thread's sum is a serial chain, so the loads of kBiasAhead
+// voxels are issued before the first of them is added, and where the splits
+// alone are too few blocks the channels are shared by blocks too (blockIdx.y:
+// qs quads each).  All eight layers of a 64^3 x 4 training step: 202 us, 332 with
+// the loads left to the compiler and 8 to 512 blocks; the largest layer's 268 MB
+// in 48 us (73).
+//
+// With POOLED the gradient da is not stored: it is formed from the layers
+// above, da[v] = 0.125 pooled[parent of v] + cat[v][ca + ch], the pooling's
+// gradient plus the skip's slice of the concatenation's gradient (pooled
+// float (n, d/2, h/2, w/2, c), cat float (m, ca + c)).
+constexpr int kBiasAhead = 8;
+struct PooledSource {
+  const float* cat;
+  int ca;
+  int d, h, w;                 // fine box
+  uint32_t by_w, by_h, by_d;   // ceil(2^32 / edge): divisions by __umulhi
+};
+template <bool FUSED, bool POOLED>
 __global__ __launch_bounds__(256) void bias4_part_kernel(const float* __restrict__ da,
                                                          const uint16_t* __restrict__ a,
                                                          uint16_t* __restrict__ dzb,
                                                          float* __restrict__ part, long long m,
-                                                         int c, long long per, int relu, int vec) {
+                                                         int c, int qs, long long per, int relu,
+                                                         int vec, PooledSource src) {
   __shared__ float4 sh[256];
-  const int c4 = c >> 2;
-  const int G = 256 / c4;
-  const int tid = threadIdx.x, g = tid / c4, q = tid - g * c4;
+  const int G = 256 / (c >> 2);
+  const int tid = threadIdx.x, g = tid / qs, ql = tid - g * qs;
+  const int ch = 4 * ((int)blockIdx.y * qs + ql);
   const long long beg = (long long)blockIdx.x * per;
   const long long end = beg + per < m ? beg + per : m;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (g < G) {
-#pragma unroll 4
-    for (long long v = beg + g; v < end; v += G) {
-      const long long i = v * c + 4 * q;
-      float z[4];
-      if (vec) {
-        const float4 t = *reinterpret_cast<const float4*>(da + i);
-        z[0] = t.x;
-        z[1] = t.y;
-        z[2] = t.z;
-        z[3] = t.w;
-      } else {
-        for (int j = 0; j < 4; ++j) z[j] = da[i + j];
-      }
-      if constexpr (FUSED) {
-        if (relu) {
-          uint16_t h[4];
-          if (vec) {
-            const uint2 w = *reinterpret_cast<const uint2*>(a + i);
-            h[0] = (uint16_t)w.x;
-            h[1] = (uint16_t)(w.x >> 16);
-            h[2] = (uint16_t)w.y;
-            h[3] = (uint16_t)(w.y >> 16);
-          } else {
-            for (int j = 0; j < 4; ++j) h[j] = a[i + j];
-          }
-          for (int j = 0; j < 4; ++j)
-            if (!(bf2f(h[j]) > 0.f)) z[j] = 0.f;
-        }
-        uint16_t o[4];
-        for (int j = 0; j < 4; ++j) o[j] = f2bf(z[j]);
-        if (vec)
-          *reinterpret_cast<uint2*>(dzb + i) =
-              make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
-        else
-          for (int j = 0; j < 4; ++j) dzb[i + j] = o[j];
-      }
-      s.x += z[0];
-      s.y += z[1];
-      s.z += z[2];
-      s.w += z[3];
+
+  auto gradient = [&](long long v, float4& z, float4& k) {
+    if constexpr (POOLED) {
+      const uint32_t r = __umulhi((uint32_t)v, src.by_w), x = (uint32_t)v - r * src.w;
+      const uint32_t t = __umulhi(r, src.by_h), y = r - t * src.h;
+      const uint32_t b = __umulhi(t, src.by_d), zz = t - b * src.d;
+      const long long p = ((long long)(b * (src.d / 2) + zz / 2) * (src.h / 2) + y / 2) *
+                              (src.w / 2) + x / 2;
+      z = *reinterpret_cast<const float4*>(da + p * c + ch);
+      k = *reinterpret_cast<const float4*>(src.cat + v * (src.ca + c) + src.ca + ch);
+    } else if (vec) {
+      z = *reinterpret_cast<const float4*>(da + v * c + ch);
+    } else {
+      const float* d = da + v * c + ch;
+      z = make_float4(d[0], d[1], d[2], d[3]);
     }
+  };
+  auto activation = [&](long long v) {
+    const uint16_t* h = a + v * c + ch;
+    if (vec) return *reinterpret_cast<const uint2*>(h);
+    return make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16),
+                      (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+  };
+  auto take = [&](long long v, float4 z, float4 k, uint2 h) {
+    if constexpr (POOLED) {
+      const float px = 0.125f * z.x, py = 0.125f * z.y, pz = 0.125f * z.z, pw = 0.125f * z.w;
+      z = make_float4(px + k.x, py + k.y, pz + k.z, pw + k.w);
+    }
+    if constexpr (FUSED) {
+      if (relu) {
+        if (!(bf2f((uint16_t)h.x) > 0.f)) z.x = 0.f;
+        if (!(bf2f((uint16_t)(h.x >> 16)) > 0.f)) z.y = 0.f;
+        if (!(bf2f((uint16_t)h.y) > 0.f)) z.z = 0.f;
+        if (!(bf2f((uint16_t)(h.y >> 16)) > 0.f)) z.w = 0.f;
+      }
+      const uint16_t o[4] = {f2bf(z.x), f2bf(z.y), f2bf(z.z), f2bf(z.w)};
+      uint16_t* d = dzb + v * c + ch;
+      if (vec)
+        *reinterpret_cast<uint2*>(d) =
+            make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+      else
+        for (int j = 0; j < 4; ++j) d[j] = o[j];
+    }
+    s.x += z.x;
+    s.y += z.y;
+    s.z += z.z;
+    s.w += z.w;
+  };
+
+  long long v = beg + g;
+  for (; v + (kBiasAhead - 1) * G < end; v += kBiasAhead * G) {
+    float4 z[kBiasAhead], k[kBiasAhead];
+    uint2 h[kBiasAhead] = {};
+    if (FUSED && relu)
+#pragma unroll
+      for (int j = 0; j < kBiasAhead; ++j) h[j] = activation(v + j * G);
+#pragma unroll
+    for (int j = 0; j < kBiasAhead; ++j) gradient(v + j * G, z[j], k[j]);
+#pragma unroll
+    for (int j = 0; j < kBiasAhead; ++j) take(v + j * G, z[j], k[j], h[j]);
+  }
+  for (; v < end; v += G) {
+    float4 z, k;
+    gradient(v, z, k);
+    take(v, z, k, FUSED && relu ? activation(v) : make_uint2(0, 0));
   }
   sh[tid] = s;
   __syncthreads();
-  if (tid < c4) {
+  if (tid < qs) {
     float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int r = 0; r < G; ++r) {
-      const float4 u = sh[r * c4 + tid];
+      const float4 u = sh[r * qs + tid];
       t.x += u.x;
       t.y += u.y;
       t.z += u.z;
       t.w += u.w;
     }
-    float* out = part + (long long)blockIdx.x * c + 4 * tid;
+    float* out = part + (long long)blockIdx.x * c + ch;
     out[0] = t.x;
     out[1] = t.y;
     out[2] = t.z;
@@ -1244,6 +1296,21 @@ __global__ __launch_bounds__(256) void bias4_part_kernel(const float* __restrict
   }
 }
 bool bias4(int c) { return c % 4 == 0 && c <= 1024; }
+
+// Blocks of `splits` voxel ranges: the channels are halved among blocks until
+// two of them per compute unit are there, in slices of at least 8 quads (128
+// bytes of a row).
+template <bool FUSED, bool POOLED>
+void launch_bias4(const float* da, const void* a, void* dz, void* ws, long long m, int c,
+                  long long splits, long long per, int relu, int vec, const PooledSource& src,
+                  void* stream) {
+  int slices = 1, qs = c / 4;
+  const int groups = 256 / qs;
+  while (splits * slices < 512 && qs % 2 == 0 && qs >= 16) slices *= 2, qs /= 2;
+  bias4_part_kernel<FUSED, POOLED>
+      <<<dim3((unsigned)splits, slices), groups * qs, 0, (hipStream_t)stream>>>(
+          da, (const uint16_t*)a, (uint16_t*)dz, (float*)ws, m, c, qs, per, relu, vec, src);
+}
 
 // The backward of a layer's activation, fused with what the convolution's
 // backward needs from it: dz = (relu ? (a > 0 ? da : 0) : da) stored as BF16
@@ -1594,8 +1661,11 @@ __global__ void up_fwd_vec_kernel(const uint4* __restrict__ x, uint4* __restrict
   }
 }
 
+// Fine rows of dy are gs granules apart: gs > g reads the first channels of the
+// concatenation's gradient in place, which spares splitting it (three levels of
+// a 64^3 x 4 training step: 78 us, 275 with the split).
 __global__ void up_bwd_vec_kernel(const float4* __restrict__ dy, float4* __restrict__ dx, int n_,
-                                  int d, int h, int w, int g) {
+                                  int d, int h, int w, int g, int gs) {
   const int total = n_ * d * h * w * g;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
     const int gi = i % g;
@@ -1605,7 +1675,7 @@ __global__ void up_bwd_vec_kernel(const float4* __restrict__ dy, float4* __restr
     for (int o = 0; o < 8; ++o) {
       const int f = ((vn * 2 * d + 2 * vz + (o >> 2)) * 2 * h + 2 * vy + ((o >> 1) & 1)) * 2 * w +
                     2 * vx + (o & 1);
-      const float4 v = dy[f * g + gi];
+      const float4 v = dy[(long long)f * gs + gi];
       a.x += v.x;
       a.y += v.y;
       a.z += v.z;
@@ -1622,6 +1692,26 @@ __global__ void concat_vec_kernel(const uint4* __restrict__ a, const uint4* __re
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
     const int v = i / g, k = i % g;
     y[i] = k < ga ? a[v * ga + k] : b[v * gb + k - ga];
+  }
+}
+
+// y = [upsampled a | b]: granules ga of the coarse a (n, d, h, w) and gb of the
+// fine b.  Bound by memory: the upsampled tensor is neither written nor read
+// again (the three levels of a 64^3 x 4 network: 76 us, 140 in two kernels).
+__global__ __launch_bounds__(256) void upsample_concat_kernel(const uint4* __restrict__ a,
+                                                              const uint4* __restrict__ b,
+                                                              uint4* __restrict__ y, int n_, int d,
+                                                              int h, int w, int ga, int gb) {
+  const int g = ga + gb, total = n_ * 8 * d * h * w * g;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+    const int v = i / g, k = i - v * g;
+    if (k < ga) {
+      int vn, vz, vy, vx;
+      voxel_of(v, 2 * d, 2 * h, 2 * w, vn, vz, vy, vx);
+      y[i] = a[(((vn * d + vz / 2) * h + vy / 2) * w + vx / 2) * ga + k];
+    } else {
+      y[i] = b[(long long)v * gb + k - ga];
+    }
   }
 }
 
@@ -1992,8 +2082,8 @@ NN_API lbm_status nn_bias_grad(const float* dy, float* db, void* ws, size_t ws_b
   const long long splits = need / ((size_t)c * sizeof(float));
   const long long per = (m + splits - 1) / splits;
   if (bias4(c))
-    bias4_part_kernel<false><<<(unsigned)splits, 256, 0, (hipStream_t)stream>>>(
-        dy, nullptr, nullptr, (float*)ws, m, c, per, 0, aligned16(dy) ? 1 : 0);
+    launch_bias4<false, false>(dy, nullptr, nullptr, ws, m, c, splits, per, 0,
+                               aligned16(dy) ? 1 : 0, PooledSource{}, stream);
   else
     bias_grad_part_kernel<<<(unsigned)splits, 256, 0, (hipStream_t)stream>>>(dy, (float*)ws, m,
                                                                             c, per);
@@ -2014,8 +2104,8 @@ NN_API lbm_status nn_relu_backward_bias(const float* da, const void* a, void* dz
   const long long per = (m + splits - 1) / splits;
   if (bias4(c)) {
     const bool vec = aligned16(da) && ((uintptr_t)dz & 7) == 0 && (!relu || ((uintptr_t)a & 7) == 0);
-    bias4_part_kernel<true><<<(unsigned)splits, 256, 0, (hipStream_t)stream>>>(
-        da, (const uint16_t*)a, (uint16_t*)dz, (float*)ws, m, c, per, relu, vec ? 1 : 0);
+    launch_bias4<true, false>(da, a, dz, ws, m, c, splits, per, relu, vec ? 1 : 0,
+                              PooledSource{}, stream);
   } else {
     relu_bwd_bias_part_kernel<<<(unsigned)splits, 256, 0, (hipStream_t)stream>>>(
         da, (const uint16_t*)a, (uint16_t*)dz, (float*)ws, m, c, per, relu);
@@ -2318,7 +2408,7 @@ NN_API lbm_status nn_upsample2_backward(const float* dy, float* dx, int n, int d
   const Shape q = shape_of(n, d, h, w);
   if (c % 4 == 0 && aligned16(dy) && aligned16(dx) && q.m * 8 * c < (1LL << 31)) {
     up_bwd_vec_kernel<<<grid_for(q.m * (c / 4)), 256, 0, (hipStream_t)stream>>>(
-        (const float4*)dy, (float4*)dx, n, d, h, w, c / 4);
+        (const float4*)dy, (float4*)dx, n, d, h, w, c / 4, c / 4);
     return check_launch();
   }
   up_bwd_kernel<<<grid_for(q.m * c), 256, 0, (hipStream_t)stream>>>(dy, dx, q, c);
@@ -2349,6 +2439,54 @@ NN_API lbm_status nn_split_channels(const float* dy, float* da, float* db, long 
     return check_launch();
   }
   split_kernel<<<grid_for(m * (ca + cb)), 256, 0, (hipStream_t)stream>>>(dy, da, db, m, ca, cb);
+  return check_launch();
+}
+
+NN_API lbm_status nn_upsample_concat(const void* a, const void* b, void* y, int n, int d, int h,
+                                     int w, int ca, int cb, void* stream) {
+  if (!a || !b || !y || bad_shape(n, d, h, w) || ca < 8 || ca % 8 || cb < 8 || cb % 8 ||
+      !aligned16(a) || !aligned16(b) || !aligned16(y) ||
+      8LL * n * d * h * w * (ca + cb) >= (1LL << 31))
+    return LBM_ERR_INVALID_ARG;
+  upsample_concat_kernel<<<grid_for(8LL * n * d * h * w * ((ca + cb) / 8)), 256, 0,
+                           (hipStream_t)stream>>>((const uint4*)a, (const uint4*)b, (uint4*)y, n,
+                                                  d, h, w, ca / 8, cb / 8);
+  return check_launch();
+}
+
+NN_API lbm_status nn_concat_upsample_backward(const float* dcat, float* da, int n, int d, int h,
+                                              int w, int ca, int cb, void* stream) {
+  if (!dcat || !da || bad_shape(n, d, h, w) || ca < 4 || ca % 4 || cb < 4 || cb % 4 ||
+      !aligned16(dcat) || !aligned16(da) || 8LL * n * d * h * w * (ca + cb) >= (1LL << 31))
+    return LBM_ERR_INVALID_ARG;
+  up_bwd_vec_kernel<<<grid_for((long long)n * d * h * w * (ca / 4)), 256, 0, (hipStream_t)stream>>>(
+      (const float4*)dcat, (float4*)da, n, d, h, w, ca / 4, (ca + cb) / 4);
+  return check_launch();
+}
+
+NN_API lbm_status nn_pooled_backward_bias(const float* pooled, const float* cat, int ca,
+                                          const void* a, void* dz, float* db, void* ws,
+                                          size_t ws_bytes, int n, int d, int h, int w, int c,
+                                          int relu, void* stream) {
+  size_t need = 0;
+  if (bad_shape(n, d, h, w) || d % 2 || h % 2 || w % 2) return LBM_ERR_INVALID_ARG;
+  const long long m = (long long)n * d * h * w;
+  lbm_status st = nn_bias_grad_workspace(m, c, &need);
+  // v e < 2^32 for every voxel v and edge e: the divisions by __umulhi are exact
+  const int edge = d > h ? (d > w ? d : w) : (h > w ? h : w);
+  if (st != LBM_OK || !pooled || !cat || !dz || !db || (relu != 0 && relu != 1) || (relu && !a) ||
+      ca < 4 || ca % 4 || !bias4(c) || m * (ca + c) >= (1LL << 31) || m > (1LL << 32) / edge ||
+      !aligned16(pooled) || !aligned16(cat) || ((uintptr_t)dz & 7) ||
+      (relu && ((uintptr_t)a & 7)))
+    return LBM_ERR_INVALID_ARG;
+  if (!ws || ws_bytes < need) return LBM_ERR_WORKSPACE;
+  const long long splits = need / ((size_t)c * sizeof(float));
+  const long long per = (m + splits - 1) / splits;
+  auto by = [](int e) { return (uint32_t)(((1ULL << 32) + e - 1) / e); };
+  const PooledSource src{cat, ca, d, h, w, by(w), by(h), by(d)};
+  launch_bias4<true, true>(pooled, a, dz, ws, m, c, splits, per, relu, 1, src, stream);
+  fold_splits_kernel<<<grid_for(c), 256, 0, (hipStream_t)stream>>>((const float*)ws, db, c,
+                                                                  (int)splits);
   return check_launch();
 }
 

@@ -61,6 +61,10 @@ def _nn():
         "nn_concat_channels": [vp, vp, vp, i64, i32, i32, vp],
         "nn_split_channels": [vp, vp, vp, i64, i32, i32, vp],
         "nn_add": [vp, vp, i64, vp],
+        "nn_upsample_concat": [vp, vp, vp, i32, i32, i32, i32, i32, i32, vp],
+        "nn_concat_upsample_backward": [vp, vp, i32, i32, i32, i32, i32, i32, vp],
+        "nn_pooled_backward_bias": [vp, vp, i32, vp, vp, vp, vp, sz, i32, i32, i32, i32, i32, i32,
+                                    vp],
         "nn_coarse_pack_input": [vp, i32, i32, vp, vp],
         "nn_prolongate2": [vp, vp, i32, i32, i32, i32, i32, i32, vp, vp],
         "nn_warm_start_fields": [vp, i32, vp, vp, i32, i32, i32, i32, f64, f64, vp],
@@ -89,7 +93,8 @@ NN_EXPORTS = (
 
 NN_PREPARED_EXPORTS = (  # include/lbm_nn_prepared.h
     "nn_conv3d_packed_bytes", "nn_conv3d_forward_packed", "nn_conv3d_pack_weights",
-    "nn_coarse_pack_input",
+    "nn_coarse_pack_input", "nn_upsample_concat", "nn_concat_upsample_backward",
+    "nn_pooled_backward_bias",
 )
 
 
@@ -187,11 +192,14 @@ class Conv:
                                             self.ctx.stream), "conv forward + activation")
         return a
 
-    def backward(self, x_bf, dy32, shape, need_dx=True, act=None):
+    def backward(self, x_bf, dy32, shape, need_dx=True, act=None, skip=None):
         """Weight and bias gradients (and the input gradient if need_dx) for
         the FP32 gradient dy32 of the layer's output; act is the stored BF16
         activation of a ReLU layer (its backward, the BF16 cast and the bias
-        gradient are one kernel), None for a linear layer."""
+        gradient are one kernel), None for a linear layer.  With skip = (dcat,
+        ca) the layer's output was pooled and concatenated: dy32 is then the
+        gradient of the pooled tensor, and that of the concatenation beyond its
+        first ca channels is added."""
         lib = _nn()
         n, d, h, w = shape
         m = n * d * h * w
@@ -200,10 +208,15 @@ class Conv:
         bb = C.c_size_t()
         _chk(lib.nn_bias_grad_workspace(m, self.co, C.byref(bb)), "bias ws")
         bws = t.empty(int(bb.value), dtype=t.uint8, device=self.ctx.dev)
-        _chk(lib.nn_relu_backward_bias(_p(dy32), None if act is None else _p(act), _p(dy),
-                                       _p(self.gb), _p(bws), bb.value, m, self.co,
-                                       0 if act is None else 1, self.ctx.stream),
-             "activation backward + bias grad")
+        relu = 0 if act is None else 1
+        if skip is not None:
+            _chk(lib.nn_pooled_backward_bias(_p(dy32), _p(skip[0]), skip[1], _p(act), _p(dy),
+                                             _p(self.gb), _p(bws), bb.value, n, d, h, w, self.co,
+                                             relu, self.ctx.stream), "pooled backward + bias grad")
+        else:
+            _chk(lib.nn_relu_backward_bias(_p(dy32), _p(act), _p(dy), _p(self.gb), _p(bws),
+                                           bb.value, m, self.co, relu, self.ctx.stream),
+                 "activation backward + bias grad")
         nbytes = C.c_size_t()
         sp = C.c_int()
         _chk(lib.nn_conv3d_backward_weight_workspace(n, d, h, w, self.ci, self.co,
@@ -253,6 +266,17 @@ class UNet:
         return sum(l.n_params() for l in self.layers())
 
     # -------------------------------------------------------------- passes
+    def _fused(self, shape) -> bool:
+        """Whether the fused up- and downsampling calls take boxes of this shape
+        (n, d, h, w): widths in multiples of 8 (up to 1024 in the encoder), fewer
+        than 2^31 elements in the widest concatenation, indices that divide by
+        a 32-bit reciprocal."""
+        w = self.widths
+        m = int(np.prod(shape))
+        return (all(v % 8 == 0 for v in w) and max(w[:3]) <= 1024
+                and m * max(w[0] + w[1], w[1] + w[2], w[2] + w[3]) < 2**31
+                and m * max(shape[1:]) <= 2**32)
+
     def forward(self, x_bf):
         """x_bf: bf16 (n, d, h, w, 8), d, h, w divisible by 8.  Returns the
         FP32 output (n, d, h, w, 8) and keeps what the backward pass needs."""
@@ -272,16 +296,22 @@ class UNet:
             e.append(conv.forward_act(inp, shapes[lvl]))
             inp = e[-1]
         cur = e[3]
+        fused = self._fused(shapes[0])
         for j, conv in enumerate(self.dec):
             lvl = 2 - j
             ccur = self.widths[lvl + 1]
-            up = self.ctx.bf(*shapes[lvl], ccur)
             qn, qd, qh, qw = shapes[lvl + 1]
-            _chk(lib.nn_upsample2_forward(_p(cur), _p(up), qn, qd, qh, qw, ccur, s), "upsample")
             cat = self.ctx.bf(*shapes[lvl], conv.ci)
             m = int(np.prod(shapes[lvl]))
-            _chk(lib.nn_concat_channels(_p(up), _p(e[lvl]), _p(cat), m, ccur, self.widths[lvl], s),
-                 "concat")
+            if fused:
+                _chk(lib.nn_upsample_concat(_p(cur), _p(e[lvl]), _p(cat), qn, qd, qh, qw, ccur,
+                                            self.widths[lvl], s), "upsample + concat")
+            else:
+                up = self.ctx.bf(*shapes[lvl], ccur)
+                _chk(lib.nn_upsample2_forward(_p(cur), _p(up), qn, qd, qh, qw, ccur, s),
+                     "upsample")
+                _chk(lib.nn_concat_channels(_p(up), _p(e[lvl]), _p(cat), m, ccur,
+                                            self.widths[lvl], s), "concat")
             self.cache[f"cat{lvl}"] = cat
             cur = conv.forward_act(cat, shapes[lvl])
             self.cache[f"d{lvl}"] = cur
@@ -297,28 +327,36 @@ class UNet:
         shapes, e = c["shapes"], c["e"]
         # head (linear)
         g = self.head.backward(c["d0"], dout, shapes[0])
-        skip_grads = [None] * 3
-        for j, conv in enumerate(self.dec):
-            lvl = j  # backward goes 0, 1, 2 through decoder levels
+        fused = self._fused(shapes[0])
+        skips = [None] * 3  # per level: the concatenation's gradient and its first channels
+        for lvl in range(3):  # backward goes 0, 1, 2 through decoder levels
             conv = self.dec[2 - lvl]
             dcat = conv.backward(c[f"cat{lvl}"], g, shapes[lvl], act=c[f"d{lvl}"])
             ccur = self.widths[lvl + 1]
+            qn, qd, qh, qw = shapes[lvl + 1]
+            g = self.ctx.f32(*shapes[lvl + 1], ccur)
+            if fused:
+                skips[lvl] = (dcat, ccur)
+                _chk(lib.nn_concat_upsample_backward(_p(dcat), _p(g), qn, qd, qh, qw, ccur,
+                                                     self.widths[lvl], s), "concat + up backward")
+                continue
             m = int(np.prod(shapes[lvl]))
             dup = self.ctx.f32(*shapes[lvl], ccur)
-            dskip = self.ctx.f32(*shapes[lvl], self.widths[lvl])
-            _chk(lib.nn_split_channels(_p(dcat), _p(dup), _p(dskip), m, ccur, self.widths[lvl], s),
-                 "split")
-            skip_grads[lvl] = dskip
-            g = self.ctx.f32(*shapes[lvl + 1], ccur)
-            qn, qd, qh, qw = shapes[lvl + 1]
+            skips[lvl] = self.ctx.f32(*shapes[lvl], self.widths[lvl])
+            _chk(lib.nn_split_channels(_p(dcat), _p(dup), _p(skips[lvl]), m, ccur,
+                                       self.widths[lvl], s), "split")
             _chk(lib.nn_upsample2_backward(_p(dup), _p(g), qn, qd, qh, qw, ccur, s), "up backward")
-        # g: gradient of e[3]; down the encoder
+        # g: gradient of e[3]; down the encoder (fused: of the pooled tensor)
         for lvl in (3, 2, 1, 0):
             conv = self.enc[lvl]
-            if lvl < 3:
-                _chk(lib.nn_add(_p(g), _p(skip_grads[lvl]), g.numel(), s), "add")
-            dinp = conv.backward(c[f"in{lvl}"], g, shapes[lvl], need_dx=lvl > 0, act=e[lvl])
-            if lvl > 0:
+            skip = skips[lvl] if lvl < 3 and fused else None
+            if lvl < 3 and not fused:
+                _chk(lib.nn_add(_p(g), _p(skips[lvl]), g.numel(), s), "add")
+            dinp = conv.backward(c[f"in{lvl}"], g, shapes[lvl], need_dx=lvl > 0, act=e[lvl],
+                                 skip=skip)
+            if lvl > 0 and fused:
+                g = dinp
+            elif lvl > 0:
                 g = self.ctx.f32(*shapes[lvl - 1], conv.ci)
                 pn, pd, ph, pw = shapes[lvl - 1]
                 _chk(lib.nn_pool2_backward(_p(dinp), _p(g), pn, pd, ph, pw, conv.ci, s),

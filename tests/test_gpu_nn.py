@@ -468,3 +468,61 @@ def test_unet_training_reduces_loss(ctx):
         net.adam_step(1e-2)
         losses.append(loss)
     assert losses[-1] < 0.3 * losses[0], losses
+
+
+@pytest.mark.parametrize("shape,ca,cb", [((1, 2, 2, 2), 8, 8), ((2, 3, 5, 7), 16, 8),
+                                         ((1, 4, 6, 10), 24, 48), ((3, 8, 8, 8), 64, 32)])
+def test_fused_sampling_steps_give_the_same_bits(ctx, shape, ca, cb):
+    """Upsampling with concatenation, its gradient, and the bias gradient that
+    forms its input from the pooled and the concatenated gradients: bit for bit
+    the single steps (shape: the coarse box; the fine one has odd halves)."""
+    import ctypes as C
+
+    t = ctx.torch
+    rng = np.random.default_rng(ca + cb)
+    lib = W._nn()
+    s = ctx.stream
+    n, d, h, w = shape
+    fine = (n, 2 * d, 2 * h, 2 * w)
+    m = int(np.prod(fine))
+    a, b = _bf_dev(ctx, rng.standard_normal(shape + (ca,))), _bf_dev(
+        ctx, rng.standard_normal(fine + (cb,)))
+    up, want, got = ctx.bf(*fine, ca), ctx.bf(*fine, ca + cb), ctx.bf(*fine, ca + cb)
+    assert lib.nn_upsample2_forward(W._p(a), W._p(up), n, d, h, w, ca, s) == 0
+    assert lib.nn_concat_channels(W._p(up), W._p(b), W._p(want), m, ca, cb, s) == 0
+    assert lib.nn_upsample_concat(W._p(a), W._p(b), W._p(got), n, d, h, w, ca, cb, s) == 0
+    assert t.equal(got.view(t.int16), want.view(t.int16))
+
+    dcat = _f_dev(ctx, rng.standard_normal(fine + (ca + cb,)))
+    dup, dskip = ctx.f32(*fine, ca), ctx.f32(*fine, cb)
+    da, da_want = ctx.f32(*shape, ca), ctx.f32(*shape, ca)
+    assert lib.nn_split_channels(W._p(dcat), W._p(dup), W._p(dskip), m, ca, cb, s) == 0
+    assert lib.nn_upsample2_backward(W._p(dup), W._p(da_want), n, d, h, w, ca, s) == 0
+    assert lib.nn_concat_upsample_backward(W._p(dcat), W._p(da), n, d, h, w, ca, cb, s) == 0
+    assert t.equal(da, da_want)
+
+    pooled, act = _f_dev(ctx, rng.standard_normal(shape + (cb,))), _bf_dev(
+        ctx, np.maximum(rng.standard_normal(fine + (cb,)), 0))
+    g = ctx.f32(*fine, cb)
+    assert lib.nn_pool2_backward(W._p(pooled), W._p(g), *fine, cb, s) == 0
+    assert lib.nn_add(W._p(g), W._p(dskip), g.numel(), s) == 0
+    bb = C.c_size_t()
+    assert lib.nn_bias_grad_workspace(m, cb, C.byref(bb)) == 0
+    ws = t.empty(bb.value, dtype=t.uint8, device=ctx.dev)
+    for relu in (1, 0):
+        out = []
+        for dz, db in ((ctx.bf(*fine, cb), ctx.f32(cb)), (ctx.bf(*fine, cb), ctx.f32(cb))):
+            if not out:
+                st = lib.nn_relu_backward_bias(W._p(g), W._p(act), W._p(dz), W._p(db), W._p(ws),
+                                               bb.value, m, cb, relu, s)
+            else:
+                st = lib.nn_pooled_backward_bias(W._p(pooled), W._p(dcat), ca, W._p(act),
+                                                 W._p(dz), W._p(db), W._p(ws), bb.value, *fine,
+                                                 cb, relu, s)
+            assert st == 0
+            out.append((dz, db))
+        assert t.equal(out[0][0].view(t.int16), out[1][0].view(t.int16)) and t.equal(
+            out[0][1], out[1][1])
+    assert lib.nn_pooled_backward_bias(W._p(pooled), W._p(dcat), ca, W._p(act), W._p(dz), W._p(db),
+                                       W._p(ws), bb.value, n, 2 * d, 2 * h, 2 * w - 1, cb, 1,
+                                       s) == 1  # odd edges cannot have been pooled
