@@ -2,8 +2,7 @@
  * lbm_nn_prepared.h - C ABI of the network's calls on prepared operands
  * (liblbm.so): convolutions from weights packed once for the kernels, steps of
  * the network fused with their neighbours, and the network input of a sphere
- * pack formed on the device.  Conventions as in
- * lbm_nn.h.
+ * pack formed on the device.  Conventions as in lbm_nn.h.
  */
 #ifndef LBM_NN_PREPARED_H
 #define LBM_NN_PREPARED_H
@@ -29,6 +28,27 @@ lbm_status nn_conv3d_forward_packed(const void* x, const void* packed, const flo
  * ci = co, co = ci)). */
 lbm_status nn_conv3d_pack_weights(const void* w, void* packed, int ci, int co, int flip,
                                   void* stream);
+
+/* nn_conv3d_pack_weights of `count` layers in few launches. */
+typedef struct {
+  const void* w;
+  void* packed;
+  int ci, co, flip;
+} nn_pack_item;
+lbm_status nn_conv3d_pack_weights_many(const nn_pack_item* items, int count, void* stream);
+
+/* nn_adam of `count` tensors in few launches (w_bf16 may be NULL); both lists
+ * are read before the call returns, and no tensor may be listed twice. */
+typedef struct {
+  float* w;
+  const float* g;
+  float* m1;
+  float* m2;
+  void* w_bf16;
+  long long n;
+} nn_adam_tensor;
+lbm_status nn_adam_many(const nn_adam_tensor* tensors, int count, float lr, float b1, float b2,
+                        float eps, int step, void* stream);
 
 /* Network input of a periodic pack of spheres on the grid of half the
  * resolution (the two-grid start): x (bf16, ec,ec,ec,8 with ec = edge / 2) is 1

@@ -65,6 +65,8 @@ def _nn():
         "nn_concat_upsample_backward": [vp, vp, i32, i32, i32, i32, i32, i32, vp],
         "nn_pooled_backward_bias": [vp, vp, i32, vp, vp, vp, vp, sz, i32, i32, i32, i32, i32, i32,
                                     vp],
+        "nn_conv3d_pack_weights_many": [vp, i32, vp],
+        "nn_adam_many": [vp, i32, f32, f32, f32, f32, i32, vp],
         "nn_coarse_pack_input": [vp, i32, i32, vp, vp],
         "nn_prolongate2": [vp, vp, i32, i32, i32, i32, i32, i32, vp, vp],
         "nn_warm_start_fields": [vp, i32, vp, vp, i32, i32, i32, i32, f64, f64, vp],
@@ -94,8 +96,21 @@ NN_EXPORTS = (
 NN_PREPARED_EXPORTS = (  # include/lbm_nn_prepared.h
     "nn_conv3d_packed_bytes", "nn_conv3d_forward_packed", "nn_conv3d_pack_weights",
     "nn_coarse_pack_input", "nn_upsample_concat", "nn_concat_upsample_backward",
-    "nn_pooled_backward_bias",
+    "nn_pooled_backward_bias", "nn_conv3d_pack_weights_many", "nn_adam_many",
 )
+
+
+class _AdamTensor(C.Structure):
+    _fields_ = [(k, C.c_void_p) for k in ("w", "g", "m1", "m2", "w_bf16")] + [("n", C.c_longlong)]
+
+
+class _PackItem(C.Structure):
+    _fields_ = [("w", C.c_void_p), ("packed", C.c_void_p), ("ci", C.c_int), ("co", C.c_int),
+                ("flip", C.c_int)]
+
+
+def _items(kind, rows):
+    return (kind * len(rows))(*(kind(*r) for r in rows)), len(rows)
 
 
 def _p(t):
@@ -233,12 +248,23 @@ class Conv:
         return dx
 
     def adam(self, lr, step, b1=0.9, b2=0.999, eps=1e-8):
-        lib = _nn()
-        _chk(lib.nn_adam(_p(self.w), _p(self.gw), _p(self.mw), _p(self.vw), _p(self.wb),
-                         self.w.numel(), lr, b1, b2, eps, step, self.ctx.stream), "adam")
-        _chk(lib.nn_adam(_p(self.b), _p(self.gb), _p(self.mb), _p(self.vb), None, self.co, lr,
-                         b1, b2, eps, step, self.ctx.stream), "adam")
-        self._pack()
+        _adam((self,), lr, step, b1, b2, eps)
+
+
+def _adam(layers, lr, step, b1=0.9, b2=0.999, eps=1e-8):
+    """One optimizer step of the layers: master weights, BF16 weights and their
+    packed forms, in one launch each."""
+    lib, ctx = _nn(), layers[0].ctx
+    tensors, packs = [], []
+    for l in layers:
+        tensors += [(l.w.data_ptr(), l.gw.data_ptr(), l.mw.data_ptr(), l.vw.data_ptr(),
+                     l.wb.data_ptr(), l.w.numel()),
+                    (l.b.data_ptr(), l.gb.data_ptr(), l.mb.data_ptr(), l.vb.data_ptr(), None, l.co)]
+        packs += [(l.wb.data_ptr(), p.data_ptr(), l.ci, l.co, flip)
+                  for p, flip in ((l.wp, 0), (l.wtp, 1)) if p is not None]
+    _chk(lib.nn_adam_many(*_items(_AdamTensor, tensors), lr, b1, b2, eps, step, ctx.stream), "adam")
+    if packs:
+        _chk(lib.nn_conv3d_pack_weights_many(*_items(_PackItem, packs), ctx.stream), "pack")
 
 
 class UNet:
@@ -364,8 +390,7 @@ class UNet:
 
     def adam_step(self, lr: float):
         self.step_count += 1
-        for l in self.layers():
-            l.adam(lr, self.step_count)
+        _adam(self.layers(), lr, self.step_count)
 
     # --------------------------------------------------------------- loss
     def loss(self, out, target, weight, norm: float, sync: bool = True):

@@ -526,3 +526,43 @@ def test_fused_sampling_steps_give_the_same_bits(ctx, shape, ca, cb):
     assert lib.nn_pooled_backward_bias(W._p(pooled), W._p(dcat), ca, W._p(act), W._p(dz), W._p(db),
                                        W._p(ws), bb.value, n, 2 * d, 2 * h, 2 * w - 1, cb, 1,
                                        s) == 1  # odd edges cannot have been pooled
+
+
+@pytest.mark.parametrize("sizes", [[5], [1024, 1, 0, 1025, 300], [257] * 60])
+def test_updates_and_packings_of_many_tensors_give_the_same_bits(ctx, sizes):
+    """nn_adam_many and nn_conv3d_pack_weights_many (one block's span, its edges,
+    an empty tensor, more tensors than one launch takes) against the calls per
+    tensor."""
+    import ctypes as C
+
+    t = ctx.torch
+    rng = np.random.default_rng(len(sizes))
+    lib = W._nn()
+    s = ctx.stream
+
+    def tensors(seed):
+        r = np.random.default_rng(seed)
+        return [[_f_dev(ctx, np.abs(r.standard_normal(n + 1))) for _ in range(4)]
+                + [ctx.bf(n + 1).zero_()] for n in sizes]
+
+    one, many = tensors(3), tensors(3)
+    for n, q in zip(sizes, one):
+        assert not n or lib.nn_adam(*map(W._p, q), n, 1e-2, 0.9, 0.999, 1e-8, 3, s) == 0
+    rows = [tuple(v.data_ptr() for v in q) + (n,) for n, q in zip(sizes, many)]
+    assert lib.nn_adam_many(*W._items(W._AdamTensor, rows), 1e-2, 0.9, 0.999, 1e-8, 3, s) == 0
+    for a, b in zip(one, many):
+        assert all(t.equal(x.view(t.int16), y.view(t.int16)) for x, y in zip(a, b))
+
+    shapes = [(8, 5), (32, 16), (16, 48), (64, 24)][:len(sizes)] * (1 if len(sizes) < 30 else 8)
+    items, pairs = [], []
+    for ci, co in shapes:
+        w = _bf_dev(ctx, rng.standard_normal((co, 27, ci)))
+        for flip in (0, 1) if co % 8 == 0 else (0,):
+            nb = C.c_size_t()
+            assert lib.nn_conv3d_packed_bytes(*((co, ci) if flip else (ci, co)), C.byref(nb)) == 0
+            a, b = ctx.bf(nb.value // 2), ctx.bf(nb.value // 2)
+            assert lib.nn_conv3d_pack_weights(W._p(w), W._p(a), ci, co, flip, s) == 0
+            items.append((w.data_ptr(), b.data_ptr(), ci, co, flip))
+            pairs.append((a, b, w))
+    assert lib.nn_conv3d_pack_weights_many(*W._items(W._PackItem, items), s) == 0
+    assert all(t.equal(a.view(t.int16), b.view(t.int16)) for a, b, _ in pairs)
