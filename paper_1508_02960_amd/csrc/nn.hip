@@ -1832,11 +1832,17 @@ void launch_fwd_rows_of(const uint16_t* x, const uint16_t* w, const float* bias,
 // Channel groups of 32 per wavefront (16 for few channels); pairs of groups
 // share a block's halo where their count is even (96 channels: 257 us with
 // one group per block against 293 us with two, a quarter of them empty).
+// Multiples of 96 channels are pairs of groups of 48 where two layers a block
+// still are two blocks per CU: a fragment serves three weight tiles, the halo
+// all channels (32 -> 96 channels at 64^3 x 4, packed, FP32 output 308 -> 287
+// us, BF16 221 -> 207; 64 -> 96 at 32^3 x 4: 52 -> 48).
 template <bool PK, bool ACT>
 void launch_fwd_spatial(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                         const Shape& s, int ci, int co, int relu, hipStream_t st) {
   if (co <= 16)
     launch_fwd_rows_of<1, 1, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
+  else if (co % 96 == 0 && s.w % 16 == 0 && s.m / 256 * (co / 96) >= 2 * kFillBlocks)
+    launch_fwd_tile<16, 8, 3, 2, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   else if ((co + 31) / 32 % 2)
     launch_fwd_rows_of<2, 1, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   else
