@@ -39,6 +39,9 @@ enum { kSRT = 0, kTRT = 1, kMRT = 2 };
 // and the general interpolated rules (LIBB, QIBB, IEBB, MR; q in the solid
 // slot, rule chosen at run time by StepParams::wall, FP32/FP64 only).
 enum { kSBB = 0, kCLI = 1, kGEN = 2 };
+// Where a domain's two states live: within the last-level cache, beyond it, or
+// so far beyond that streaming stores pay.
+enum { kCached = 0, kBeyondCache = 1, kStreaming = 2 };
 // run-time rule numbers (lbm_wall)
 enum { kRuleSBB = 0, kRuleCLI = 1, kRuleLIBB = 2, kRuleQIBB = 3, kRuleIEBB = 4, kRuleMR = 5 };
 
@@ -52,11 +55,17 @@ struct Tiling {
   int nx, ny;            // box edge in x and y (cells)
   int tw_log2, th_log2;  // tile width and height, log2 (sum 6 or 7: tiles of 64 or 128 cells)
   int ntx;               // tiles per tile row (padded nx / tile width)
+  unsigned by_ntx;       // ceil(2^32 / ntx), 0 for one tile: tile / ntx is __umulhi (see tile_row)
   int nty;               // tile rows per plane
   int plane;             // cells per z plane including padding: ntx * nty * tile cells
   int run_log2;          // state buffers: runs of 2^run_log2 consecutive addresses,
   long long run_pitch;   // ... each direction of a run run_pitch elements after the last
   __host__ __device__ int tile_log2() const { return tw_log2 + th_log2; }
+  // tile / ntx without a division (exact: tile ntx < 2^32, as tiles of 64 cells
+  // fill a plane of fewer than 2^31)
+  __device__ int tile_row(int tile) const {
+    return by_ntx ? (int)__umulhi((unsigned)tile, by_ntx) : tile;
+  }
   __host__ __device__ int xpart(int x) const {
     return ((x >> tw_log2) << tile_log2()) | (x & ((1 << tw_log2) - 1));
   }
@@ -106,49 +115,82 @@ __device__ __forceinline__ long long state_slot(const Tiling& t, int k, long lon
     return ((((a >> t.run_log2) * kQ) + k) << t.run_log2) + (a & ((1LL << t.run_log2) - 1));
 }
 
-// Byte offset of direction k of the cell at address zstart + r, split into a
-// wavefront-uniform part (direction k and the z plane that starts at address
-// zstart, a whole number of runs) and a 32-bit part per lane (the in-plane
-// address r), so that a load is a scalar base plus a lane offset.  The host
-// keeps planes small enough for the lane part to fit in 32 bits.
-// The run length stays a run-time value here: the per-direction bases are
-// then computed on the scalar unit and every pull is a scalar base plus a
-// lane offset (512^3 sphere pack, FP32: 2.31 ms per step, against 2.37 ms
-// with the run length fixed at compile time, where the compiler folds the
-// direction offsets into 64-bit lane addresses, and 2.34-2.36 ms with 64-bit
-// lane addresses throughout).
-template <typename S>
-__device__ __forceinline__ long long state_base(const Tiling& t, int k, long long zstart) {
-  if constexpr (sizeof(S) == 2)
-    return 2LL * (k * t.run_pitch + zstart);
-  else  // zstart / run length runs of kQ directions before, then k directions
-    return (long long)sizeof(S) * (zstart * kQ + ((long long)k << t.run_log2));
+// A wavefront-uniform pointer, kept in scalar registers: without this the
+// compiler shares the lane part of an address between the directions and adds
+// each direction's offset to it in 64 bits per lane (a quarter of the vector
+// instructions of an FP32 step).
+template <typename T>
+__device__ __forceinline__ T* scalar_base(T* p) {
+  auto q = (__attribute__((address_space(1))) T*)p;  // (global: a pointer of unknown kind is flat)
+  asm("" : "+s"(q));
+  return (T*)q;
 }
-template <typename S>
+
+// Byte offset of the cell with in-plane address r from its z plane's values of
+// direction 0 (FP32 and FP64: RUN the log2 of the run length, 0 to take it from
+// the tiling).  The host keeps planes small enough for 32 bits.
+template <typename S, int RUN>
 __device__ __forceinline__ uint32_t state_lane(const Tiling& t, int r) {
   if constexpr (sizeof(S) == 2) {
     return 2u * (uint32_t)r;
-  } else {
+  } else if constexpr (RUN == 0) {
     const uint32_t run = (uint32_t)r >> t.run_log2, in = (uint32_t)r & ((1u << t.run_log2) - 1u);
     return (uint32_t)sizeof(S) * (((run * (uint32_t)kQ) << t.run_log2) + in);
+  } else {  // r = run 2^RUN + in; kQ directions per run (24-bit factors: a full-rate multiply)
+    return (uint32_t)sizeof(S) * (uint32_t)r +
+           __umul24((uint32_t)r >> RUN, (uint32_t)((kQ - 1) * sizeof(S)) << RUN);
   }
 }
-template <typename S, typename P>
-__device__ __forceinline__ P* state_at(P* base, const Tiling& t, int k, long long zstart, int r) {
-  using B = typename std::conditional<std::is_const<P>::value, const char, char>::type;
-  return reinterpret_cast<P*>(reinterpret_cast<B*>(base) + state_base<S>(t, k, zstart) +
-                              state_lane<S>(t, r));
-}
 
-// Element of direction k of the cell at address a: for direction planes the
-// plane's base (wavefront-uniform) plus the 32-bit address.
-template <typename S, typename P>
-__device__ __forceinline__ P* state_ptr(P* base, const Tiling& t, int k, int a) {
-  if constexpr (sizeof(S) == 2)
-    return (base + k * t.run_pitch) + a;
-  else
-    return base + state_slot<S>(t, k, a);
-}
+// The values of one z plane, which starts at address zstart (a whole number of
+// runs), for accesses of a scalar base plus a 32-bit lane offset (state_lane).
+// FP32 and FP64: direction k of a run lies k runs after direction 0, and with
+// the run length known the instruction's own offset (-4096 to 4095 bytes)
+// reaches eight directions from one base.  16-bit values: a base per direction
+// plane.
+//
+// States that fit the last-level cache, and the general wall rules, take run
+// lengths known at compile time: 448 vector and 170 scalar instructions per
+// wavefront against 582 and 287 (FP32 CLI; MRT in BF16 697 against 783), and a
+// step of 32^3 in FP64 takes 4.6 us against 4.9, of 64^3 in FP32 7.8 against
+// 8.1, of 90 x 75 x 101 in BF16 MRT 16.5 against 18.  States beyond the cache
+// are bound by memory and keep RUN = 0, where the compiler forms
+// the stores' and the walls' addresses per lane: with the shorter form their
+// wavefronts reach memory in denser bursts and a step is slower (FP32 512^3
+// sphere pack 2.37 ms against 2.30, 48 cells of 64^3 324 us against 315, 96 x
+// 128 x 144 in FP64 132 us against 131).
+template <typename S, int RUN, typename P>
+struct PlaneRows {
+  using B = typename std::conditional<std::is_const<P>::value, const char, char>::type;
+  B* base[3];
+  long long pitch;   // 16-bit values: bytes between direction planes
+  long long zstart;  // RUN = 0
+  int run_log2;
+  __device__ __forceinline__ PlaneRows(P* state, const Tiling& t, long long zstart) {
+    if constexpr (sizeof(S) == 2) {
+      base[0] = reinterpret_cast<B*>(state) + 2 * zstart;
+      pitch = 2 * t.run_pitch;
+    } else if constexpr (RUN == 0) {
+      base[0] = reinterpret_cast<B*>(state);
+      this->zstart = zstart;
+      run_log2 = t.run_log2;
+    } else {
+#pragma unroll
+      for (int g = 0; g < 3; ++g)
+        base[g] = scalar_base(reinterpret_cast<B*>(state) +
+                              (long long)sizeof(S) * (zstart * kQ + ((8 * g + 4) << RUN)));
+    }
+  }
+  __device__ __forceinline__ P* at(int k, uint32_t lane) const {
+    if constexpr (sizeof(S) == 2)
+      return reinterpret_cast<P*>(scalar_base(base[0] + k * pitch) + lane);
+    else if constexpr (RUN == 0)
+      return reinterpret_cast<P*>(
+          base[0] + (long long)sizeof(S) * (zstart * kQ + ((long long)k << run_log2)) + lane);
+    else
+      return reinterpret_cast<P*>(base[k >> 3] + lane + ((k & 7) - 4) * (int)(sizeof(S) << RUN));
+  }
+};
 
 // Cell classes (one byte per cell, tiled order).
 constexpr uint8_t kClsSolid = 1;  // solid (or padding) cell
@@ -176,6 +218,7 @@ struct StepParams {
   // or two x-adjacent tiles with two cells per lane) of bh consecutive tile
   // rows; nbx workgroups span a band of bh tile rows
   int bw, bh, nbx;
+  int by_bw;          // ceil(2^16 / bw): j / bw of a wavefront j < 16 is j by_bw >> 16
   // IEBB, one domain: the velocity (momentum j, as stored_moments) of the
   // cells marked kClsNearWall, 4 values of the compute type per address;
   // side_in belongs to the step's source state, side_out to the state it
@@ -339,12 +382,39 @@ __device__ __forceinline__ void moments(const C* g, C& rho, C& ux, C& uy, C& uz)
   uz = ((g[5] - g[6]) + (g[11] - g[14])) + ((g[12] - g[13]) + (g[15] - g[18])) + (g[16] - g[17]);
 }
 
-// Deviation equilibrium w_k {drho + 3 e.u + 4.5 (e.u)^2 - 1.5 u.u}.
+// e_k . u without the zero components (the compiler keeps products with a zero)
 template <typename C, int K>
-__device__ __forceinline__ C geq(C rho, C ux, C uy, C uz, C usq) {
+__device__ __forceinline__ C along(C ux, C uy, C uz) {
+  constexpr int ex = kLat.ex[K], ey = kLat.ey[K], ez = kLat.ez[K];
+  const C a = ex == 1 ? ux : -ux, b = ey == 1 ? uy : -uy, c = ez == 1 ? uz : -uz;
+  if constexpr (ex != 0 && ey != 0) return a + b;
+  else if constexpr (ex != 0 && ez != 0) return a + c;
+  else if constexpr (ey != 0 && ez != 0) return b + c;
+  else return ex != 0 ? a : (ey != 0 ? b : c);
+}
+
+// Deviation equilibrium w_k {drho + 3 e.u + 4.5 (e.u)^2 - 1.5 u.u} of the rest
+// direction and of an opposite pair, whose e.u differ in sign.
+template <typename C>
+__device__ __forceinline__ C geq_rest(C rho, C usq) {
+  return (C)kLat.w[0] * (rho - (C)1.5 * usq);
+}
+template <typename C, int K>
+__device__ __forceinline__ void geq_pair(C rho, C ux, C uy, C uz, C usq, C& a, C& b) {
   constexpr C w = (C)kLat.w[K];
-  const C eu = (C)kLat.ex[K] * ux + (C)kLat.ey[K] * uy + (C)kLat.ez[K] * uz;
-  return w * (rho + (C)3 * eu + (C)4.5 * eu * eu - (C)1.5 * usq);
+  const C eu = along<C, K>(ux, uy, uz);
+  const C t = (C)4.5 * eu;
+  a = w * (rho + (C)3 * eu + t * eu - (C)1.5 * usq);
+  b = w * (rho - (C)3 * eu + t * eu - (C)1.5 * usq);
+}
+
+template <typename C, int K>
+__device__ __forceinline__ void srt_pair(C* g, C rho, C ux, C uy, C uz, C usq, C omega) {
+  constexpr int KB = kLat.opp[K];
+  C a, b;
+  geq_pair<C, K>(rho, ux, uy, uz, usq, a, b);
+  g[K] = g[K] - omega * (g[K] - a);
+  g[KB] = g[KB] - omega * (g[KB] - b);
 }
 
 template <typename C>
@@ -352,11 +422,16 @@ __device__ __forceinline__ void collide_srt(C* g, C omega) {
   C rho, ux, uy, uz;
   moments(g, rho, ux, uy, uz);
   const C usq = ux * ux + uy * uy + uz * uz;
-#define LBM_SRT(K) g[K] = g[K] - omega * (g[K] - geq<C, K>(rho, ux, uy, uz, usq));
-  LBM_SRT(0) LBM_SRT(1) LBM_SRT(2) LBM_SRT(3) LBM_SRT(4) LBM_SRT(5) LBM_SRT(6) LBM_SRT(7)
-  LBM_SRT(8) LBM_SRT(9) LBM_SRT(10) LBM_SRT(11) LBM_SRT(12) LBM_SRT(13) LBM_SRT(14)
-  LBM_SRT(15) LBM_SRT(16) LBM_SRT(17) LBM_SRT(18)
-#undef LBM_SRT
+  g[0] = g[0] - omega * (g[0] - geq_rest<C>(rho, usq));
+  srt_pair<C, 1>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 3>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 5>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 7>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 8>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 11>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 12>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 15>(g, rho, ux, uy, uz, usq, omega);
+  srt_pair<C, 16>(g, rho, ux, uy, uz, usq, omega);
 }
 
 // TRT (eq. (TRT)): symmetric part relaxed with omega+, antisymmetric with
@@ -364,7 +439,7 @@ __device__ __forceinline__ void collide_srt(C* g, C omega) {
 template <typename C, int K, int KB>
 __device__ __forceinline__ void trt_pair(C* g, C rho, C ux, C uy, C uz, C usq, C wp, C wm) {
   constexpr C w = (C)kLat.w[K];
-  const C eu = (C)kLat.ex[K] * ux + (C)kLat.ey[K] * uy + (C)kLat.ez[K] * uz;
+  const C eu = along<C, K>(ux, uy, uz);
   const C eq_p = w * (rho + (C)4.5 * eu * eu - (C)1.5 * usq);
   const C eq_m = w * (C)3 * eu;
   const C dp = wp * ((C)0.5 * (g[K] + g[KB]) - eq_p);
@@ -425,10 +500,15 @@ __device__ __forceinline__ void collide_mrt(C* g, C s_nu, C s_e, C s_zeta) {
   moments(g, rho, ux, uy, uz);
   const C usq = ux * ux + uy * uy + uz * uz;
   C d[kQ];
-  d[0] = g[0] - geq<C, 0>(rho, ux, uy, uz, usq);
-#define LBM_D(K) d[K] = g[K] - geq<C, K>(rho, ux, uy, uz, usq);
-  LBM_D(1) LBM_D(2) LBM_D(3) LBM_D(4) LBM_D(5) LBM_D(6) LBM_D(7) LBM_D(8) LBM_D(9)
-  LBM_D(10) LBM_D(11) LBM_D(12) LBM_D(13) LBM_D(14) LBM_D(15) LBM_D(16) LBM_D(17) LBM_D(18)
+  d[0] = g[0] - geq_rest<C>(rho, usq);
+#define LBM_D(K)                                               \
+  {                                                            \
+    C a, b;                                                    \
+    geq_pair<C, K>(rho, ux, uy, uz, usq, a, b);                \
+    d[K] = g[K] - a;                                           \
+    d[kLat.opp[K]] = g[kLat.opp[K]] - b;                       \
+  }
+  LBM_D(1) LBM_D(3) LBM_D(5) LBM_D(7) LBM_D(8) LBM_D(11) LBM_D(12) LBM_D(15) LBM_D(16)
 #undef LBM_D
   // pair sums and differences of the non-equilibrium part
   C ps[9], pd[9];
@@ -552,17 +632,6 @@ __device__ __forceinline__ void block_reduce(double (&v)[NV], const int (&kind)[
 }
 
 // ---------------------------------------------------------------- the step
-
-// Address of the node at (x + dx, y + dy, z + dz) given the tiled-address
-// parts of the thread's wrapped neighbour coordinates.
-struct Nbr {
-  int xs[3];  // x parts of x - 1, x, x + 1 (wrapped)
-  int ys[3];  // y parts of y - 1, y, y + 1 (wrapped)
-  int zs[3];  // plane offsets of z - 1, z, z + 1 (wrapped)
-  __device__ __forceinline__ int at(int dx, int dy, int dz) const {
-    return xs[dx + 1] + ys[dy + 1] + zs[dz + 1];
-  }
-};
 
 // Weight class of direction k: 0 rest, 1 axis, 2 diagonal.
 __device__ __host__ constexpr int wclass(int k) { return k == 0 ? 0 : (k < 7 ? 1 : 2); }
@@ -968,70 +1037,86 @@ __device__ __forceinline__ void finish_node(typename ComputeOf<S>::type (&g)[kQ]
   round_node<S>(g, p, c, out);
 }
 
-// The 19 pulled raw stored values of a node.  SPLIT selects pulls from scalar
-// per-direction bases plus 32-bit lane offsets (state_at); without it every
-// lane forms 64-bit addresses.  The split form needs about 40 more scalar
-// registers; in the kernels with the general wall rules it made the compiler
-// spill scalar registers (5-11% slower at 512^3), and the batch kernel, whose
-// cell base comes from a table, got no scalar-base loads from it and was 1%
-// slower, so only the single-domain SBB / CLI kernels use it.
-template <typename S, bool SPLIT>
-__device__ __forceinline__ void pull_node(const S* __restrict__ src, const StepParams& p, int x,
-                                          int y, int z, typename ComputeOf<S>::type (&g)[kQ]) {
-  using C = typename ComputeOf<S>::type;
-  using St = Storage<S>;
-  const int nx = p.nx, plane = p.t.plane;
-  Nbr n;
-  n.xs[0] = p.t.xpart(x == 0 ? nx - 1 : x - 1);
-  n.xs[1] = p.t.xpart(x);
-  n.xs[2] = p.t.xpart(x == nx - 1 ? 0 : x + 1);
-  n.ys[0] = p.t.ypart(y == 0 ? p.ny - 1 : y - 1);
-  n.ys[1] = p.t.ypart(y);
-  n.ys[2] = p.t.ypart(y == p.ny - 1 ? 0 : y + 1);
-  n.zs[0] = (z == 0 ? p.nz - 1 : z - 1) * plane;
-  n.zs[1] = z * plane;
-  n.zs[2] = (z == p.nz - 1 ? 0 : z + 1) * plane;
-  // direction k arrives from x - e_k
-#pragma unroll
-  for (int k = 0; k < kQ; ++k) {
-    if constexpr (SPLIT)
-      g[k] = (C)St::to_float(*state_at<S>(src, p.t, k, n.zs[1 - kLat.ez[k]],
-                                          n.xs[1 - kLat.ex[k]] + n.ys[1 - kLat.ey[k]]));
-    else
-      g[k] = (C)St::to_float(
-          *state_ptr<S>(src, p.t, k, n.at(-kLat.ex[k], -kLat.ey[k], -kLat.ez[k])));
-  }
+// Flag word of a cell from its class byte: only cells with wall links (or
+// link slots, for solid cells) read the word.
+__device__ __forceinline__ uint32_t flag_word(uint8_t k, const uint32_t* __restrict__ flags, int c) {
+  if (k & kClsLinks) return flags[c];
+  return (k & kClsSolid) ? kSolid : 0u;
 }
 
-// One time step for the node (x, y, z), fluid, with flag word fl, SBB and CLI
-// walls: pull (one lane, one node), then finish_node (edge_x as there).
-template <typename S, int COLL, int WALL, bool SPLIT>
+// The 19 pulled stored values of a node.
+template <typename S, int RUN>
+__device__ __forceinline__ void pull_node(const S* __restrict__ src, const StepParams& p, int x,
+                                          int y, int z, S (&raw)[kQ]) {
+  const int nx = p.nx;
+  const long long plane = p.t.plane;
+  const int xs[3] = {p.t.xpart(x == 0 ? nx - 1 : x - 1), p.t.xpart(x),
+                     p.t.xpart(x == nx - 1 ? 0 : x + 1)};
+  const int ys[3] = {p.t.ypart(y == 0 ? p.ny - 1 : y - 1), p.t.ypart(y),
+                     p.t.ypart(y == p.ny - 1 ? 0 : y + 1)};
+  const PlaneRows<S, RUN, const S> zs[3] = {{src, p.t, (z == 0 ? p.nz - 1 : z - 1) * plane},
+                                            {src, p.t, z * plane},
+                                            {src, p.t, (z == p.nz - 1 ? 0 : z + 1) * plane}};
+  // direction k arrives from x - e_k
+#pragma unroll
+  for (int k = 0; k < kQ; ++k)
+    raw[k] =
+        *zs[1 - kLat.ez[k]].at(k, state_lane<S, RUN>(p.t, xs[1 - kLat.ex[k]] + ys[1 - kLat.ey[k]]));
+}
+template <typename S>
+__device__ __forceinline__ void to_compute(const S (&raw)[kQ],
+                                           typename ComputeOf<S>::type (&g)[kQ]) {
+#pragma unroll
+  for (int k = 0; k < kQ; ++k)
+    g[k] = (typename ComputeOf<S>::type)Storage<S>::to_float(raw[k]);
+}
+
+// One time step for the node (x, y, z), fluid, in-plane address r, address c,
+// class byte cls, SBB and CLI walls: pull (one lane, one node), then
+// finish_node (edge_x as there).
+//
+// A node with wall links also needs its flag word and its own stored values of
+// every moving direction (the wall rules use g_j and g_k at x).  They are
+// requested together, not per link (512^3 sphere pack, FP32 CLI: 2.84 -> 2.56
+// ms per step).  Which nodes need them is known from the class, so within the
+// last-level cache all of it is requested with the pulls, before the first use
+// of any: one memory round trip per node (64^3 in FP32: 8.0 us per step against
+// 8.4 after the flag word); the scheduling barrier keeps the requests together.
+// Beyond the cache (RUN = 0) the flag word comes first and the own values after
+// the pulls, where most of their lines are already on the way (512^3: 2.31
+// against 2.34 ms).
+template <typename S, int RUN, int COLL, int WALL>
 __device__ __forceinline__ void update_node(const S* __restrict__ src, S (&out)[kQ],
-                                            const StepParams& p, int x, int y, int z, int c,
-                                            uint32_t fl, bool edge_x,
+                                            const uint32_t* __restrict__ flags,
+                                            const StepParams& p, int x, int y, int z, int r,
+                                            int c, uint8_t cls, bool edge_x,
                                             typename ComputeOf<S>::type (&mom)[5]) {
   static_assert(WALL != kGEN, "the general rules take update_node_general");
-  typename ComputeOf<S>::type g[kQ];
-  pull_node<S, SPLIT>(src, p, x, y, z, g);
-  // wall links: the pulled raw value is the stored coefficient a (CLI)
-  S own[kQ];
-  if (fl & kLinkMask) {
-    // The node's own stored values of every moving direction (the wall rules
-    // need g_j and g_k at x), all requested before the first use: one memory
-    // round trip per boundary node instead of one per link direction (512^3
-    // sphere pack, FP32 CLI: 2.84 -> 2.56 ms per step).  (64-bit lane
-    // addresses: with scalar bases per direction as for the pulls, the
-    // boundary wavefronts' extra scalar work made the 512^3 sphere-pack step
-    // 3% slower.)
+  constexpr bool kAhead = RUN != 0;
+  S raw[kQ], own[kQ];
+  uint32_t fl = kAhead ? 0u : flag_word(cls, flags, c);
+  pull_node<S, RUN>(src, p, x, y, z, raw);
+  if (kAhead ? (cls & kClsLinks) != 0 : (fl & kLinkMask) != 0) {
+    if constexpr (kAhead) {
+      fl = flags[c];
+      const PlaneRows<S, RUN, const S> zp(src, p.t, (long long)z * p.t.plane);
+      const uint32_t lane = state_lane<S, RUN>(p.t, r);
 #pragma unroll
-    for (int k = 1; k < kQ; ++k) own[k] = *state_ptr<S>(src, p.t, k, c);
+      for (int k = 1; k < kQ; ++k) own[k] = *zp.at(k, lane);
+    } else {
+#pragma unroll
+      for (int k = 1; k < kQ; ++k) own[k] = src[state_slot<S>(p.t, k, c)];
+    }
   }
+  if constexpr (kAhead) __builtin_amdgcn_sched_barrier(0);
+  typename ComputeOf<S>::type g[kQ];
+  to_compute<S>(raw, g);
   finish_node<S, COLL, WALL>(g, own, out, p, x, c, fl, edge_x, mom);
 }
 
 // update_node for the general wall rules.  Every lane of the wavefront calls;
 // fluid says whether the lane's cell is stepped (out and mom are set then).
-template <typename S, int COLL>
+template <typename S, int RUN, int COLL>
 __device__ __forceinline__ void update_node_general(
     const S* __restrict__ src, S (&out)[kQ], const uint32_t* __restrict__ flags,
     const StepParams& p, int x, int y, int z, int c, uint32_t fl, bool fluid, bool edge_x,
@@ -1053,7 +1138,11 @@ __device__ __forceinline__ void update_node_general(
     general_walls<S, C>(src, flags, p, x, y, z, c, links, m1, list);
   }
   C g[kQ];
-  if (fluid) pull_node<S, false>(src, p, x, y, z, g);
+  if (fluid) {
+    S raw[kQ];
+    pull_node<S, RUN>(src, p, x, y, z, raw);
+    to_compute<S>(raw, g);
+  }
   if (walls) take_walls<C>(links, list, g);
   if (fluid) {
     const S own[kQ] = {};
@@ -1069,13 +1158,15 @@ __device__ __forceinline__ void update_node_general(
 // many lines,
 // partly written lines cost far more than their bytes (a batch of 64^3 cells
 // holding spheres of diameter 50 steps 17% faster with mode 1).
-template <typename S>
+template <typename S, int RUN>
 __device__ __forceinline__ void solid_node(const S* __restrict__ src, S (&out)[kQ],
-                                           const Tiling& t, int c, uint32_t fl) {
+                                           const Tiling& t, long long zstart, int r, uint32_t fl) {
+  const PlaneRows<S, RUN, const S> zp(src, t, zstart);
+  const uint32_t lane = state_lane<S, RUN>(t, r);
   out[0] = Storage<S>::from_float(0);
 #pragma unroll
   for (int k = 1; k < kQ; ++k)
-    out[k] = (fl & (1u << k)) ? src[state_slot<S>(t, k, c)] : Storage<S>::from_float(0);
+    out[k] = (fl & (1u << k)) ? *zp.at(k, lane) : Storage<S>::from_float(0);
 }
 
 // Whether this lane stores, given the fluid lanes of its wavefront: fluid
@@ -1107,12 +1198,14 @@ __device__ __forceinline__ void nontemporal_store(S v, S* p) {
     __builtin_nontemporal_store(v, p);
 }
 
-template <typename S, bool NT, bool SPLIT>
+template <typename S, int RUN, bool NT>
 __device__ __forceinline__ void store_node(S* __restrict__ dst, const S (&out)[kQ],
                                            const Tiling& t, long long zstart, int r) {
+  const PlaneRows<S, RUN, S> zp(dst, t, zstart);
+  const uint32_t lane = state_lane<S, RUN>(t, r);
 #pragma unroll
   for (int k = 0; k < kQ; ++k) {
-    S* q = SPLIT ? state_at<S>(dst, t, k, zstart, r) : state_ptr<S>(dst, t, k, (int)zstart + r);
+    S* q = zp.at(k, lane);
     if constexpr (NT)
       nontemporal_store(out[k], q);
     else
@@ -1145,9 +1238,10 @@ struct TileCell {
   bool inside;
 };
 __device__ __forceinline__ TileCell tile_cell(const Tiling& t, int z) {
-  const int tile = blockIdx.x * blockDim.y + threadIdx.y;
+  const int tile =
+      blockIdx.x * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);  // (64 lanes share it)
   const int l = threadIdx.x;
-  const int tx = tile % t.ntx, ty = tile / t.ntx;
+  const int ty = t.tile_row(tile), tx = tile - ty * t.ntx;
   TileCell r;
   r.x = (tx << t.tw_log2) + (l & ((1 << t.tw_log2) - 1));
   r.y = (ty << t.th_log2) + (l >> t.tw_log2);
@@ -1162,9 +1256,10 @@ __device__ __forceinline__ TileCell tile_cell(const Tiling& t, int z) {
 // bh tile rows times the bands times the z planes).  Units past the row end
 // give u >= units per row.
 __device__ __forceinline__ void step_unit(const StepParams& p, int& u, int& ty) {
-  const int j = threadIdx.y;
-  u = blockIdx.x * p.bw + j % p.bw;
-  ty = blockIdx.y * p.bh + j / p.bw;
+  const int j = __builtin_amdgcn_readfirstlane(threadIdx.y);  // (64 lanes share it)
+  const int row = (j * p.by_bw) >> 16;                        // j / bw
+  u = blockIdx.x * p.bw + j - row * p.bw;
+  ty = blockIdx.y * p.bh + row;
 }
 
 // Partial-sum slot of a step workgroup.
@@ -1191,21 +1286,15 @@ __device__ __forceinline__ TileCell step_tile_cell(const StepParams& p, int z) {
   return r;
 }
 
-// Flag word of a cell from its class byte: only cells with wall links (or
-// link slots, for solid cells) read the word.
-__device__ __forceinline__ uint32_t flag_word(uint8_t k, const uint32_t* __restrict__ flags, int c) {
-  if (k & kClsLinks) return flags[c];
-  return (k & kClsSolid) ? kSolid : 0u;
-}
-
 // The fused stream-and-collide step over the box.  A block of blockDim.y
 // wavefronts covers that many consecutive tiles of one z plane; with 16 x 4
 // tiles and 8 wavefronts it spans 128 x 4 cells, so most of the lines that
 // the +-1 shifted pulls share with neighbouring tiles are read by the same
 // workgroup.  With RED the block also writes FP64 partial sums of the state
-// it produced (u, drho, max |u|^2, non-finite count) to partials[block].  NT
-// selects non-temporal stores (the new state is not read again in the step).
-template <typename S, int COLL, int WALL, bool RED, bool NT>
+// it produced (u, drho, max |u|^2, non-finite count) to partials[block].  MEM
+// says where the two states live: kStreaming selects non-temporal stores (the
+// new state is not read again in the step), and see PlaneRows.
+template <typename S, int COLL, int WALL, bool RED, int MEM>
 __global__ __launch_bounds__(kStepThreads) void step_kernel(const S* __restrict__ src,
                                                             S* __restrict__ dst,
                                                             const uint8_t* __restrict__ cls,
@@ -1213,7 +1302,7 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(const S* __restrict_
                                                             const StepParams p,
                                                             double* __restrict__ partials) {
   using C = typename ComputeOf<S>::type;
-  constexpr bool kSplit = WALL != kGEN;  // (pull_node)
+  constexpr int RUN = MEM != kCached && sizeof(S) > 2 && WALL != kGEN ? 0 : kStepRunLog2;
   const int z = blockIdx.z;
   const TileCell tc = step_tile_cell(p, z);
   const uint8_t k = tc.inside ? cls[tc.c] : kClsSolid;
@@ -1226,16 +1315,16 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(const S* __restrict_
     extern __shared__ __attribute__((aligned(16))) unsigned char wall_lds[];
     if (__ballot(fluid) != 0) {
       const uint32_t fl = fluid ? flag_word(k, flags, tc.c) : 0u;
-      update_node_general<S, COLL>(src, out, flags, p, tc.x, tc.y, z, tc.c, fl, fluid, edge_x,
+      update_node_general<S, RUN, COLL>(src, out, flags, p, tc.x, tc.y, z, tc.c, fl, fluid, edge_x,
                                    mom, reinterpret_cast<C*>(wall_lds) + threadIdx.y * kQ * 64);
     }
   } else {
     if (fluid)
-      update_node<S, COLL, WALL, kSplit>(src, out, p, tc.x, tc.y, z, tc.c,
-                                         flag_word(k, flags, tc.c), edge_x, mom);
+      update_node<S, RUN, COLL, WALL>(src, out, flags, p, tc.x, tc.y, z, tc.r, tc.c, k, edge_x,
+                                      mom);
   }
   if (fluid) {
-    store_node<S, NT, kSplit>(dst, out, p.t, (long long)z * p.t.plane, tc.r);
+    store_node<S, RUN, MEM == kStreaming>(dst, out, p.t, (long long)z * p.t.plane, tc.r);
     if constexpr (WALL == kGEN) store_side<C>(p, k, tc.c, mom);
     if constexpr (RED) {
       const double rho = mom[0], ux = mom[1], uy = mom[2], uz = mom[3];
@@ -1514,14 +1603,29 @@ __global__ __launch_bounds__(kStepThreads) void step_pair_kernel(const S* __rest
 // blocks ran.  p.solid_writes selects which solid cells also store
 // (solid_stores, solid_node).
 
-template <typename S, int COLL, int WALL, bool RED, bool NT>
-__global__ __launch_bounds__(kBatchThreads) void batch_step_kernel(
+//
+// Bound by memory and, for small cells, by latency.  MEM and the two address
+// forms are the single-domain step's; the wavefronts per SIMD are limited to
+// what steps fastest (the registers would allow 5 to 8: more wavefronts spread
+// the reads over more lines than the caches keep).  Against 64-bit lane
+// addresses throughout, us per step: 200 cells of 16^3 in FP32 57.2 -> 46.7, 60
+// of 32^3 73.4 -> 64.0 (70.9 with RUN = 0), 10 of 32^3 in FP64 22.6 -> 20.8,
+// 100 of 16^3 with MR 50 -> 40; without the limits 12 cells of 64^3 in FP64 195
+// -> 199 and 40 of 40^3 with MR 170 -> 176.
+constexpr int batch_waves(bool fp64, int wall, int mem) {
+  if (wall == kGEN) return mem == kCached ? 8 : 4;
+  return fp64 ? 4 : (mem == kCached ? 6 : 8);
+}
+template <typename S, int COLL, int WALL, bool RED, int MEM>
+__global__ __launch_bounds__(kBatchThreads)
+__attribute__((amdgpu_waves_per_eu(4, batch_waves(sizeof(S) == 8, WALL, MEM)))) void batch_step_kernel(
     const S* __restrict__ src, S* __restrict__ dst, const uint8_t* __restrict__ cls,
     const uint32_t* __restrict__ flags, const StepParams* __restrict__ cells,
     const int* __restrict__ active, const int* __restrict__ list,
     const int* __restrict__ n_list, int nz_cell, long long cell_size, int zper,
     double* __restrict__ partials) {
   using C = typename ComputeOf<S>::type;
+  constexpr int RUN = MEM == kCached || WALL == kGEN ? kBatchRunLog2 : 0;  // (PlaneRows)
   const int zblocks = nz_cell / zper;
   const int slot = blockIdx.z / zblocks;
   const int zb = blockIdx.z - slot * zblocks;  // z block within the cell
@@ -1543,7 +1647,6 @@ __global__ __launch_bounds__(kBatchThreads) void batch_step_kernel(
     const int c = tc.c;
     const uint8_t k = tc.inside ? cl[c] : kClsSolid;
     const bool solid = k & kClsSolid;
-    const uint32_t fl = tc.inside ? flag_word(k, f, c) : kSolid;
     const unsigned long long fluid = __ballot(!solid);
     const bool edge_x = __ballot(tc.x == 0 || tc.x == p.nx - 1) != 0;
     const bool stores = solid_stores<S>(p.solid_writes, solid, fluid);
@@ -1551,18 +1654,22 @@ __global__ __launch_bounds__(kBatchThreads) void batch_step_kernel(
     C mom[5];
     if constexpr (WALL == kGEN) {
       extern __shared__ __attribute__((aligned(16))) unsigned char wall_lds[];
+      const uint32_t fl = solid ? kSolid : flag_word(k, f, c);
       if (fluid != 0)
-        update_node_general<S, COLL>(s, out, f, p, tc.x, tc.y, z, c, fl, !solid, edge_x, mom,
+        update_node_general<S, RUN, COLL>(s, out, f, p, tc.x, tc.y, z, c, fl, !solid, edge_x, mom,
                                      reinterpret_cast<C*>(wall_lds) + threadIdx.y * kQ * 64);
     }
     if (!stores) continue;
     if (solid) {
-      solid_node<S>(s, out, p.t, c, fl);
+      const uint32_t fl = tc.inside ? flag_word(k, f, c) : kSolid;
+      solid_node<S, RUN>(s, out, p.t, (long long)z * p.t.plane, tc.r, fl);
     } else {
       if constexpr (WALL != kGEN)
-        update_node<S, COLL, WALL, false>(s, out, p, tc.x, tc.y, z, c, fl, edge_x, mom);
+        update_node<S, RUN, COLL, WALL>(s, out, f, p, tc.x, tc.y, z, tc.r, c, k, edge_x,
+                                                  mom);
     }
-    if (tc.inside) store_node<S, NT, false>(d, out, p.t, (long long)z * p.t.plane, tc.r);
+    if (tc.inside)
+      store_node<S, RUN, MEM == kStreaming>(d, out, p.t, (long long)z * p.t.plane, tc.r);
     if (solid) continue;
     if constexpr (RED) {
       const double rho = mom[0], ux = mom[1], uy = mom[2], uz = mom[3];
@@ -1927,10 +2034,9 @@ __global__ void init_eq_kernel(S* __restrict__ buf, const uint32_t* __restrict__
           uz = (C)stage[3 * n + i];
   const C usq = ux * ux + uy * uy + uz * uz;
   C g[kQ];
-#define LBM_EQ(K) g[K] = geq<C, K>(rho, ux, uy, uz, usq);
-  LBM_EQ(0) LBM_EQ(1) LBM_EQ(2) LBM_EQ(3) LBM_EQ(4) LBM_EQ(5) LBM_EQ(6) LBM_EQ(7) LBM_EQ(8)
-  LBM_EQ(9) LBM_EQ(10) LBM_EQ(11) LBM_EQ(12) LBM_EQ(13) LBM_EQ(14) LBM_EQ(15) LBM_EQ(16)
-  LBM_EQ(17) LBM_EQ(18)
+  g[0] = geq_rest<C>(rho, usq);
+#define LBM_EQ(K) geq_pair<C, K>(rho, ux, uy, uz, usq, g[K], g[kLat.opp[K]]);
+  LBM_EQ(1) LBM_EQ(3) LBM_EQ(5) LBM_EQ(7) LBM_EQ(8) LBM_EQ(11) LBM_EQ(12) LBM_EQ(15) LBM_EQ(16)
 #undef LBM_EQ
 #pragma unroll
   for (int k = 0; k < kQ; ++k) buf[state_slot<S>(t, k, c)] = g_to_stored<S>((double)g[k], k, sigma);

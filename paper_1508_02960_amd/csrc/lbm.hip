@@ -36,6 +36,7 @@ struct lbm_domain_s {
   int waves = 16;        // wavefronts per step workgroup
   int rows = 1;          // tile rows per step workgroup (waves / rows units across)
   bool streaming = false;  // non-temporal stores in the step kernels
+  int mem = 0;             // kCached, kBeyondCache or kStreaming (= streaming)
   bool pairs = false;      // 16-bit storage: two cells per lane (step_pair_kernel)
   double nu = 0, omega_p = 0, omega_m = 0, s_e = 0, s_zeta = 0;
   double sigma = 1.0;    // 16-bit storage scale (h = sigma g / w), a power of two
@@ -148,6 +149,7 @@ Tiling make_tiling(int nx, int ny, int tw_log2, int tile_log2) {
   t.ntx = (nx + (1 << t.tw_log2) - 1) >> t.tw_log2;
   t.nty = (ny + (1 << t.th_log2) - 1) >> t.th_log2;
   t.plane = (t.ntx * t.nty) << tile_log2;
+  t.by_ntx = t.ntx > 1 ? (unsigned)(((1ULL << 32) + t.ntx - 1) / t.ntx) : 0;
   return t;
 }
 
@@ -172,6 +174,12 @@ dim3 step_grid(lbm_domain d) {
 // 256 MB last-level cache (measured: 15% faster at 256^3 FP32, 2.5 GB;
 // 1.6% slower at 128^3, 0.32 GB, where much of the state stays cached).
 constexpr size_t kStreamingBytes = size_t(1) << 30;
+// The step within the cache pays off for small states (64^3 in FP32, 40 MB: 3%
+// faster; 96^3, 134 MB: even; 80^3 in FP64, 156 MB: 1% slower).
+constexpr size_t kCacheBytes = size_t(128) << 20;
+// Batches (60 cells of 32^3 in FP32, 0.3 GB: 10% faster; in FP64, 0.6 GB: even;
+// 40 cells of 40^3 with MR, 0.4 GB: 3% slower).
+constexpr size_t kBatchCacheBytes = size_t(320) << 20;
 
 // IEBB on one domain keeps the velocity of the cells next to its wall links
 // in a side buffer per state (StepParams::side_in / side_out); batches sum
@@ -182,7 +190,11 @@ void layout(lbm_domain d) {
   d->elem = storage_bytes(d->p.storage);
   // large states: compact tiles and streaming stores (sizes estimated on the
   // unpadded cell count; padding adds at most a few percent)
-  d->streaming = 2 * (size_t)kQ * (size_t)d->geo.ncell * d->elem > kStreamingBytes;
+  const size_t bytes = 2 * (size_t)kQ * (size_t)d->geo.ncell * d->elem;
+  d->streaming = bytes > kStreamingBytes;
+  d->mem = d->streaming                                              ? kStreaming
+           : bytes > (d->batch ? kBatchCacheBytes : kCacheBytes) ? kBeyondCache
+                                                                    : kCached;
   // compact tiles 16 x 4; the 16-bit formats' tiles are 32 cells wide (a
   // 16-lane DPP row of the two-cell lanes is then one tile row).  Batches
   // take 8 x 8: a 128-byte line is then an 8 x 4 patch, which the walls of
@@ -344,6 +356,7 @@ StepParams step_params(lbm_domain d) {
   sp.side_out = d->side[1 - d->cur];
   sp.bw = std::max(1, d->waves / std::max(1, d->rows));
   sp.bh = std::max(1, d->rows);
+  sp.by_bw = (65536 + sp.bw - 1) / sp.bw;
   sp.nbx = d->batch ? 1 : step_nbx(d);
   sp.seed = hash32((uint32_t)d->step_count ^ hash32((uint32_t)(d->step_count >> 32) + 0x5bd1e995u));
   return sp;
@@ -361,7 +374,7 @@ size_t walls_lds(lbm_domain d, int waves) {
 const void* step_function(lbm_domain d, bool red) {
   return with_storage(d->p.storage, [&](auto tag) -> const void* {
     using S = decltype(tag);
-    return step_kernel_entry<S>(red, d->streaming, d->pairs, d->p.collision,
+    return step_kernel_entry<S>(red, d->mem, d->pairs, d->p.collision,
                                 wall_template(d->p.wall));
   });
 }
@@ -472,8 +485,8 @@ dim3 batch_grid(lbm_domain d, int slots = -1) {
 const void* batch_function(lbm_domain d, bool red) {
   const int wt = wall_template(d->p.wall);
   if (d->p.storage == LBM_FP64)
-    return batch_kernel_entry<double>(red, d->streaming, d->p.collision, wt);
-  return batch_kernel_entry<float>(red, d->streaming, d->p.collision, wt);
+    return batch_kernel_entry<double>(red, d->mem, d->p.collision, wt);
+  return batch_kernel_entry<float>(red, d->mem, d->p.collision, wt);
 }
 
 // Kernel-node or launch arguments of one batch step from buffer `from`.

@@ -5,6 +5,6 @@
 #include "step_impl.hpp"
 
 namespace lbm {
-template const void* step_kernel_entry<bf16s_t>(bool, bool, bool, int, int);
-template const void* step_kernel_entry<bf16_t>(bool, bool, bool, int, int);
+template const void* step_kernel_entry<bf16s_t>(bool, int, bool, int, int);
+template const void* step_kernel_entry<bf16_t>(bool, int, bool, int, int);
 }  // namespace lbm

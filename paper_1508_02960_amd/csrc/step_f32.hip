@@ -5,6 +5,6 @@
 #include "step_impl.hpp"
 
 namespace lbm {
-template const void* step_kernel_entry<float>(bool, bool, bool, int, int);
-template const void* batch_kernel_entry<float>(bool, bool, int, int);
+template const void* step_kernel_entry<float>(bool, int, bool, int, int);
+template const void* batch_kernel_entry<float>(bool, int, int, int);
 }  // namespace lbm

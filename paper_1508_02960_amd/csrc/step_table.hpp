@@ -16,12 +16,13 @@ constexpr bool kUnscaledStorage = std::is_same_v<S, float> || std::is_same_v<S, 
 
 // Single-domain step (step_kernel, or step_pair_kernel with pairs) for the
 // collision operator (kSRT, kTRT, kMRT) and wall template (kSBB, kCLI,
-// kGEN); red adds the block partial sums, nt stores non-temporally.
+// kGEN); red adds the block partial sums, mem says where the states live
+// (kCached, kBeyondCache, kStreaming).
 template <typename S>
-const void* step_kernel_entry(bool red, bool nt, bool pairs, int collision, int wall_tmpl);
+const void* step_kernel_entry(bool red, int mem, bool pairs, int collision, int wall_tmpl);
 
 // Batch step (batch_step_kernel), FP32 and FP64 storage.
 template <typename S>
-const void* batch_kernel_entry(bool red, bool nt, int collision, int wall_tmpl);
+const void* batch_kernel_entry(bool red, int mem, int collision, int wall_tmpl);
 
 }  // namespace lbm

@@ -532,3 +532,48 @@ def test_device_fields_match_host(storage):
     with pytest.raises(lbm.LbmError):
         c.init_equilibrium_device(f)
     c.close()
+
+
+# copies of a 12 x 20 x 50 box along z and y: just beyond the size up to which
+# the step takes its form for states within the cache, and just beyond that of
+# the streaming form
+@pytest.mark.parametrize("storage,nz,ny", [("fp32", 8, 10), ("fp32", 20, 30), ("fp64", 5, 8),
+                                           ("fp64", 15, 20)])
+@pytest.mark.parametrize("wall,collision", [("cli", "trt"), ("sbb", "mrt"), ("mr", "trt")])
+def test_step_forms_by_state_size_give_the_same_bits(storage, nz, ny, wall, collision):
+    """The box and its periodic copies (sphere centres and radii in quarters, so
+    that the wall distances are exact in every copy) after six steps."""
+    import torch
+
+    base = (12, 20, 50)
+    spheres = np.array([[10.25, 5.5, 3.75, 4.25], [30.5, 12.25, 8.0, 5.25], [44.0, 18.5, 5.5, 3.5]])
+    kw = dict(tau=0.7, delta_rho=1e-3, storage=storage, wall=wall, collision=collision)
+    fields = []
+    for cz, cy in ((1, 1), (nz, ny)):
+        sp = np.concatenate([spheres + [0.0, 20.0 * j, 12.0 * i, 0.0]
+                             for i in range(cz) for j in range(cy)])
+        d = lbm.Domain((12 * cz, 20 * cy, 50), spheres=sp, **kw)
+        d.step(6)
+        f = d.macroscopic_device().clone().reshape(4, cz, 12, cy, 20, 50)
+        fields.append(f.permute(1, 3, 0, 2, 4, 5).reshape(cz * cy, 4, *base))
+        d.close()
+    assert float(fields[0].abs().max()) > 0
+    assert torch.equal(fields[1], fields[0].expand_as(fields[1]))
+
+
+@pytest.mark.parametrize("storage,n", [("fp32", 560), ("fp64", 300)])
+@pytest.mark.parametrize("wall,collision", [("cli", "mrt"), ("libb", "trt"), ("iebb", "srt")])
+def test_batch_forms_by_state_size_give_the_same_bits(storage, n, wall, collision):
+    """Equal cells of 16^3, two of them (within the cache) and n (just beyond
+    the size of the batch's form within the cache)."""
+    cell = dict(spheres=np.array([[7.25, 8.5, 7.75, 5.5]]), tau=0.7, delta_rho=1e-3)
+    fields = []
+    for m in (2, n):
+        b = lbm.Batch((16, 16, 16), [cell] * m, storage=storage, wall=wall, collision=collision)
+        b.step(6)
+        drho, u = b.macroscopic()
+        fields.append((np.asarray(drho).reshape(m, -1), np.asarray(u)))
+        b.close()
+    (r2, u2), (rn, un) = fields
+    assert np.max(np.abs(r2)) > 0 and np.array_equal(rn, np.broadcast_to(r2[0], rn.shape))
+    assert np.array_equal(un, np.broadcast_to(u2[:, :1], un.shape))
