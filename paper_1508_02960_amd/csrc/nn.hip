@@ -279,9 +279,10 @@ __device__ __forceinline__ void load_to_lds(const void* g, void* lds) {
 
 // Consecutive workgroups go to the eight XCDs in turn; work item of block b of
 // n so that each XCD takes a contiguous range of items (neighbouring tiles
-// share halo lines in its L2).
+// share halo lines in its L2; the first n % 8 XCDs take one item more).
 __device__ __forceinline__ int xcd_item(int b, int n) {
-  return n % 8 ? b : (b % 8) * (n / 8) + b / 8;
+  const int x = b % 8, r = n % 8;
+  return x * (n / 8) + (x < r ? x : r) + b / 8;
 }
 
 template <int TX, int MT, int NT, int WC, bool PK, bool ACT>
@@ -1869,9 +1870,13 @@ void launch_rows(const uint16_t* x, const uint16_t* w, const float* bias, void* 
 // boxes beyond that.  False where gathered tiles are the better kernel: the
 // halo does not fit in LDS; or more than 32 channels in boxes of more blocks,
 // for unpacked weights, whose scattered rows then bound the launch (20^3 x 3,
-// 64 -> 128: 47 against 42 us), and for packed ones where only two rows fit
-// (20^3 x 4, 384 -> 128: 204 against 194 us; with up to 256 channels packed
-// weights win, 20^3 x 3, 64 -> 128: 30 against 42 us).
+// 64 -> 128: 47 against 42 us), and for packed ones in boxes of several rounds
+// of blocks (with one block's halo in LDS a CU waits for the next): more than
+// 512 blocks where only two rows fit (20^3 x 4, 384 -> 128: 204 against 194 us)
+// or the box's edges leave the tiles half empty (11 x 13 x 9 x 4, 128 -> 384: 80
+// against 63 us), more than 800 from 128 channels on (20^3 x 3, 128 -> 256: 129
+// against 90; 672 blocks of 14 x 15 x 15 x 4, 128 -> 384: 86 against 94).  Below
+// 128 channels packed weights win (20^3 x 3, 64 -> 128: 30 against 41 us).
 template <int NT, int WC, bool PK, bool ACT>
 bool launch_rows_of(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                     const Shape& s, int ci, int co, int relu, hipStream_t st) {
@@ -1885,7 +1890,11 @@ bool launch_rows_of(const uint16_t* x, const uint16_t* w, const float* bias, voi
   const long long blocks = mt == 1   ? rows_blocks<1, WC>(s, cgs)
                            : mt == 2 ? rows_blocks<2, WC>(s, cgs)
                                      : rows_blocks<4, WC>(s, cgs);
-  if (PK ? ci > 256 && blocks > 512 : ci >= 32 && blocks > 256) return false;
+  const long long tile = (4 / WC) * 2 * mt * kRX;  // voxels of a block
+  const bool sparse = blocks / cgs * tile * 2 > 3 * s.m;
+  if (PK ? (ci >= 128 && blocks > 800) || ((ci > 256 || (ci >= 128 && sparse)) && blocks > 512)
+         : ci >= 32 && blocks > 256)
+    return false;
   if (mt == 1)
     launch_rows<1, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   else if (mt == 2)

@@ -114,7 +114,9 @@ FORWARD_TILES = [((2, 32, 64, 64), 32, 32), ((1, 32, 32, 32), 64, 64), ((1, 16, 
                  ((1, 32, 40, 40), 32, 33), ((1, 16, 32, 32), 32, 32), ((1, 32, 32, 24), 8, 32),
                  ((2, 40, 40, 40), 8, 32), ((2, 9, 7, 5), 16, 24), ((1, 3, 2, 1), 8, 8),
                  ((1, 11, 13, 10), 40, 13), ((1, 4, 6, 8), 64, 136), ((1, 4, 4, 8), 704, 16),
-                 ((2, 36, 36, 30), 32, 32), ((2, 32, 32, 64), 32, 96)]
+                 ((2, 36, 36, 30), 32, 32), ((2, 32, 32, 64), 32, 96),
+                 # from packed weights: half-empty tiles, and many blocks
+                 ((4, 11, 13, 9), 128, 384), ((3, 20, 20, 20), 128, 160)]
 
 
 @pytest.mark.parametrize("shape,ci,co", FORWARD_TILES)
