@@ -100,7 +100,7 @@ struct Tiling {
 
 // FP32 and FP64 states are cut into runs of 2^7 addresses for one domain and
 // of 2^6 for batches (every batch cell then starts on a run); every z plane
-// starts on a run (state_base).
+// starts on a run (PlaneRows).
 constexpr int kStepRunLog2 = 7, kBatchRunLog2 = 6;
 
 // Tiling::slot for a kernel's storage type, with the layout fixed at compile
