@@ -568,3 +568,23 @@ def test_updates_and_packings_of_many_tensors_give_the_same_bits(ctx, sizes):
             pairs.append((a, b, w))
     assert lib.nn_conv3d_pack_weights_many(*W._items(W._PackItem, items), s) == 0
     assert all(t.equal(a.view(t.int16), b.view(t.int16)) for a, b, _ in pairs)
+
+
+@pytest.mark.parametrize("m", [1, 300, 4097, 131072])
+@pytest.mark.parametrize("c", [4, 33, 64])
+def test_bias_gradient_folds_every_split(ctx, m, c):
+    """One split to 512, channel counts around a block's 32.  Positive terms, so
+    a chain of at most 64 + 64 + 512 additions rounds by less than 640 2^-24 of
+    the sum."""
+    import ctypes as C
+
+    rng = np.random.default_rng(m + c)
+    dy = _f_dev(ctx, rng.uniform(0.5, 1.0, (m, c)))
+    lib = W._nn()
+    bb = C.c_size_t()
+    assert lib.nn_bias_grad_workspace(m, c, C.byref(bb)) == 0
+    ws = ctx.torch.full((bb.value,), 255, dtype=ctx.torch.uint8, device=ctx.dev)
+    db = ctx.f32(c)
+    assert lib.nn_bias_grad(W._p(dy), W._p(db), W._p(ws), bb.value, m, c, ctx.stream) == 0
+    want = _host(dy).sum(axis=0)
+    assert np.max(np.abs(_host(db) - want) / want) < 640 * 2.0**-24
