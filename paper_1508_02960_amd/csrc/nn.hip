@@ -1117,7 +1117,8 @@ __global__ __launch_bounds__(256) void conv_bwdw_kernel(const uint16_t* __restri
 
 // dw[i] = the splits' partials of i, added in order.  A thread's adds are a
 // serial chain, but their loads are not: kFold of them are in flight (64^3 x 4
-// training step, all sixteen folds: 121 us, 188 with eight at a time).
+// training step, weight and bias folds together: 121 us, 188 with eight at a
+// time; the bias folds have a kernel of their own since).
 constexpr int kFold = 32;
 __global__ __launch_bounds__(256) void fold_splits_kernel(const float* __restrict__ part,
                                                           float* __restrict__ dw, long long n,
