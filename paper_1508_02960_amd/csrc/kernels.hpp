@@ -55,16 +55,23 @@ struct Tiling {
   int nx, ny;            // box edge in x and y (cells)
   int tw_log2, th_log2;  // tile width and height, log2 (sum 6 or 7: tiles of 64 or 128 cells)
   int ntx;               // tiles per tile row (padded nx / tile width)
-  unsigned by_ntx;       // ceil(2^32 / ntx), 0 for one tile: tile / ntx is __umulhi (see tile_row)
+  unsigned by_ntx;       // reciprocal(ntx): ceil(2^32 / ntx), 0 for one tile (tile_row)
   int nty;               // tile rows per plane
   int plane;             // cells per z plane including padding: ntx * nty * tile cells
   int run_log2;          // state buffers: runs of 2^run_log2 consecutive addresses,
   long long run_pitch;   // ... each direction of a run run_pitch elements after the last
   __host__ __device__ int tile_log2() const { return tw_log2 + th_log2; }
-  // tile / ntx without a division (exact: tile ntx < 2^32, as tiles of 64 cells
-  // fill a plane of fewer than 2^31)
-  __device__ int tile_row(int tile) const {
-    return by_ntx ? (int)__umulhi((unsigned)tile, by_ntx) : tile;
+  static unsigned reciprocal(int ntx) {
+    return ntx > 1 ? (unsigned)(((1ULL << 32) + ntx - 1) / ntx) : 0;
+  }
+  // tile / ntx without a division, for tiles and ntx below 2^31.  by_ntx is
+  // (2^32 + e) / ntx with 0 <= e < ntx, so the product exceeds tile / ntx by less
+  // than tile / 2^32 < 1/2 and its whole part is the quotient or one more; one
+  // more happens from tile ntx >= 2^32 on (long boxes: 65537 tiles in a row).
+  __host__ __device__ int tile_row(int tile) const {
+    if (!by_ntx) return tile;
+    const unsigned q = (unsigned)(((unsigned long long)(unsigned)tile * by_ntx) >> 32);
+    return (int)(q * (unsigned)ntx > (unsigned)tile ? q - 1 : q);
   }
   __host__ __device__ int xpart(int x) const {
     return ((x >> tw_log2) << tile_log2()) | (x & ((1 << tw_log2) - 1));

@@ -149,7 +149,7 @@ Tiling make_tiling(int nx, int ny, int tw_log2, int tile_log2) {
   t.ntx = (nx + (1 << t.tw_log2) - 1) >> t.tw_log2;
   t.nty = (ny + (1 << t.th_log2) - 1) >> t.th_log2;
   t.plane = (t.ntx * t.nty) << tile_log2;
-  t.by_ntx = t.ntx > 1 ? (unsigned)(((1ULL << 32) + t.ntx - 1) / t.ntx) : 0;
+  t.by_ntx = Tiling::reciprocal(t.ntx);
   return t;
 }
 
