@@ -144,7 +144,12 @@ class _Ctx:
 class Conv:
     """3x3x3 periodic convolution ci -> co with bias; FP32 master weights,
     BF16 copies (as they are, and packed for the forward and the
-    backward-data convolution), Adam moments."""
+    backward-data convolution), Adam moments.
+
+    wb and wt are the BF16 weights and their flipped form of the backward-data
+    convolution.  A caller who asks for either may write it at any time, so
+    from then on this layer's convolutions read these tensors themselves and
+    no packed copy of them (the same bits, at the unpacked kernels' speed)."""
 
     def __init__(self, ctx: _Ctx, ci: int, co: int, rng: np.random.Generator):
         self.ctx, self.ci, self.co = ctx, ci, co
@@ -153,7 +158,7 @@ class Conv:
         t = ctx.torch
         self.w = t.from_numpy(w).to(ctx.dev)
         self.b = ctx.zeros(co)
-        self.wb = ctx.bf(co, 27, ci)
+        self._wb, self._wt = ctx.bf(co, 27, ci), None
         self.wp, self.wtp = self._packed(ci, co), self._packed(co, ci)
         self.gw = ctx.zeros(co, 27, ci)
         self.gb = ctx.zeros(co)
@@ -173,38 +178,79 @@ class Conv:
         _chk(_nn().nn_conv3d_packed_bytes(ci, co, C.byref(nb)), "packed bytes")
         return self.ctx.bf(int(nb.value) // 2)
 
-    def _pack(self):
-        for buf, flip in ((self.wp, 0), (self.wtp, 1)):
-            if buf is not None:
-                _chk(_nn().nn_conv3d_pack_weights(_p(self.wb), _p(buf), self.ci, self.co, flip,
-                                                  self.ctx.stream), "pack")
+    def _packs(self):
+        """Arguments (w, packed, ci, co, flip) of the packings of wb."""
+        if self._wt is not None:
+            return []
+        return [(self._wb.data_ptr(), buf.data_ptr(), self.ci, self.co, flip)
+                for buf, flip in ((self.wp, 0), (self.wtp, 1)) if buf is not None]
+
+    def _flip(self):
+        _chk(_nn().nn_conv3d_flip_weights(_p(self._wb), _p(self._wt), self.ci, self.co,
+                                          self.ctx.stream), "flip")
+
+    def _hand_out(self):
+        if self._wt is None:
+            self._wt = self.ctx.bf(self.ci, 27, self.co)
+            self._flip()
+
+    @property
+    def wb(self):
+        """The BF16 weights wb[co][tap][ci], which the forward convolution reads."""
+        self._hand_out()
+        return self._wb
+
+    @wb.setter
+    def wb(self, t):
+        self._hand_out()
+        self._wb = t
 
     @property
     def wt(self):
-        """The flipped weights wt[ci][tap][co] of the backward-data convolution."""
-        wt = self.ctx.bf(self.ci, 27, self.co)
-        _chk(_nn().nn_conv3d_flip_weights(_p(self.wb), _p(wt), self.ci, self.co,
-                                          self.ctx.stream), "flip")
-        return wt
+        """The flipped weights wt[ci][tap][co], which the backward-data convolution
+        reads: those of wb at the last refresh or optimizer step."""
+        self._hand_out()
+        return self._wt
+
+    @wt.setter
+    def wt(self, t):
+        self._hand_out()
+        self._wt = t
 
     def refresh(self):
-        _chk(_nn().nn_cast_bf16(_p(self.w), _p(self.wb), self.w.numel(), self.ctx.stream), "cast")
-        self._pack()
+        lib = _nn()
+        _chk(lib.nn_cast_bf16(_p(self.w), _p(self._wb), self.w.numel(), self.ctx.stream), "cast")
+        if self._wt is not None:
+            self._flip()
+        for args in self._packs():
+            _chk(lib.nn_conv3d_pack_weights(*args, self.ctx.stream), "pack")
 
     def forward(self, x_bf, shape):
         n, d, h, w = shape
         y = self.ctx.f32(n, d, h, w, self.co)
-        _chk(_nn().nn_conv3d_forward_packed(_p(x_bf), _p(self.wp), _p(self.b), _p(y), 0, n, d, h, w,
-                                            self.ci, self.co, self.ctx.stream), "conv forward")
+        args = (n, d, h, w, self.ci, self.co)
+        if self._wt is not None:
+            st = _nn().nn_conv3d_forward(_p(x_bf), _p(self._wb), _p(self.b), _p(y), *args,
+                                         self.ctx.stream)
+        else:
+            st = _nn().nn_conv3d_forward_packed(_p(x_bf), _p(self.wp), _p(self.b), _p(y), 0, *args,
+                                                self.ctx.stream)
+        _chk(st, "conv forward")
         return y
 
     def forward_act(self, x_bf, shape, relu=True):
         """bf16(relu(conv(x))): the convolution and the activation in one kernel."""
         n, d, h, w = shape
         a = self.ctx.bf(n, d, h, w, self.co)
-        _chk(_nn().nn_conv3d_forward_packed(_p(x_bf), _p(self.wp), _p(self.b), _p(a),
-                                            2 if relu else 1, n, d, h, w, self.ci, self.co,
-                                            self.ctx.stream), "conv forward + activation")
+        args = (n, d, h, w, self.ci, self.co)
+        relu = 1 if relu else 0
+        if self._wt is not None:
+            st = _nn().nn_conv3d_forward_act(_p(x_bf), _p(self._wb), _p(self.b), _p(a), *args, relu,
+                                             self.ctx.stream)
+        else:
+            st = _nn().nn_conv3d_forward_packed(_p(x_bf), _p(self.wp), _p(self.b), _p(a), 1 + relu,
+                                                *args, self.ctx.stream)
+        _chk(st, "conv forward + activation")
         return a
 
     def backward(self, x_bf, dy32, shape, need_dx=True, act=None, skip=None):
@@ -243,8 +289,13 @@ class Conv:
         if not need_dx:
             return None
         dx = self.ctx.f32(n, d, h, w, self.ci)
-        _chk(lib.nn_conv3d_forward_packed(_p(dy), _p(self.wtp), None, _p(dx), 0, n, d, h, w, self.co,
-                                          self.ci, self.ctx.stream), "conv backward data")
+        if self._wt is not None:
+            st = lib.nn_conv3d_backward_data(_p(dy), _p(self._wt), _p(dx), n, d, h, w, self.ci,
+                                             self.co, self.ctx.stream)
+        else:
+            st = lib.nn_conv3d_forward_packed(_p(dy), _p(self.wtp), None, _p(dx), 0, n, d, h, w,
+                                              self.co, self.ci, self.ctx.stream)
+        _chk(st, "conv backward data")
         return dx
 
     def adam(self, lr, step, b1=0.9, b2=0.999, eps=1e-8):
@@ -253,18 +304,21 @@ class Conv:
 
 def _adam(layers, lr, step, b1=0.9, b2=0.999, eps=1e-8):
     """One optimizer step of the layers: master weights, BF16 weights and their
-    packed forms, in one launch each."""
+    packed forms, in one launch each (and the flipped weights of layers that
+    handed theirs out)."""
     lib, ctx = _nn(), layers[0].ctx
     tensors, packs = [], []
     for l in layers:
         tensors += [(l.w.data_ptr(), l.gw.data_ptr(), l.mw.data_ptr(), l.vw.data_ptr(),
-                     l.wb.data_ptr(), l.w.numel()),
+                     l._wb.data_ptr(), l.w.numel()),
                     (l.b.data_ptr(), l.gb.data_ptr(), l.mb.data_ptr(), l.vb.data_ptr(), None, l.co)]
-        packs += [(l.wb.data_ptr(), p.data_ptr(), l.ci, l.co, flip)
-                  for p, flip in ((l.wp, 0), (l.wtp, 1)) if p is not None]
+        packs += l._packs()
     _chk(lib.nn_adam_many(*_items(_AdamTensor, tensors), lr, b1, b2, eps, step, ctx.stream), "adam")
     if packs:
         _chk(lib.nn_conv3d_pack_weights_many(*_items(_PackItem, packs), ctx.stream), "pack")
+    for l in layers:
+        if l._wt is not None:
+            l._flip()
 
 
 class UNet:

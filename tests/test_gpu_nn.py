@@ -588,3 +588,47 @@ def test_bias_gradient_folds_every_split(ctx, m, c):
     assert lib.nn_bias_grad(W._p(dy), W._p(db), W._p(ws), bb.value, m, c, ctx.stream) == 0
     want = _host(dy).sum(axis=0)
     assert np.max(np.abs(_host(db) - want) / want) < 640 * 2.0**-24
+
+
+def test_weights_written_by_the_caller_reach_the_convolutions(ctx):
+    """Conv.wb and Conv.wt are the operands of the forward and the backward-data
+    convolution also after a caller has written or replaced them; refresh and
+    the optimizer step renew both, also through tensors handed out before; and
+    a layer that handed them out computes the bits of one that did not."""
+    t = ctx.torch
+    shape, ci, co = (1, 4, 8, 8), 32, 48
+    rng = np.random.default_rng(23)
+    x = _bf_dev(ctx, rng.standard_normal(shape + (ci,)))
+    dy = _f_dev(ctx, rng.standard_normal(shape + (co,)))
+
+    def layer(seed):
+        return W.Conv(ctx, ci, co, np.random.default_rng(seed))
+
+    def results(c):
+        dx = c.backward(x, dy, shape)
+        return [v.clone() for v in (c.forward(x, shape), c.forward_act(x, shape), dx)]
+
+    def same(a, b):
+        return [t.equal(p, q) for p, q in zip(a, b)]
+
+    c, other, twin = layer(1), layer(2), layer(1)
+    ra, rb = results(twin), results(other)
+    assert same(ra, rb) == [False] * 3
+    wb, wt = c.wb, c.wt
+    assert same(results(c), ra) == [True] * 3
+    wb.copy_(other.wb)  # forward follows at once, backward-data reads wt
+    assert same(results(c), [rb[0], rb[1], ra[2]]) == [True] * 3
+    wt.copy_(other.wt)
+    assert same(results(c), rb) == [True] * 3
+    c.refresh()  # both from the master weights again
+    assert same(results(c), ra) == [True] * 3
+    assert t.equal(wb, c.wb) and t.equal(wt, c.wt)
+    for step in (1, 2):  # the gradients of both are those of the last results()
+        c.adam(1e-2, step)
+        twin.adam(1e-2, step)
+        r = results(twin)
+        assert same(results(c), r) == [True] * 3
+        assert same(r, ra) == [False] * 3
+    assert t.equal(wb, twin.wb) and t.equal(wt, twin.wt)
+    c.wb, c.wt, c.b = other.wb, other.wt, other.b
+    assert same(results(c), rb) == [True] * 3
