@@ -466,13 +466,14 @@ class UNet:
     def target_scale(self, used: int):
         """Device factors of the first `used` output channels in the two-grid
         prolongation: the output scale times 4 (velocity) or 2 (density)."""
-        key = (self.scale, used)
-        if self._target_scale[0] != key:
+        key, kept = (self.scale, used), self._target_scale
+        if kept[0] != key:
             lengths = [4.0] * min(used, 3) + [2.0] * max(used - 3, 0)
             t = self.ctx.torch
-            self._target_scale = (key, t.tensor([self.scale * s for s in lengths],
-                                                dtype=t.float32, device=self.ctx.dev))
-        return self._target_scale[1]
+            kept = (key, t.tensor([self.scale * s for s in lengths], dtype=t.float32,
+                                  device=self.ctx.dev))
+            self._target_scale = kept  # (another thread may put its own here meanwhile)
+        return kept[1]
 
     def predict(self, fluid: np.ndarray, used: int = 4) -> np.ndarray:
         """Targets (nz, ny, nx, used) for one fluid mask (edges multiples of

@@ -100,3 +100,34 @@ def test_prolongate2_interpolates_linear_fields_and_scales_lengths():
     inner = (fz > 0) & (fz < 2 * ec - 1) & (fy > 0) & (fy < 2 * ec - 1) & (fx > 0) & (fx < 2 * ec - 1)
     want = np.stack([4 * (cx + 2 * cy), 4 * 3 * cz, 4 * np.ones_like(cx), 2 * (cx - cz)], axis=-1)
     assert np.allclose(f[inner], want[inner], atol=1e-5)
+
+
+def test_target_scale_is_the_callers_own():
+    """Two threads may predict with one network and different channel counts:
+    each gets the factors that it asked for, also where the other's call comes
+    between the look at the kept ones and their use."""
+    from types import SimpleNamespace
+
+    import torch
+
+    class Interleaved(W.UNet):
+        def __init__(self):
+            self.ctx = SimpleNamespace(torch=torch, dev="cpu")
+            self.scale, self.kept, self.other = 0.5, (None, None), False  # (other's call due)
+
+        @property
+        def _target_scale(self):
+            kept = self.kept
+            if self.other:  # another thread's whole call, after this look
+                self.other = False
+                self.target_scale(3)
+            return kept
+
+        @_target_scale.setter
+        def _target_scale(self, v):
+            self.kept = v
+
+    net = Interleaved()
+    for _ in range(3):
+        net.other = True
+        assert net.target_scale(4).tolist() == [2.0, 2.0, 2.0, 1.0]
