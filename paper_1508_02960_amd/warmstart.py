@@ -348,14 +348,19 @@ class UNet:
     # -------------------------------------------------------------- passes
     def _fused(self, shape) -> bool:
         """Whether the fused up- and downsampling calls take boxes of this shape
-        (n, d, h, w): widths in multiples of 8 (up to 1024 in the encoder), fewer
-        than 2^31 elements in the widest concatenation, indices that divide by
-        a 32-bit reciprocal."""
+        (n, d, h, w): widths in multiples of 8 (up to 1024 in the encoder), and
+        at each level fewer than 2^31 elements in its concatenation and indices
+        that divide by a 32-bit reciprocal."""
         w = self.widths
-        m = int(np.prod(shape))
-        return (all(v % 8 == 0 for v in w) and max(w[:3]) <= 1024
-                and m * max(w[0] + w[1], w[1] + w[2], w[2] + w[3]) < 2**31
-                and m * max(shape[1:]) <= 2**32)
+        if any(v % 8 for v in w) or max(w[:3]) > 1024:
+            return False
+        n, *box = (int(v) for v in shape)
+        for lvl in range(3):
+            edges = [v >> lvl for v in box]
+            m = n * int(np.prod(edges, dtype=np.int64))
+            if m * (w[lvl] + w[lvl + 1]) >= 2**31 or m * max(edges) > 2**32:
+                return False
+        return True
 
     def forward(self, x_bf):
         """x_bf: bf16 (n, d, h, w, 8), d, h, w divisible by 8.  Returns the

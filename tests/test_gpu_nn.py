@@ -632,3 +632,27 @@ def test_weights_written_by_the_caller_reach_the_convolutions(ctx):
     assert t.equal(wb, twin.wb) and t.equal(wt, twin.wt)
     c.wb, c.wt, c.b = other.wb, other.wt, other.b
     assert same(results(c), rb) == [True] * 3
+
+
+@pytest.mark.parametrize("widths,shape", [((16, 24, 32, 40), (2, 8, 16, 24)),
+                                          ((32, 64, 128, 256), (1, 184, 184, 184))])
+def test_unet_with_single_calls_gives_the_same_bits(ctx, monkeypatch, widths, shape):
+    """UNet forward and backward through the fused up- and downsampling calls
+    and through the single ones that boxes beyond their limits take: the same
+    output and gradients bit for bit (a small box of odd levels, and one whose
+    voxels times the widest concatenation exceed 2^31)."""
+    t = ctx.torch
+    g = t.Generator(device="cuda").manual_seed(17)
+    net = W.UNet(widths=widths, seed=3, device="cuda")
+    x = W.network_input(net.ctx, (t.rand(shape, generator=g, device="cuda") > 0.3).to(t.uint8))
+    dout = t.randn(shape + (8,), generator=g, device="cuda")
+    runs = []
+    for fused in (True, False):
+        if not fused:
+            monkeypatch.setattr(W.UNet, "_fused", lambda self, s: False)
+        assert net._fused(shape) is fused
+        out = net.forward(x)
+        net.backward(dout)
+        runs.append([out] + [v.clone() for l in net.layers() for v in (l.gw, l.gb)])
+    assert all(t.equal(a, b) for a, b in zip(*runs))
+    assert all(bool(t.isfinite(a).all()) and float(a.abs().max()) > 0 for a in runs[0])

@@ -131,3 +131,26 @@ def test_target_scale_is_the_callers_own():
     for _ in range(3):
         net.other = True
         assert net.target_scale(4).tolist() == [2.0, 2.0, 2.0, 1.0]
+
+
+@pytest.mark.parametrize("widths,shape,fused", [
+    ((32, 64, 128, 256), (4, 64, 64, 64), True),
+    ((32, 64, 128, 256), (1, 184, 184, 184), True),
+    ((32, 64, 128, 256), (1, 256, 256, 256), True),    # 2^32 = voxels times edge
+    ((32, 64, 128, 256), (1, 264, 256, 256), False),
+    ((32, 64, 128, 256), (21, 104, 96, 104), True),    # 2.09e9 elements in the finest level's
+    ((32, 64, 128, 256), (22, 104, 96, 104), False),   # 2.19e9
+    ((8, 16, 512, 1024), (1, 128, 128, 128), True),    # coarser levels: an eighth, a 64th
+    ((8, 16, 2000, 8), (1, 64, 64, 64), False),
+    ((8, 16, 24, 32), (1, 8, 8, 8192), True),          # 2^32 again
+    ((8, 16, 24, 32), (1, 8, 8, 8200), False),
+    ((8, 8, 8, 8192), (1, 256, 256, 256), False),      # 2^18 voxels x 8200 in the coarsest
+    ((12, 16, 24, 32), (1, 8, 8, 8), False),
+])
+def test_fused_passes_cover_what_their_calls_take(widths, shape, fused):
+    """UNet takes the fused up- and downsampling calls wherever these accept
+    every level (nn_upsample_concat: fewer than 2^31 elements of that level's
+    concatenation; nn_pooled_backward_bias: up to 2^32 voxels times edge)."""
+    net = W.UNet.__new__(W.UNet)
+    net.widths = widths
+    assert net._fused(shape) is fused
