@@ -835,6 +835,14 @@ __device__ __forceinline__ C general_wall_value(const S* __restrict__ src,
   }
 }
 
+// Orders the wavefront's LDS accesses before it and those after it, between
+// lanes too (costs no instruction: a wavefront's LDS accesses are done in order).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The general rules for the wall links of a wavefront's nodes, one link per
 // lane.  Only some lanes of a wavefront have links, and each only in some
 // directions; with the rule run per direction under a branch, every direction
@@ -854,8 +862,10 @@ __device__ __forceinline__ void general_walls(const S* __restrict__ src,
                                               const StepParams& p, int x, int y, int z, int c,
                                               uint32_t links, const C (&m1)[4], C* list) {
   const int lane = (int)__lane_id();
-  uint32_t* entry = reinterpret_cast<uint32_t*>(list);
+  typedef uint32_t __attribute__((may_alias)) Entry;
+  Entry* entry = reinterpret_cast<Entry*>(list);
   constexpr int W = sizeof(C) / 4;  // entries sit where their results go
+  wave_lds_sync();                  // (the last plane's results have been taken)
   int total = 0;                    // wavefront-uniform
 #pragma unroll
   for (int k = 1; k < kQ; ++k) {
@@ -866,8 +876,7 @@ __device__ __forceinline__ void general_walls(const S* __restrict__ src,
     if ((links >> k) & 1u) entry[at * W] = (uint32_t)lane | ((uint32_t)k << 8);
     total += __popcll(m);
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_sync();
   for (int i0 = 0; i0 < total; i0 += 64) {
     const int i = i0 + lane;
     const uint32_t e = i < total ? entry[i * W] : (uint32_t)lane;
@@ -882,8 +891,7 @@ __device__ __forceinline__ void general_walls(const S* __restrict__ src,
     }
     if (i < total) list[i] = general_wall_value<S, C>(src, flags, p, lx, ly, z, lc, k, lf, lm);
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_sync();
 }
 
 // The results of general_walls into the pulled values of the links' nodes.

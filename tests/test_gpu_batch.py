@@ -296,3 +296,43 @@ def test_batch_cell_of_a_very_long_row(orc):
     fluid = mask == 0
     err = np.abs(u[:, 0] - uo)[:, fluid]
     assert err.max() <= 1e-5 * np.abs(uo[:, fluid]).max()
+
+
+@pytest.mark.parametrize("storage", ["fp32", "fp64"])
+@pytest.mark.parametrize("wall", ["libb", "qibb", "iebb", "mr"])
+def test_general_walls_in_every_block_shape(storage, wall):
+    """The interpolated rules pass a wavefront's links and their results through
+    one list in LDS, plane after plane of a block: batch blocks of one plane and
+    of eight, of one wavefront and of 16 (FP64: 156 KB of LDS), in plain and
+    graph launches, store the same state; and so do the domain's workgroups."""
+    shape = (16, 16, 128)
+    cells = [dict(spheres=inputs.random_spheres(shape, 30, (2.0, 3.5), seed=410 + i), tau=0.8,
+                  magic=3 / 16, delta_rho=1e-3) for i in range(2)]
+    u0 = inputs.random_velocity((2 * 16, 16, 128), 1e-2, seed=42)
+
+    def state(d, u):
+        d.init_equilibrium(u0=u)
+        d.step(3)
+        d.run_to_residual(0.0, 10)
+        g = d.get_state()
+        d.close()
+        return g
+
+    outs = []
+    for by, zp in [(1, 1), (1, 8), (16, 8), (16, 1)]:
+        b = lbm.Batch(shape, cells, wall=wall, storage=storage, check_interval=5)
+        b.set_shape(by, zp)
+        outs.append(state(b, u0))
+    alone = []
+    for waves, rows in [(1, 1), (16, 4), (16, 16)]:
+        d = lbm.Domain(shape, wall=wall, storage=storage, check_interval=5, **cells[1])
+        d.set_step_shape(waves, rows, False)
+        alone.append(state(d, u0[:, 16:]))
+    for g in outs[1:]:
+        assert np.array_equal(g, outs[0])
+    for g in alone[1:]:
+        assert np.array_equal(g, alone[0])
+    assert np.isfinite(alone[0]).all() and np.abs(alone[0]).max() > 0
+    fluid = alone[0][0] != 0
+    err = np.abs(outs[0][:, 1] - alone[0])[:, fluid].max()
+    assert err <= (1e-5 if storage == "fp32" else 1e-13) * np.abs(alone[0]).max()
