@@ -677,13 +677,18 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 // 16 bytes per active lane from global memory to LDS byte address lds + 16
 // lane, not tracked by the compiler, which would otherwise wait for it before
-// any LDS read: lds_loads_done() before the barrier that publishes them.  M0
-// holds the LDS address; nothing else in the kernels that use this needs it.
+// any LDS read: lds_loads_done() before the barrier that publishes them.  The
+// load takes its LDS address from M0, a reserved register that an asm statement
+// cannot name as clobbered: it is put back, so that what the compiler keeps
+// there holds.
 __device__ __forceinline__ void load_to_lds_async(const void* g, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               :
-               : "s"(lds), "v"(g)
-               : "memory");
+  uint32_t m0;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+      : "=&s"(m0)
+      : "s"(lds), "v"(g)
+      : "memory");
 }
 __device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
