@@ -656,3 +656,16 @@ def test_unet_with_single_calls_gives_the_same_bits(ctx, monkeypatch, widths, sh
         runs.append([out] + [v.clone() for l in net.layers() for v in (l.gw, l.gb)])
     assert all(t.equal(a, b) for a, b in zip(*runs))
     assert all(bool(t.isfinite(a).all()) and float(a.abs().max()) > 0 for a in runs[0])
+
+
+# boxes whose edges leave halo tiles mostly empty (gathered tiles of 64 and 32
+# channels, the last ones partial; a K of 3.4 stages; from packed weights halo
+# tiles for the last), channels that do not fit in LDS (gathered tiles of 16 and
+# 32 channels, 300.4 stages), and odd numbers of channel octets in halo tiles
+@pytest.mark.parametrize("shape,ci,co", [((30, 30, 8, 1), 8, 200), ((12, 30, 17, 1), 120, 100),
+                                         ((40, 30, 20, 1), 8, 24), ((1, 4, 4, 8), 712, 16),
+                                         ((1, 4, 4, 8), 712, 24), ((1, 9, 8, 10), 56, 40),
+                                         ((24, 48, 4, 2), 16, 72)])
+def test_conv_forward_of_thin_boxes_and_odd_octets(ctx, shape, ci, co):
+    test_conv_forward_tiles_match_reference(ctx, shape, ci, co)
+    test_packed_weights_give_the_same_bits(ctx, shape, ci, co)
