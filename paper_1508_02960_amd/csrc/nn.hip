@@ -459,9 +459,10 @@ __global__ __launch_bounds__(256, 2) void conv_fwd_spatial_kernel(const uint16_t
 //
 // These launches are bound by latency and by the weights, which every
 // wavefront reads once in a row (L2 resident): they are loaded U steps ahead.
-// Halo voxels are 2 ci + 16 bytes apart in LDS (8 consecutive ones read at
-// one octet cover all banks) and loaded straight from global memory; the
-// padding lanes load a neighbour's bytes that nothing reads.
+// Halo voxels are an odd number of octets apart in LDS (8 consecutive ones read
+// at one octet then cover all banks) and loaded straight from global memory; the
+// padding lanes of even channel counts load a neighbour's bytes that nothing
+// reads.
 //
 // Against 128-voxel tiles gathered stage by stage (conv_fwd_tiled_kernel), BF16
 // output: 8 -> 32 channels at 64^3 x 4 119 -> 45 us; 128 -> 256 at 8^3 x 4 56
@@ -475,7 +476,7 @@ constexpr int rows_halo() {  // halo voxels of a block's tile
 // LDS bytes: the halo in whole wavefront loads, a zero voxel octet, the table
 template <int MT, int WC>
 size_t rows_lds(int ci) {
-  const size_t halo = (size_t)rows_halo<MT, WC>() * (2 * ci + 16);
+  const size_t halo = (size_t)rows_halo<MT, WC>() * ((ci / 8) | 1) * 16;
   return (halo + 1023) / 1024 * 1024 + 16 + (size_t)((27 * (ci / 8) + 3) / 4 * 4) * 4;
 }
 
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __re
   t /= ty_n;
   const int z0 = (t % tz_n) * WZ;
   const int bn_ = t / tz_n;
-  const int g8 = ci >> 3, gs = g8 + 1;  // octets of a voxel; with its padding
+  const int g8 = ci >> 3, gs = g8 | 1;  // octets of a voxel; with its padding
   const int nq = (HV * gs + 63) >> 6;
   const int octets = 27 * g8, steps = (octets + 3) >> 2;
   unsigned char* zero = Rs + nq * 1024;
