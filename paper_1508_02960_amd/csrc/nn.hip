@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <type_traits>
@@ -1909,39 +1910,63 @@ void launch_rows(const uint16_t* x, const uint16_t* w, const float* bias, void* 
       <<<(unsigned)rows_blocks<MT, WC>(s, cgs), 256, rows_lds<MT, WC>(ci), st>>>(
           x, w, bias, y, s, ci, co, relu, vector_stores<ACT>(y, co));
 }
-// Rows per wavefront: the fewest whose blocks run at once, one per CU (a
-// second block on a CU doubles the time of a latency-bound launch), four for
-// boxes beyond that.  False where gathered tiles are the better kernel: the
-// halo does not fit in LDS; or more than 32 channels in boxes of more blocks,
-// for unpacked weights, whose scattered rows then bound the launch (20^3 x 3,
-// 64 -> 128: 47 against 42 us), and for packed ones in boxes of several rounds
-// of blocks (with one block's halo in LDS a CU waits for the next): more than
-// 512 blocks where only two rows fit (20^3 x 4, 384 -> 128: 204 against 194 us)
-// or the box's edges leave the tiles half empty (11 x 13 x 9 x 4, 128 -> 384: 80
-// against 63 us), more than 800 from 128 channels on (20^3 x 3, 128 -> 256: 129
-// against 90; 672 blocks of 14 x 15 x 15 x 4, 128 -> 384: 86 against 94).  Below
-// 128 channels packed weights win (20^3 x 3, 64 -> 128: 30 against 41 us).
+// Which of the kernel above with 1, 2 or 4 row pairs a wavefront and the gathered
+// tiles takes a box: the least of four estimated times, us.  A launch is whole
+// rounds of the blocks that the 256 CUs hold and the last round's fullest CU;
+// block(k) is the time of k blocks together on a CU, the larger of a block's own
+// latency and what k of them ask of the CU (MFMAs, weights, LDS).  The constants
+// are fits to launches of 1400 random boxes (edges 1 to 96, 8 to 512 channels,
+// thin and half-empty boxes among them), which they give to 8% (gathered tiles
+// 5%).  Halo tiles are taken where they are estimated a fifth ahead: of those
+// 1400 boxes, from packed weights, 10 are then 4 to 9% slower than gathered tiles
+// from unpacked ones, the mean takes 0.46 of their time.  (Limits on the block
+// count in place of the estimates: 75 slower, up to 3.9 times where the edges
+// leave the 8-wide tiles empty: 20 x 51 x 1 x 12, 8 -> 512 channels, 50 against
+// 20 us.)
+//
+// Unpacked weights of 32 channels and more are scattered rows that bound the
+// launch: there the fewest row pairs whose blocks run at once, one per CU, and
+// gathered tiles beyond (20^3 x 3, 64 -> 128: 47 against 42 us).
+template <typename F>
+double launch_time(long long blocks, long long resident, F block) {
+  const long long per = (blocks + 255) / 256, last = per % resident;
+  return (double)(per / resident) * block((double)resident) + (last ? block((double)last) : 0.0);
+}
+template <int MT, int NT, int WC, bool PK>
+double rows_time(const Shape& s, int ci, int co) {
+  const size_t lds = rows_lds<MT, WC>(ci);
+  if (lds > kLdsBytes) return HUGE_VAL;
+  const long long blocks = rows_blocks<MT, WC>(s, (co + 16 * NT * WC - 1) / (16 * NT * WC));
+  if (!PK && ci >= 32) return blocks <= 256 ? MT : HUGE_VAL;  // (an order, not a time)
+  const double steps = k_steps(ci), kb = (double)lds / 1024;
+  const double own = PK ? 0.029 + 0.038 * MT : 0.05 * MT;
+  const double shared = NT * (PK ? 0.0088 * MT + 0.0187 : 0.0187 * MT + 0.0424);
+  const double stage = (PK ? 0.029 : 0.005) * kb, start = PK ? 1.4 : 0.9;
+  return (PK ? 3.1 : 3.9) +
+         launch_time(blocks, std::min<long long>(4, (long long)(kLdsBytes / lds)),
+                     [&](double k) { return start + stage * k + steps * std::max(own, k * shared); });
+}
+double gathered_time(const Shape& s, int ci, int co) {
+  const int nt = co <= 16 ? 1 : (co <= 32 ? 2 : 4);
+  const double stages = (27 * ci + 63) / 64;
+  return 5.6 + launch_time((s.m + 127) / 128 * ((co + 16 * nt - 1) / (16 * nt)), nt == 4 ? 3 : 4,
+                           [&](double k) {
+                             return 4.6 + stages * std::max(0.455 + 0.097 * nt,
+                                                            k * (0.059 * nt + 0.261));
+                           });
+}
+// False where gathered tiles are the better kernel.
 template <int NT, int WC, bool PK, bool ACT>
 bool launch_rows_of(const uint16_t* x, const uint16_t* w, const float* bias, void* y,
                     const Shape& s, int ci, int co, int relu, hipStream_t st) {
-  const int cgs = (co + 16 * NT * WC - 1) / (16 * NT * WC);
-  const bool fit1 = rows_lds<1, WC>(ci) <= kLdsBytes, fit2 = rows_lds<2, WC>(ci) <= kLdsBytes,
-             fit4 = rows_lds<4, WC>(ci) <= kLdsBytes;
-  if (!fit1) return false;
-  const int mt = rows_blocks<1, WC>(s, cgs) <= 256 || !fit2   ? 1
-                 : rows_blocks<2, WC>(s, cgs) <= 256 || !fit4 ? 2
-                                                              : 4;
-  const long long blocks = mt == 1   ? rows_blocks<1, WC>(s, cgs)
-                           : mt == 2 ? rows_blocks<2, WC>(s, cgs)
-                                     : rows_blocks<4, WC>(s, cgs);
-  const long long tile = (4 / WC) * 2 * mt * kRX;  // voxels of a block
-  const bool sparse = blocks / cgs * tile * 2 > 3 * s.m;
-  if (PK ? (ci >= 128 && blocks > 800) || ((ci > 256 || (ci >= 128 && sparse)) && blocks > 512)
-         : ci >= 32 && blocks > 256)
-    return false;
-  if (mt == 1)
+  const double t1 = rows_time<1, NT, WC, PK>(s, ci, co), t2 = rows_time<2, NT, WC, PK>(s, ci, co),
+               t4 = rows_time<4, NT, WC, PK>(s, ci, co);
+  const double t = std::min(t1, std::min(t2, t4));
+  const double limit = !PK && ci >= 32 ? HUGE_VAL : 0.8 * gathered_time(s, ci, co);
+  if (!(t < limit)) return false;
+  if (t == t1)
     launch_rows<1, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
-  else if (mt == 2)
+  else if (t == t2)
     launch_rows<2, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
   else
     launch_rows<4, NT, WC, PK, ACT>(x, w, bias, y, s, ci, co, relu, st);
