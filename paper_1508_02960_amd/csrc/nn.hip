@@ -2109,12 +2109,15 @@ static BwdwPlan bwdw_plan(int n, int d, int h, int w, int ci, int co) {
     sp = std::min<long long>(sp, 256);
     p.splits = (int)sp;
     p.chunks_per_split = (chunks + sp - 1) / sp;
-    if (w % 8 || m >= (1LL << 31)) return p;
+    if (w % 8 || m >= (1LL << 31) || p.chunks_per_split < 2) return p;
     // tiles of whole rows that follow each other in memory (rows of a plane,
     // or whole planes), a multiple of 64 voxels: the largest of 128 to 256
     // whose buffer leaves room for a second block on the CU (single rows of 64
     // are slower than the general kernel, 18 against 15 us: their halo is nine
-    // times the tile)
+    // times the tile).  Splits of one chunk take the general kernel: they would
+    // bring a tile of two chunks or more to LDS and use one (138 random boxes: 11%
+    // slower in the median, 8 x 8 x 8 x 3, 64 -> 32: 15.4 against 10.9 us; of two
+    // chunks 12% faster, of more up to 3 times).
     g.tx = w;
     int vox = 0;
     for (int ty = 1; ty <= h && (long long)ty * w <= 256; ++ty) {

@@ -669,3 +669,14 @@ def test_unet_with_single_calls_gives_the_same_bits(ctx, monkeypatch, widths, sh
 def test_conv_forward_of_thin_boxes_and_odd_octets(ctx, shape, ci, co):
     test_conv_forward_tiles_match_reference(ctx, shape, ci, co)
     test_packed_weights_give_the_same_bits(ctx, shape, ci, co)
+
+
+# splits of two and three chunks of 64 voxels over tiles of three and four 8 x 8
+# planes, two of 16 x 8, 16 x 16, 8 and 3 rows of a plane, with partial channel
+# tiles on either side and on both, in one LDS buffer and in two
+@pytest.mark.parametrize("shape,ci,co", [((1, 52, 8, 8), 96, 96), ((1, 12, 16, 8), 104, 136),
+                                         ((2, 10, 8, 24), 96, 72), ((1, 6, 16, 32), 72, 168),
+                                         ((1, 3, 18, 64), 88, 96), ((3, 7, 16, 16), 160, 24),
+                                         ((5, 6, 8, 8), 128, 96)])
+def test_conv_weight_gradient_in_tiles_of_rows(ctx, shape, ci, co):
+    test_conv_weight_gradient_tiles_match_reference(ctx, shape, ci, co)
