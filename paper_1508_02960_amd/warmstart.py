@@ -666,10 +666,13 @@ def predict_two_grid_device(net, spheres, edge: int, out=None, used: int = 4):
     lib = _nn()
     ctx = net.ctx
     ec = edge // 2
-    if edge % 2 or edge > 2048:
-        x = network_input(ctx, coarse_fluid(spheres, edge)[None].astype(np.uint8))
+    sp = np.reshape(spheres, (-1, 4))
+    wide = sp.dtype == np.float64 or (sp.dtype.kind in "iu" and sp.dtype.itemsize >= 4)
+    if edge % 2 or edge > 2048 or not wide:
+        # (coarse_fluid squares the radii of other types in their own precision)
+        x = network_input(ctx, coarse_fluid(sp, edge)[None].astype(np.uint8))
     else:
-        sp = np.ascontiguousarray(np.reshape(spheres, (-1, 4)), np.float64)
+        sp = np.ascontiguousarray(sp, np.float64)
         x = ctx.bf(1, ec, ec, ec, IN_CH)
         _chk(lib.nn_coarse_pack_input(sp.ctypes.data_as(C.c_void_p), len(sp), edge, _p(x),
                                       ctx.stream), "coarse input")

@@ -153,3 +153,20 @@ def test_coarse_pack_input_matches_host(edge, n):
     assert ctx.torch.equal(x, want)
     assert W._nn().nn_coarse_pack_input(sp.ctypes.data_as(C.c_void_p), n, edge + 1, W._p(x),
                                         ctx.stream) != 0
+
+
+@pytest.mark.parametrize("rows", [
+    np.array([[14.463912, 16.5, 16.5, 3.963912]], np.float32),  # a node between r^2 in 24 and 53 bits
+    np.array([[14.463912, 16.5, 16.5, 3.963912]], np.float32).astype(np.float64),
+    np.array([[14, 16, 16, 4], [3, 30, 9, 5]]), np.array([[14, 16, 16, 9]], np.int8),
+    [14.5, 16.5, 16.5, 4.0]])
+def test_two_grid_prediction_takes_spheres_of_any_type(rows):
+    """The mask of the two-grid start is coarse_fluid's for rows of every type:
+    single-precision radii are squared in single precision there, which can put
+    a node on the other side of the surface."""
+    ctx_net = W.UNet(widths=(8, 16, 16, 32), seed=5, device="cuda")
+    got = W.predict_two_grid(ctx_net, rows, 32)
+    want = W.prolongate2(ctx_net.predict(W.coarse_fluid(rows, 32)))
+    assert np.max(np.abs(got - want)) <= 1e-5 * np.max(np.abs(want))
+    if isinstance(rows, np.ndarray) and rows.dtype == np.float32:
+        assert (W.coarse_fluid(rows, 32) != W.coarse_fluid(rows.astype(np.float64), 32)).sum() == 1
