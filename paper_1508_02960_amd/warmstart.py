@@ -354,11 +354,10 @@ class UNet:
         w = self.widths
         if any(v % 8 for v in w) or max(w[:3]) > 1024:
             return False
-        n, *box = (int(v) for v in shape)
+        n, d, h, wd = (int(v) for v in shape)
         for lvl in range(3):
-            edges = [v >> lvl for v in box]
-            m = n * int(np.prod(edges, dtype=np.int64))
-            if m * (w[lvl] + w[lvl + 1]) >= 2**31 or m * max(edges) > 2**32:
+            m = n * (d >> lvl) * (h >> lvl) * (wd >> lvl)
+            if m * (w[lvl] + w[lvl + 1]) >= 2**31 or m * (max(d, h, wd) >> lvl) > 2**32:
                 return False
         return True
 
