@@ -93,9 +93,9 @@ __device__ __forceinline__ long long neighbour(int n, int z, int y, int x, int t
 // 4 q.. of K = 27 ci, lane l's 16 bytes (row l % 16, octet l / 16) at 16 l; zeros
 // past the last row or octet.  A fragment is then one 1 KB run, where the
 // rows of w[co][27][ci] give 16 segments of 64 bytes (the
-// weight reads of the spatial kernel: 192 -> 64 channels at 32^3 x 4 101 -> 70 us,
-// 1250 TFLOP/s; 96 -> 32 at 64^3 x 4 215 -> 190 us; of the halo kernel: 128 -> 256 at
-// 8^3 x 4 31 -> 14 us, 384 -> 128 at one 16^3 box 83 -> 34 us).
+// weight reads of the spatial kernel: 192 -> 64 channels at 32^3 x 4 105 -> 82 us,
+// 1050 TFLOP/s; 96 -> 32 at 64^3 x 4 200 -> 187 us; of the halo kernel: 128 -> 256 at
+// 8^3 x 4 30 -> 14 us, 384 -> 128 at one 16^3 box 83 -> 34 us).
 __host__ __device__ __forceinline__ int k_steps(int ci) { return (27 * (ci >> 3) + 3) >> 2; }
 
 // ---------------------------------------------------------------- forward
@@ -274,9 +274,9 @@ __global__ __launch_bounds__(256) void conv_fwd_tiled_kernel(const uint16_t* __r
 // permuted by (hx >> 1) ^ 2 R (mod 4), so that 8 consecutive voxels of a row
 // read at one octet cover all banks.
 //
-// 96 -> 32 channels at 64^3 x 4 (174 GFLOP), BF16 output: 323 -> 215 us (808
-// TFLOP/s) against one LDS read per tap and row, 190 us (916) from packed
-// weights; 192 -> 64 at 32^3 x 4: 172 -> 101, packed 70 us (1250 TFLOP/s).
+// 96 -> 32 channels at 64^3 x 4 (174 GFLOP), BF16 output: 316 -> 200 us (870
+// TFLOP/s) against one LDS read per tap and row, 187 us (930) from packed
+// weights; 192 -> 64 at 32^3 x 4: 182 -> 105, packed 82 us (1050 TFLOP/s).
 constexpr int kTZ = 4, kTY = 8, kTX = 8;
 constexpr int kCC = 32;                 // channels per chunk
 
@@ -466,8 +466,8 @@ __global__ __launch_bounds__(256, 2) void conv_fwd_spatial_kernel(const uint16_t
 // reads.
 //
 // Against 128-voxel tiles gathered stage by stage (conv_fwd_tiled_kernel), BF16
-// output: 8 -> 32 channels at 64^3 x 4 119 -> 45 us; 128 -> 256 at 8^3 x 4 56
-// -> 31 us, 14 from packed weights; 384 -> 128 at one 16^3 box 147 -> 83, 34 us.
+// output: 8 -> 32 channels at 64^3 x 4 117 -> 40 us; 128 -> 256 at 8^3 x 4 56
+// -> 30 us, 14 from packed weights; 384 -> 128 at one 16^3 box 145 -> 83, 34 us.
 constexpr int kRX = 8, kRHX = kRX + 2;  // x extent of a tile, of its halo
 
 template <int MT, int WC>
@@ -669,9 +669,12 @@ __global__ __launch_bounds__(256) void conv_fwd_rows_kernel(const uint16_t* __re
 // addresses (xtab), and a load fills whole kilobytes.
 //
 // Against transposed copies written to LDS two bytes at a time, and the general
-// kernel for boxes of few tiles (bit-identical, fold included): 96 -> 32 channels
-// at 64^3 x 4 642 -> 241 us (721 TFLOP/s), 192 -> 64 at 32^3 x 4 314 -> 125 us, 384
-// -> 128 at 16^3 x 4 318 -> 106 us, 128 -> 256 at 8^3 x 4 49 -> 27 us.
+// kernel for boxes of few tiles (bit-identical), whole calls with their fold in a
+// short loop: 96 -> 32 channels at 64^3 x 4 641 -> 245 us, 192 -> 64 at 32^3 x 4 311
+// -> 123 us, 384 -> 128 at 16^3 x 4 317 -> 105 us, 128 -> 256 at 8^3 x 4 49 -> 27 us.
+// In a training step, where the clock is up, this kernel alone takes 195 to 207
+// us (840 to 890 TFLOP/s) for the first and 109 to 113 us for the second, their
+// folds 10 us each.
 struct BwdwTiles {
   int tz, ty, tx;      // tile
   int ntx, nty, ntz;   // tiles per row, per plane of rows, per box
@@ -1159,7 +1162,7 @@ __global__ __launch_bounds__(256) void fold_splits_kernel(const float* __restric
 // into part[b][c].  Thread (g, ch) of the G = 256 / c groups handles
 // channel ch (consecutive threads read consecutive channels of a voxel) and
 // voxels g, g + G, ...; the groups are folded in a fixed order in LDS, and
-// fold_splits_kernel sums the blocks in order (deterministic).
+// fold_bias_kernel sums the blocks in order (deterministic).
 __global__ __launch_bounds__(256) void bias_grad_part_kernel(const float* __restrict__ dy,
                                                              float* __restrict__ part,
                                                              long long m, int c,
